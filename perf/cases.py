@@ -5,7 +5,8 @@ one megabyte to the 0.25-degree grid.
 
 listed() are the fixed cases, draw() gives more of the same ranges; prepare() makes what a program
 holds before the call, run() is one pass through the public entry points, work() the bytes and
-operations it cannot do without, tolerance() how far another correct implementation may differ.
+operations it cannot do without, tolerance() how far another correct implementation may differ,
+exact() the values in 64 bits.
 """
 import ctypes
 import math
@@ -324,6 +325,150 @@ def run(s):
     g = B.aeris_swiglu_fwd(s["uv"])
     duv = B.aeris_swiglu_bwd(s["uv"], s["dg"])
     return dict(h=h, r=r, dx=dx, dw=dw, dgamma=dgamma, dbeta=dbeta, out=out, dy=dy, dalpha=dalpha, g=g, duv=duv)
+
+
+# ------------------------------------------------------------------------------------- 64-bit values
+def _partition(case, windows=None):
+    """(grid index, region) of every window's tokens, [windows, tokens]: the cyclic shift, and the
+    seam rules of the mask."""
+    H, W, wh, ww, sh, sw = [case[k] for k in ("H", "W", "wh", "ww", "sh", "sw")]
+    n = torch.arange((H // wh) * (W // ww), device="cuda") if windows is None else torch.tensor(windows, device="cuda")
+    t = torch.arange(wh * ww, device="cuda")
+    yh = (n // (W // ww) * wh)[:, None] + (t // ww)[None]
+    xh = (n % (W // ww) * ww)[:, None] + (t % ww)[None]
+    region = torch.zeros_like(yh)
+    if case["mask"] != "none":
+        region += 2 * (yh >= H - sh) * (sh > 0)
+    if case["mask"] == "swin":
+        region += (xh >= W - sw) * (sw > 0)
+    last = ((yh >= H - wh).int() * 2 + (xh >= W - ww).int()) * 4      # other windows never meet a seam
+    return (yh + sh) % H * W + (xh + sw) % W, region + last
+
+
+def _attention64(case, q, k, v, do=None, windows=None):
+    """Attention inside the windows and, with dO, its gradients; q .. dO are [B, H, W, heads, d]."""
+    idx, region = _partition(case, windows)
+    nb, H, W, nh, d = q.shape
+    n, T = idx.shape
+    flat = lambda t: t.reshape(nb, H * W, nh, d)
+    new = lambda: torch.zeros(nb, H * W, nh, d, dtype=torch.float64, device="cuda")
+    o, lse = new(), torch.zeros(nb, nh, H * W, dtype=torch.float64, device="cuda")
+    grads = [new() for _ in range(3)] if do is not None else []
+    step = max(1, int(1.7e9 / (nh * T * T * 8)))
+    for b in range(nb):
+        for i in range(0, n, step):
+            at, reg = idx[i:i + step], region[i:i + step]
+            rows = lambda t: flat(t)[b][at].permute(0, 2, 1, 3).to(torch.float64, memory_format=torch.contiguous_format)
+            turned = lambda t: t.transpose(-1, -2).contiguous()
+            Q, K, V = rows(q), rows(k), rows(v)
+            P = Q @ turned(K)
+            P.mul_(d ** -0.5)
+            if bool((reg != reg[:, :1]).any()):
+                P.masked_fill_((reg[:, :, None] != reg[:, None, :])[:, None], -math.inf)
+            L = torch.logsumexp(P, -1)
+            P.sub_(L[..., None]).exp_()
+            O = P @ V
+            o[b][at] = O.permute(0, 2, 1, 3)
+            lse[b][:, at] = L.permute(1, 0, 2)
+            if do is None:
+                continue
+            dO = rows(do)
+            grads[2][b][at] = (turned(P) @ dO).permute(0, 2, 1, 3)
+            dS = dO @ turned(V)
+            dS.sub_((dO * O).sum(-1, keepdim=True)).mul_(P).mul_(d ** -0.5)
+            grads[0][b][at] = (dS @ K).permute(0, 2, 1, 3)
+            grads[1][b][at] = (turned(dS) @ Q).permute(0, 2, 1, 3)
+    return (o.view(q.shape), lse.view(nb, nh, H, W)) + tuple(g.view(q.shape) for g in grads)
+
+
+def _rotated64(case, t, back=False):
+    """The rotary embedding with positions inside the window: even channel pairs turn with the
+    longitude, odd ones with the latitude."""
+    H, W, d = case["H"], case["W"], case["d"]
+    theta = ROPE_BASE ** (-torch.arange(d // 4, dtype=torch.float64, device="cuda") / (d // 4))
+    y = (torch.arange(H, device="cuda") - case["sh"]) % H % case["wh"]
+    x = (torch.arange(W, device="cuda") - case["sw"]) % W % case["ww"]
+    phi = torch.stack([(x[:, None] * theta)[None].expand(H, -1, -1),
+                       (y[:, None] * theta)[:, None].expand(-1, W, -1)], -1).reshape(H, W, 1, d // 2)
+    c, s = phi.cos(), -phi.sin() if back else phi.sin()
+    a, b = t[..., 0::2].double(), t[..., 1::2].double()
+    return torch.stack([a * c - b * s, a * s + b * c], -1).reshape(t.shape)
+
+
+class _RotaryAttention64(torch.autograd.Function):
+    @staticmethod
+    def forward(ctx, q, k, v, case):
+        ctx.case = case
+        ctx.save_for_backward(q, k, v)
+        return _attention64(case, _rotated64(case, q), _rotated64(case, k), v)[0]
+
+    @staticmethod
+    def backward(ctx, do):
+        q, k, v = ctx.saved_tensors
+        case = ctx.case
+        _, _, dq, dk, dv = _attention64(case, _rotated64(case, q), _rotated64(case, k), v, do)
+        return _rotated64(case, dq, True), _rotated64(case, dk, True), dv, None
+
+
+def _norm64(x, w, gamma, beta, rows):
+    n = x * torch.rsqrt((x * x).mean(1, keepdim=True) + EPS)
+    per_row = lambda t: t.repeat_interleave(rows, 0)
+    return n * w * (1 + per_row(gamma)) + per_row(beta)
+
+
+def _silu_gate64(uv):
+    u, v = uv.chunk(2, 1)
+    return u * torch.sigmoid(u) * v
+
+
+def exact(case, seed):
+    """What run() returns, in 64 bits; None where that would take long or not fit."""
+    kind, amount = case["kind"], work(case)
+    if amount["flops"] > 1.2e14 or (kind == "layer_ops" and amount["bytes"] > 1e10):
+        return None
+    s = prepare(case, seed)
+    if kind == "attn_fwd":
+        return _attention64(case, *s["t"])
+    if kind == "attn_train":
+        return dict(zip(("o", "lse", "dq", "dk", "dv"), _attention64(case, *s["t"])))
+    if kind == "rope_share":
+        q, k, v, do = s["t"]
+        o, lse, dq, dk, dv = _attention64(case, _rotated64(case, q), _rotated64(case, k), v, do, _share(case))
+        return dict(o=o, lse=lse, dq=_rotated64(case, dq, True), dk=_rotated64(case, dk, True), dv=dv)
+    p = {n: t.double() for n, t in s.items() if torch.is_tensor(t) and t.dtype != torch.uint8}
+    s.clear()
+    if kind == "proj_fwd":
+        h = _norm64(p["x"], p["w"], p["gamma"], p["beta"], case["rows"])
+        return dict(qkv=h @ p["wqkv"].t(), y=p["x"] @ p["wo"].t(), g=_silu_gate64(h @ p["wup"].t()),
+                    y2=p["g"] @ p["wdown"].t())
+    if kind == "proj_bwd":
+        return dict(dx=p["dy"] @ p["w"], dw=p["dy"].t() @ p["x"])
+    if kind == "layer_ops":
+        rows, x = case["rows"], p["x"].requires_grad_()
+        par = [p[n].requires_grad_() for n in ("w", "gamma", "beta")]
+        h = _norm64(x, *par, rows)
+        dx, dw, dgamma, dbeta = torch.autograd.grad(h, [x] + par, p["d"])
+        y, alpha, uv = [p[n].requires_grad_() for n in ("y", "alpha", "uv")]
+        out = x + alpha.repeat_interleave(rows, 0) * y
+        dy, dalpha = torch.autograd.grad(out, [y, alpha], p["d"])
+        g = _silu_gate64(uv)
+        r = torch.rsqrt((x * x).mean(1) + EPS)
+        return {n: t.detach() for n, t in dict(
+            h=h, r=r, dx=dx + y, dw=dw, dgamma=dgamma, dbeta=dbeta, out=out, dy=dy, dalpha=dalpha, g=g,
+            duv=torch.autograd.grad(g, uv, p["dg"])[0]).items()}
+    rows, C = case["H"] * case["W"], case["heads"] * case["d"]
+    for n, t in p.items():
+        t.requires_grad_(n != "dout")
+    grid = (case["B"], case["H"], case["W"], case["heads"], case["d"])
+    per_row = lambda t: t.repeat_interleave(rows, 0)
+    qkv = _norm64(p["x"], p["w1"], p["g1"], p["b1"], rows) @ p["wqkv"].t()
+    a = _RotaryAttention64.apply(*[t.reshape(grid) for t in qkv.chunk(3, 1)], case)
+    x1 = p["x"] + per_row(p["a1"]) * (a.reshape(-1, C) @ p["wo"].t())
+    g = _silu_gate64(_norm64(x1, p["w2"], p["g2"], p["b2"], rows) @ p["wup"].t())
+    out = x1 + per_row(p["a2"]) * (g @ p["wdown"].t())
+    names = ("x", "wqkv", "wo", "wup", "wdown", "w1", "g1", "b1", "a1", "w2", "g2", "b2", "a2")
+    return dict([("out", out.detach())] + [("d" + n, t) for n, t in zip(
+        names, torch.autograd.grad(out, [p[n] for n in names], p["dout"]))])
 
 
 # ------------------------------------------------------------------------------------- accounting
