@@ -256,45 +256,76 @@ __global__ __launch_bounds__(kRowThreads) void rmsnorm_adaln_bwd_kernel(
   write_partials<2, K>(acc, red, C, partial);
 }
 
-// Second stage of the sums over tokens.  One workgroup per 64 channels; thread (c, part) adds
-// the partial rows part, part + 4, ... of a sample, the four parts are added in order.
+// Second stage of the sums over tokens.  A workgroup owns 16 channels (64 bytes of every partial
+// row, four floats per thread); its blockDim / 4 thread groups add the partial rows part,
+// part + parts, ... of a sample, the groups of a wave are added by a butterfly, the waves in
+// order: a fixed order, so the sums are bitwise reproducible.
 // mode 0 (RMSNorm backward, A = 2): dbeta = sum B, dgamma = w sum A, dw = sum_b (1+gamma_b) sum A.
 // mode 1 (gate backward, A = 1):    dalpha = sum A.
-__global__ __launch_bounds__(256) void column_sums_finish_kernel(
+// Bound by the latency of its dependent loads, not by the 33.5 MB they move at 2048 channels:
+// hence narrow column groups (128 workgroups at 2048 channels) and up to 256 rows in flight per
+// group.  Measured at 2048 channels, 2048 partial rows: 161 us with 64 columns and four rows in
+// flight per workgroup, 15 us so (128 channels, 216 rows of two samples: 32 and 6 us).
+constexpr int kFinishCols = 16;
+
+__global__ __launch_bounds__(1024) void column_sums_finish_kernel(
     const float* __restrict__ partial, int n_samples, int cps, int C, int mode,
     const float* __restrict__ w, const float* __restrict__ gamma, float* __restrict__ out0,
     float* __restrict__ out1, float* __restrict__ out_w) {
-  __shared__ float red[2][4][64];
-  const int cx = threadIdx.x & 63, part = threadIdx.x >> 6;
-  const int c = blockIdx.x * 64 + cx;
+  __shared__ __align__(16) float red[2][16][2][kFinishCols];   // [sample parity][wave][A or B][column]
+  const int quad = threadIdx.x & 3, part = threadIdx.x >> 2, parts = blockDim.x >> 2;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
+  const int c = blockIdx.x * kFinishCols + quad * 4;     // C is a multiple of 8: four valid or none
   const int A = mode == 0 ? 2 : 1;
   float dw_acc = 0.f;
   for (int b = 0; b < n_samples; ++b) {
-    float a0 = 0.f, a1 = 0.f;
+    f32x4 a[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
     if (c < C) {
-      for (int k = part; k < cps; k += 4) {
-        const float* row = partial + ((int64_t)(b * cps + k) * A) * C;
-        a0 += row[c];
-        if (A == 2) a1 += row[C + c];
+      const float* base = partial + (int64_t)b * cps * A * C + c;
+      if (A == 2) {
+#pragma unroll 4
+        for (int k = part; k < cps; k += parts) {
+          a[0] += *reinterpret_cast<const f32x4*>(base + (int64_t)k * 2 * C);
+          a[1] += *reinterpret_cast<const f32x4*>(base + (int64_t)k * 2 * C + C);
+        }
+      } else {
+#pragma unroll 4
+        for (int k = part; k < cps; k += parts)
+          a[0] += *reinterpret_cast<const f32x4*>(base + (int64_t)k * C);
       }
     }
-    red[0][part][cx] = a0;
-    red[1][part][cx] = a1;
+#pragma unroll
+    for (int m = 4; m < 64; m <<= 1)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        a[0][i] += __shfl_xor(a[0][i], m, 64);
+        a[1][i] += __shfl_xor(a[1][i], m, 64);
+      }
+    auto& slot = red[b & 1];
+    if (lane < 4) {
+      *reinterpret_cast<f32x4*>(&slot[wave][0][quad * 4]) = a[0];
+      *reinterpret_cast<f32x4*>(&slot[wave][1][quad * 4]) = a[1];
+    }
+    // one barrier per sample: this sample's slot is written again two samples later, behind the
+    // barrier of the sample in between
     __syncthreads();
-    if (part == 0 && c < C) {
-      const float s0 = ((red[0][0][cx] + red[0][1][cx]) + red[0][2][cx]) + red[0][3][cx];
-      const float s1 = ((red[1][0][cx] + red[1][1][cx]) + red[1][2][cx]) + red[1][3][cx];
+    const int cf = blockIdx.x * kFinishCols + threadIdx.x;
+    if (threadIdx.x < kFinishCols && cf < C) {
+      float s0 = slot[0][0][threadIdx.x], s1 = slot[0][1][threadIdx.x];
+      for (int v = 1; v < waves; ++v) {
+        s0 += slot[v][0][threadIdx.x];
+        s1 += slot[v][1][threadIdx.x];
+      }
       if (mode == 0) {
-        if (out1 != nullptr) out1[(int64_t)b * C + c] = s1;                 // dbeta
-        if (out0 != nullptr) out0[(int64_t)b * C + c] = w[c] * s0;          // dgamma
-        dw_acc = __builtin_fmaf(1.f + gamma[(int64_t)b * C + c], s0, dw_acc);
+        if (out1 != nullptr) out1[(int64_t)b * C + cf] = s1;                 // dbeta
+        if (out0 != nullptr) out0[(int64_t)b * C + cf] = w[cf] * s0;         // dgamma
+        dw_acc = __builtin_fmaf(1.f + gamma[(int64_t)b * C + cf], s0, dw_acc);
+        if (b == n_samples - 1 && out_w != nullptr) out_w[cf] = dw_acc;
       } else if (out0 != nullptr) {
-        out0[(int64_t)b * C + c] = s0;                                      // dalpha
+        out0[(int64_t)b * C + cf] = s0;                                      // dalpha
       }
     }
-    __syncthreads();
   }
-  if (mode == 0 && part == 0 && c < C && out_w != nullptr) out_w[c] = dw_acc;
 }
 
 // ---------------------------------------------------------------------------------------
@@ -466,6 +497,10 @@ int vectors_per_lane(int channels) {
   return v <= 1 ? 1 : v <= 2 ? 2 : v <= 4 ? 4 : 8;
 }
 
+dim3 finish_grid(int channels) { return dim3((channels + kFinishCols - 1) / kFinishCols); }
+// 256 rows in flight per group of columns where a sample has that many partial rows, else 64
+dim3 finish_block(int cps) { return dim3(cps > 64 ? 1024 : 256); }
+
 int status(int launch_rc) { return launch_rc == 0 ? AERIS_OK : AERIS_ERR_HIP_LAUNCH; }
 
 // Calls f(Const<K>) for the K that fits `channels`.
@@ -556,7 +591,7 @@ extern "C" int aeris_rmsnorm_adaln_bwd_residual(const void* x, const float* w, c
   });
   if (rc != 0) return AERIS_ERR_HIP_LAUNCH;
   if (dw || dgamma || dbeta) {
-    return status(launch_kernel(column_sums_finish_kernel, dim3((channels + 63) / 64), dim3(256), 0,
+    return status(launch_kernel(column_sums_finish_kernel, finish_grid(channels), finish_block(cps), 0,
                                 st, partial, n_samples, cps, channels, 0, w, gamma, dgamma, dbeta,
                                 dw));
   }
@@ -615,7 +650,7 @@ extern "C" int aeris_gate_residual_bwd(const void* y, const float* alpha, const 
   });
   if (rc != 0) return AERIS_ERR_HIP_LAUNCH;
   if (dalpha) {
-    return status(launch_kernel(column_sums_finish_kernel, dim3((channels + 63) / 64), dim3(256), 0,
+    return status(launch_kernel(column_sums_finish_kernel, finish_grid(channels), finish_block(cps), 0,
                                 st, partial, n_samples, cps, channels, 1, nullptr, nullptr, dalpha,
                                 nullptr, nullptr));
   }

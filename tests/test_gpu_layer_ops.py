@@ -200,6 +200,17 @@ def test_gate_residual_forward_and_backward(nb, rps, C):
     assert torch.equal(g2.view(torch.int16), tdy.view(torch.int16))
 
 
+@pytest.mark.parametrize("nb,rps,C", [
+    (1, 256, 40),       # 64 partial rows: the last size with 64 row groups; 2.5 column groups
+    (1, 260, 24),       # 65 partial rows: 256 row groups, most of them empty
+    (3, 2733, 8),       # 683 partial rows per sample: a ragged third turn, half a column group
+    (1, 9000, 72),      # the largest number of partial rows
+])
+def test_sums_over_tokens_at_the_edges_of_the_second_stage(nb, rps, C):
+    test_rmsnorm_adaln_forward_and_backward(nb, rps, C)
+    test_gate_residual_forward_and_backward(nb, rps, C)
+
+
 @pytest.mark.parametrize("n,F", [(7, 8), (33, 24), (100, 520), (64, 2048), (3, 8192), (1000, 1024)])
 def test_swiglu_forward_and_backward(n, F):
     uvb, uv64 = activations(600 + F, n, 2 * F)
