@@ -328,10 +328,9 @@ extern "C" int aeris_linear_bwd(const void* x, const void* weight, const void* d
     p.w = wt;
     p.y = static_cast<bf16_t*>(dx);
     p.rows_per_sample = n_rows;
-    p.m_tiles = (int)((n_rows + 255) / 256);
+    p.n_samples = 1;
     p.K = out_features;
     p.F = channels;
-    p.n_tiles = (channels + 255) / 256;
     if (launch_projection_gemm(p, st) != 0) return AERIS_ERR_HIP_LAUNCH;
   }
   if (dweight) {

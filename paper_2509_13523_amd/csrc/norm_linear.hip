@@ -11,7 +11,8 @@
 // per-sample bias beta_b W^T.  The SwiGLU gate is a second epilogue: a workgroup's tile holds
 // matching u and v columns, so g = silu(u) v is formed on the accumulators.
 //
-// GEMM kernel: one workgroup of eight wavefronts per 256 x 256 output tile, 64 channels per
+// GEMM kernel: one workgroup of eight wavefronts per 256 x 256 output tile (four per 128 x 128 or
+// two per 64 x 64 where there are too few rows for that, see choose_gemm_tile), 64 channels per
 // step, both operands K-contiguous ("NT").  Operand tiles go global -> LDS directly
 // (global_load_lds_dwordx4), two stages of 64 KB, 16-byte chunks XOR-swizzled so that the
 // row-major ds_read_b128 operand fetches are conflict free; v_mfma_f32_32x32x16_bf16 with the
@@ -30,40 +31,81 @@
 namespace aeris {
 namespace {
 
-constexpr int kBM = 256;                 // token rows per workgroup tile
-constexpr int kBN = 256;                 // weight rows (output features) per workgroup tile
 constexpr int kBK = 64;                  // channels per step
-constexpr int kGemmWaves = 8;
-constexpr int kPartBytes = kBN * kBK * 2;            // 32 KB: weight rows, then token rows
-constexpr int kStageBytes = 2 * kPartBytes;
-using Sub = Tile<64, kGemmWaves>;        // 64 rows x 64 channels, swizzled chunks
+using Sub = Tile<64, 8>;                 // chunk swizzle of rows of 64 channels
 
-// Workgroup id -> (token tile, feature tile).  Consecutive ids go to the eight XCDs in turn;
-// the 32 workgroups an XCD runs at a time are 8 token tiles x 4 feature tiles, so every
-// operand tile that arrives in that XCD's L2 serves 4 or 8 workgroups.
+// A workgroup tile of WM x WN wavefronts, each NB * 32 token rows x 64 features, and kStages
+// operand stages (weight rows, then token rows) in the LDS.
+template <int WM_, int WN_, int NB_, int STAGES_>
+struct GemmShape {
+  static constexpr int WM = WM_, WN = WN_, NB = NB_, kStages = STAGES_;
+  static constexpr int kWaves = WM * WN;
+  static constexpr int kBM = WM * NB * 32;             // token rows
+  static constexpr int kBN = WN * 64;                  // weight rows (output features)
+  static constexpr int kPartBytes = kBN * kBK * 2;     // weight rows of a stage
+  static constexpr int kStageBytes = kPartBytes + kBM * kBK * 2;
+  static constexpr int kPitch = 144;                   // epilogue rows: 128 bytes, on different banks
+  static constexpr int kEpilogueBytes = kWaves * NB * 32 * kPitch;
+  static constexpr int kSmem = kStages * kStageBytes > kEpilogueBytes ? kStages * kStageBytes : kEpilogueBytes;
+  // every wave issues four weight-row and four token-row copies of a stage
+  static_assert(kBN == 32 * kWaves && kBM == 32 * kWaves && kWaves % 2 == 0);
+};
+using GemmLarge = GemmShape<2, 4, 4, 2>;   // 256 x 256, one workgroup per CU
+using GemmMedium = GemmShape<2, 2, 2, 2>;  // 128 x 128, two workgroups per CU
+using GemmSmall = GemmShape<2, 1, 1, 4>;   // 64 x 64, two workgroups per CU, three stages in flight
+
+// Workgroup id -> (token tile, feature tile); false if the id has no tile.  Tiles are walked in
+// groups of eight token tiles, feature tile by feature tile, so that the 32 tiles an XCD runs at a
+// time are 8 token tiles x 4 feature tiles and every operand tile that arrives in that XCD's L2
+// serves 4 or 8 workgroups.  Which token tiles an XCD owns: see interleave_tiles.
 __device__ __forceinline__ bool gemm_tile(const GemmParams& p, int& mt, int& nt) {
-  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
   const int per_group = 8 * p.n_tiles;
-  const int group = slot / per_group, rem = slot - group * per_group;
-  nt = rem >> 3;
-  mt = ((group * 8 + (rem & 7)) << 3) + xcd;
-  return mt < p.m_tiles;
+  if (p.interleave) {          // every eighth
+    const int slot = blockIdx.x >> 3;
+    const int group = slot / per_group, rem = slot - group * per_group;
+    nt = rem >> 3;
+    mt = ((group * 8 + (rem & 7)) << 3) + (blockIdx.x & 7);
+    return mt < p.m_tiles;
+  }
+  const int id = xcd_contiguous(p.m_tiles * p.n_tiles);
+  const int group = id / per_group, rem = id - group * per_group;
+  const int left = p.m_tiles - group * 8, gm = left < 8 ? left : 8;
+  nt = rem / gm;
+  mt = group * 8 + (rem - nt * gm);
+  return true;
+}
+
+// Whether the XCDs take the token tiles in turn (the grid is then padded to 64 token tiles), or
+// each a contiguous range of them (no padding).  Padding hurts small grids out of proportion:
+// workgroups are dealt to the shader engines of an XCD in turn, idle ones included, and 237 tiles
+// (20011 x 2304 -> 768) left 9 workgroups on engines of 8 CUs while others had 6: 104 us with a
+// second round, 63 without padding.  Where it is no issue, contiguous ranges are faster for
+// medium contractions (172800 x 2048 -> 6144: 3481 us against 3661; -> 2 x 5504 gated: 6869
+// against 7336) and slower for long and short ones (6144 -> 2048: 3691 against 3577,
+// 32400 x 1024 -> 2 x 2752 gated: 401 against 392).
+bool interleave_tiles(long long m_tiles, int K) {
+  const long long padding = (m_tiles + 63) / 64 * 64 - m_tiles;
+  return padding * 16 <= m_tiles && (K < 1536 || K > 4096);
 }
 inline unsigned gemm_grid(const GemmParams& p) {
-  return 8u * (unsigned)((p.m_tiles + 63) / 64) * 8u * (unsigned)p.n_tiles;
+  const unsigned m = (unsigned)p.m_tiles;
+  return (p.interleave ? (m + 63) / 64 * 64 : m) * (unsigned)p.n_tiles;
 }
 
 __device__ __forceinline__ float silu(float u) {
   return u * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(-u * kLog2e));
 }
 
-__global__ __launch_bounds__(kGemmWaves * 64, 1) void norm_linear_gemm_kernel(GemmParams p) {
+template <class Sh, bool kSwiglu>
+__global__ __launch_bounds__(Sh::kWaves * 64, Sh::NB == 4 ? 1 : 2) void norm_linear_gemm_kernel(GemmParams p) {
+  constexpr int kBM = Sh::kBM, kBN = Sh::kBN, NB = Sh::NB, W = Sh::kWaves, kStages = Sh::kStages;
+  constexpr int kPartBytes = Sh::kPartBytes, kStageBytes = Sh::kStageBytes;
   extern __shared__ __align__(16) unsigned char smem[];
   int mt, nt;
   if (!gemm_tile(p, mt, nt)) return;
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave >> 2, wn = wave & 3;          // 2 x 4 waves: 128 token rows x 64 features
+  const int wm = wave / Sh::WN, wn = wave % Sh::WN;
   const int li = lane & 31, g = lane >> 5;
 
   const int sample = mt / p.m_tiles_per_sample;
@@ -73,10 +115,10 @@ __global__ __launch_bounds__(kGemmWaves * 64, 1) void norm_linear_gemm_kernel(Ge
   const int valid_rows = rows_left < kBM ? (int)rows_left : kBM;
   const int hidden = p.F >> 1;
 
-  // Feature (weight row) of tile row R.  SwiGLU tiles pair 128 u-features with their
+  // Feature (weight row) of tile row R.  SwiGLU tiles pair kBN / 2 u-features with their
   // v-features: wave column wn holds u rows in its first 32 tile rows, v rows in the next 32.
   auto feature = [&](int R) __attribute__((always_inline)) {
-    if (p.swiglu) {
+    if constexpr (kSwiglu) {
       int j = nt * (kBN / 2) + (R >> 6) * 32 + (R & 31);
       j = j < hidden ? j : hidden - 1;
       return ((R >> 5) & 1) ? hidden + j : j;
@@ -85,8 +127,8 @@ __global__ __launch_bounds__(kGemmWaves * 64, 1) void norm_linear_gemm_kernel(Ge
     return f < p.F ? f : p.F - 1;
   };
 
-  // ---- copies: instruction j (0..63) moves rows 8j..8j+7 of the stage; wave w issues
-  // j = w + 8i.  i < 4: weight rows, i >= 4: token rows.  Rows past the end repeat the last
+  // ---- copies: instruction j moves rows 8j..8j+7 of the stage; wave w issues
+  // j = w + W i.  i < 4: weight rows, i >= 4: token rows.  Rows past the end repeat the last
   // valid row (never stored).  Lane: row j*8 + lane/8, LDS chunk position lane%8.
   const bf16_t* wmat = p.w + (long long)sample * p.w_sample_stride;
   const unsigned long long wbase = reinterpret_cast<unsigned long long>(wmat);
@@ -98,7 +140,7 @@ __global__ __launch_bounds__(kGemmWaves * 64, 1) void norm_linear_gemm_kernel(Ge
     const int chunk = (lane & 7) ^ Sub::swz(r_sub);
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      const int R = ((wave + 8 * i) << 3) + r_in;               // 0..511
+      const int R = ((wave + W * i) << 3) + r_in;
       if (i < 4) {
         voff[i] = (uint32_t)((long long)feature(R) * p.K * 2 + chunk * 16);
       } else {
@@ -111,7 +153,7 @@ __global__ __launch_bounds__(kGemmWaves * 64, 1) void norm_linear_gemm_kernel(Ge
   const uint32_t lds0 = lds_address(smem);
   auto copy_piece = [&](int i, uint32_t stage, int k0, uint32_t enable) __attribute__((always_inline)) {
     async_copy16_off(voff[i], (i < 4 ? wbase : xbase) + (unsigned long long)k0 * 2,
-                     stage + (uint32_t)((wave + 8 * i) << 10), enable);
+                     stage + (uint32_t)((wave + W * i) << 10), enable);
   };
 
   // ---- operand reads: per lane four chunk offsets (one per 16-channel block of a step)
@@ -122,36 +164,51 @@ __global__ __launch_bounds__(kGemmWaves * 64, 1) void norm_linear_gemm_kernel(Ge
     for (int kk = 0; kk < 4; ++kk) {
       const uint32_t off = li * 128 + (((2 * kk + g) ^ s) << 4);
       va[kk] = lds0 + wn * 8192 + off;
-      vb[kk] = lds0 + kPartBytes + wm * 16384 + off;
+      vb[kk] = lds0 + kPartBytes + wm * (NB * 4096) + off;
     }
   }
 
-  f32x16 acc[2][4];
+  f32x16 acc[2][NB];
 #pragma unroll
   for (int a = 0; a < 2; ++a)
 #pragma unroll
-    for (int b = 0; b < 4; ++b)
+    for (int b = 0; b < NB; ++b)
 #pragma unroll
       for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.f;
 
   const int k_steps = p.K / kBK;
+  // stages 0 .. kStages-2 are on their way before the first step
 #pragma unroll
-  for (int i = 0; i < 8; ++i) copy_piece(i, lds0, 0, 1);
+  for (int st = 0; st < kStages - 1; ++st)
+#pragma unroll
+    for (int i = 0; i < 8; ++i) copy_piece(i, lds0 + st * kStageBytes, st * kBK, st < k_steps);
 
-  bf16x8 ao[2][2], bo[2][4];
+  bf16x8 ao[2][2], bo[2][NB];
   auto fetch = [&](int set, int kk, uint32_t stage_off) __attribute__((always_inline)) {
 #pragma unroll
     for (int a = 0; a < 2; ++a) ao[set][a] = Sub::read_rm(va[kk] + stage_off + a * 4096);
 #pragma unroll
-    for (int b = 0; b < 4; ++b) bo[set][b] = Sub::read_rm(vb[kk] + stage_off + b * 4096);
+    for (int b = 0; b < NB; ++b) bo[set][b] = Sub::read_rm(vb[kk] + stage_off + b * 4096);
   };
 
+  uint32_t stage_off = 0;
   for (int ks = 0; ks < k_steps; ++ks) {
-    const uint32_t stage_off = (ks & 1) * kStageBytes;
-    wait_async_loads();
-    __syncthreads();               // this stage has landed; every reader of the other one is done
-    const uint32_t more = ks + 1 < k_steps;
-    const uint32_t next_stage = lds0 + (kStageBytes - stage_off);
+    // This wave's copies of this stage have landed; those of up to kStages - 2 later stages
+    // (eight each, in order) may still be on their way.
+    if constexpr (kStages == 2) {
+      wait_async_loads();
+    } else {
+      static_assert(kStages <= 4);
+      const int later = k_steps - 1 - ks;
+      if (kStages >= 4 && later >= 2) asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
+      else if (later >= 1) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+      else wait_async_loads();
+    }
+    __syncthreads();               // this stage has landed; every reader of the stage before is done
+    const uint32_t more = ks + kStages - 1 < k_steps;
+    // the stage that the last step's readers have left
+    const uint32_t next_off = stage_off == 0 ? (kStages - 1) * kStageBytes : stage_off - kStageBytes;
+    const uint32_t next_stage = lds0 + next_off;
     fetch(0, 0, stage_off);
     sched_fence();
 #pragma unroll
@@ -160,44 +217,51 @@ __global__ __launch_bounds__(kGemmWaves * 64, 1) void norm_linear_gemm_kernel(Ge
 #pragma unroll
       for (int a = 0; a < 2; ++a)
 #pragma unroll
-        for (int b = 0; b < 4; ++b) {
+        for (int b = 0; b < NB; ++b) {
           acc[a][b] = mfma32(ao[kk & 1][a], bo[kk & 1][b], acc[a][b]);
-          // the next stage's copies ride in the first half of the step, one per two products,
-          // so that they have the second half to land before the wait that opens the next step
-          if (kk < 2 && (b & 1)) copy_piece(4 * kk + 2 * a + (b >> 1), next_stage, (ks + 1) * kBK, more);
+          // the next stage's copies ride in the first half of the step, spread over its
+          // products, so that they have the second half to land before the wait that opens
+          // the next step
+          if (kk < 2) {
+            const int q = (kk * 2 + a) * NB + b;
+#pragma unroll
+            for (int i = q * 2 / NB; i < (q + 1) * 2 / NB; ++i)
+              copy_piece(i, next_stage, (ks + kStages - 1) * kBK, more);
+          }
         }
       sched_fence();
     }
+    stage_off = stage_off + kStageBytes == kStages * kStageBytes ? 0 : stage_off + kStageBytes;
   }
 
   // ---- epilogue: row scale, bias, (gate); results pass through the LDS so that they leave in
-  // 16-byte pieces, eight lanes per 128-byte row segment.  Each wave stages its 128 x 64 part
+  // 16-byte pieces, eight lanes per 128-byte row segment.  Each wave stages its NB*32 x 64 part
   // in a region of its own (row pitch 144 bytes: 16-byte aligned, rows on different banks).
-  constexpr int kPitch = 144;
+  constexpr int kPitch = Sh::kPitch;
   __syncthreads();                                   // every wave is done with the operand stages
   const float* bias = p.bias ? p.bias + (long long)sample * p.F : nullptr;
-  const uint32_t stage_w = lds0 + wave * (128 * kPitch);
+  const uint32_t stage_w = lds0 + wave * (NB * 32 * kPitch);
 
-  // writes the wave's staged [128][64] bf16 block (8 chunks per row) to `dst` (row pitch ld):
+  // writes the wave's staged [NB*32][64] bf16 block (8 chunks per row) to `dst` (row pitch ld):
   // chunk c of a row goes to column col_of(c)
   auto flush = [&](bf16_t* dst, long long ld, int chunks, auto col_of, int limit)
       __attribute__((always_inline)) {
     const int rows_per_inst = 64 / chunks;
     const int r_in = lane / chunks, c = lane % chunks;
     const int col = col_of(c);
-    for (int t = 0; t < 128 / rows_per_inst; ++t) {
+    for (int t = 0; t < NB * 32 / rows_per_inst; ++t) {
       const int ml = t * rows_per_inst + r_in;
-      const int m = wm * 128 + ml;
+      const int m = wm * (NB * 32) + ml;
       const u32x4 v = *reinterpret_cast<const AERIS_LDS u32x4*>(stage_w + ml * kPitch + c * 16);
       if (m < valid_rows && col < limit)
         *reinterpret_cast<u32x4*>(dst + (row0 + m) * ld + col) = v;
     }
   };
 
-  float rs[4];
+  float rs[NB];
 #pragma unroll
-  for (int b = 0; b < 4; ++b) {
-    int m = wm * 128 + b * 32 + li;
+  for (int b = 0; b < NB; ++b) {
+    int m = wm * (NB * 32) + b * 32 + li;
     m = m < valid_rows ? m : valid_rows - 1;
     rs[b] = p.r ? p.r[row0 + m] : 1.f;
   }
@@ -207,34 +271,34 @@ __global__ __launch_bounds__(kGemmWaves * 64, 1) void norm_linear_gemm_kernel(Ge
     *reinterpret_cast<AERIS_LDS u32x2*>(stage_w + (b * 32 + li) * kPitch + col * 2) = v;
   };
 
-  if (p.swiglu) {
+  if constexpr (kSwiglu) {
     const int jw = nt * (kBN / 2) + wn * 32;         // first gate column of this wave
-    f32x4 bu[4], bv[4];
+    // u and v in place of the products; the fences here and below keep the compiler from working
+    // on all of a wave's values at once, which spills
 #pragma unroll
     for (int vq = 0; vq < 4; ++vq) {
       int j = jw + 8 * vq + 4 * g;
       j = j < hidden ? j : hidden - 4;
-      bu[vq] = bias ? *reinterpret_cast<const f32x4*>(bias + j) : f32x4{0.f, 0.f, 0.f, 0.f};
-      bv[vq] = bias ? *reinterpret_cast<const f32x4*>(bias + hidden + j) : f32x4{0.f, 0.f, 0.f, 0.f};
+      const f32x4 bu = bias ? *reinterpret_cast<const f32x4*>(bias + j) : f32x4{0.f, 0.f, 0.f, 0.f};
+      const f32x4 bv = bias ? *reinterpret_cast<const f32x4*>(bias + hidden + j) : f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          acc[0][b][4 * vq + e] = __builtin_fmaf(acc[0][b][4 * vq + e], rs[b], bu[e]);
+          acc[1][b][4 * vq + e] = __builtin_fmaf(acc[1][b][4 * vq + e], rs[b], bv[e]);
+        }
+      sched_fence();
     }
-    // u and v (kept in registers), staged as [u 32 | v 32] for the optional uv output
-    float uu[4][16], vv[4][16];
+    if (p.y) {   // the optional uv output, staged as [u 32 | v 32]
 #pragma unroll
-    for (int b = 0; b < 4; ++b)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        uu[b][i] = __builtin_fmaf(acc[0][b][i], rs[b], bu[i >> 2][i & 3]);
-        vv[b][i] = __builtin_fmaf(acc[1][b][i], rs[b], bv[i >> 2][i & 3]);
-      }
-    if (p.y) {
-#pragma unroll
-      for (int b = 0; b < 4; ++b)
+      for (int b = 0; b < NB; ++b)
 #pragma unroll
         for (int vq = 0; vq < 4; ++vq) {
-          stage_store(b, 8 * vq + 4 * g, uu[b][4 * vq], uu[b][4 * vq + 1], uu[b][4 * vq + 2],
-                      uu[b][4 * vq + 3]);
-          stage_store(b, 32 + 8 * vq + 4 * g, vv[b][4 * vq], vv[b][4 * vq + 1], vv[b][4 * vq + 2],
-                      vv[b][4 * vq + 3]);
+          stage_store(b, 8 * vq + 4 * g, acc[0][b][4 * vq], acc[0][b][4 * vq + 1],
+                      acc[0][b][4 * vq + 2], acc[0][b][4 * vq + 3]);
+          stage_store(b, 32 + 8 * vq + 4 * g, acc[1][b][4 * vq], acc[1][b][4 * vq + 1],
+                      acc[1][b][4 * vq + 2], acc[1][b][4 * vq + 3]);
         }
       // chunk c: c < 4 -> u columns jw + 8c, else v columns hidden + jw + 8(c - 4); a column
       // past `hidden` (ragged last tile) is marked by F, which the limit rejects
@@ -244,13 +308,15 @@ __global__ __launch_bounds__(kGemmWaves * 64, 1) void norm_linear_gemm_kernel(Ge
       }, p.F);
     }
 #pragma unroll
-    for (int b = 0; b < 4; ++b)
+    for (int b = 0; b < NB; ++b)
 #pragma unroll
-      for (int vq = 0; vq < 4; ++vq)
-        stage_store(b, 8 * vq + 4 * g, silu(uu[b][4 * vq]) * vv[b][4 * vq],
-                    silu(uu[b][4 * vq + 1]) * vv[b][4 * vq + 1],
-                    silu(uu[b][4 * vq + 2]) * vv[b][4 * vq + 2],
-                    silu(uu[b][4 * vq + 3]) * vv[b][4 * vq + 3]);
+      for (int vq = 0; vq < 4; ++vq) {
+        float o[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] = silu(acc[0][b][4 * vq + e]) * acc[1][b][4 * vq + e];
+        stage_store(b, 8 * vq + 4 * g, o[0], o[1], o[2], o[3]);
+        sched_fence();
+      }
     flush(p.g, hidden, 4, [&](int c) { return jw + 8 * c; }, hidden);
   } else {
     const int fw = nt * kBN + wn * 64;               // first feature of this wave
@@ -262,7 +328,7 @@ __global__ __launch_bounds__(kGemmWaves * 64, 1) void norm_linear_gemm_kernel(Ge
         f = f < p.F ? f : p.F - 4;
         const f32x4 b4 = bias ? *reinterpret_cast<const f32x4*>(bias + f) : f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int b = 0; b < 4; ++b)
+        for (int b = 0; b < NB; ++b)
           stage_store(b, a * 32 + 8 * vq + 4 * g,
                       __builtin_fmaf(acc[a][b][4 * vq], rs[b], b4[0]),
                       __builtin_fmaf(acc[a][b][4 * vq + 1], rs[b], b4[1]),
@@ -334,8 +400,9 @@ int projection_gemm_check(long long n_rows, long long rows_per_sample, int K, in
   if (n_rows / rows_per_sample > 65535) return AERIS_ERR_INVALID_SHAPE;   // a grid dimension
   // 32-bit byte offsets inside a workgroup's operand tiles, 31-bit tile counts
   if ((long long)F * K * 2 >= (1LL << 32)) return AERIS_ERR_INVALID_SHAPE;
-  const long long m_tiles = (n_rows / rows_per_sample) * ((rows_per_sample + kBM - 1) / kBM);
-  const long long n_tiles = (F + kBN - 1) / kBN;
+  const long long m_tiles = (n_rows / rows_per_sample) *
+                            ((rows_per_sample + GemmLarge::kBM - 1) / GemmLarge::kBM);
+  const long long n_tiles = (F + GemmLarge::kBN - 1) / GemmLarge::kBN;
   if (((m_tiles + 63) / 64) * 64 * n_tiles >= (1LL << 31)) return AERIS_ERR_INVALID_SHAPE;
   return AERIS_OK;
 }
@@ -353,14 +420,68 @@ bool bad16(const void* ptr) { return (reinterpret_cast<uintptr_t>(ptr) & 15) != 
 
 }  // namespace
 
+namespace {
+
+// Fills in the tile counts of a shape; false if its grid does not fit a launch.
+template <class Sh>
+bool gemm_tiles(GemmParams& p) {
+  const long long per_sample = (p.rows_per_sample + Sh::kBM - 1) / Sh::kBM;
+  const long long m_tiles = per_sample * p.n_samples;
+  const int features = p.swiglu ? p.F / 2 : p.F, tile = p.swiglu ? Sh::kBN / 2 : Sh::kBN;
+  p.n_tiles = (features + tile - 1) / tile;
+  if ((m_tiles + 63) / 64 * 64 * p.n_tiles >= (1LL << 31)) return false;
+  p.m_tiles_per_sample = (int)per_sample;
+  p.m_tiles = (int)m_tiles;
+  p.interleave = Sh::NB == 4 && interleave_tiles(m_tiles, p.K);
+  return true;
+}
+
+template <class Sh, bool kSwiglu>
+int launch_gemm_kernel(const GemmParams& p, hipStream_t stream) {
+  if (!allow_full_lds<norm_linear_gemm_kernel<Sh, kSwiglu>>()) return -1;
+  return launch_kernel(norm_linear_gemm_kernel<Sh, kSwiglu>, dim3(gemm_grid(p)),
+                       dim3(Sh::kWaves * 64), (size_t)Sh::kSmem, stream, p);
+}
+template <class Sh>
+int launch_gemm_shape(const GemmParams& p, hipStream_t stream) {
+  return p.swiglu ? launch_gemm_kernel<Sh, true>(p, stream) : launch_gemm_kernel<Sh, false>(p, stream);
+}
+
+// Which tile shape: the one whose rounds of workgroups are estimated to end first, from the time
+// a round takes (microseconds: a fixed part plus a part per 64-channel step; measured over
+// 500 ... 172800 rows, 128 ... 5504 channels, 128 ... 3072 features).  Small tiles have the
+// shortest steps and are taken as long as each has a CU of its own: 500 rows x 1024 -> 1024
+// takes 22.7 / 11.2 / 10.0 us with large / medium / small tiles, 2000 x 512 -> 1536 (768 small
+// tiles) 15.4 / 9.0 / 13.8.  Medium tiles win while large ones leave CUs without work
+// (4000 x 1024 -> 1024: 27.4 / 14.1 us; 8000 x 1024 -> 3072: 57 / 54), large ones, which move
+// half as many operand bytes per product, from about one full round on (20011 x 2304 -> 768:
+// 62.8 / 75.6; 172800 x 2048 -> 2048: 1247 / 1444).
+enum class GemmTile { kLarge, kMedium, kSmall };
+GemmTile choose_gemm_tile(long long large_tiles, long long medium_tiles, long long small_tiles, int steps) {
+  constexpr long long kCus = 256;
+  if (small_tiles <= kCus) return GemmTile::kSmall;
+  const double large = (double)((large_tiles + kCus - 1) / kCus) * (8.0 + 1.6 * steps);
+  const double round = 3.0 + 1.05 * steps, half_round = 3.0 + 0.6 * steps;   // two or one per CU
+  const long long rest = medium_tiles % (2 * kCus);
+  const double medium = (double)(medium_tiles / (2 * kCus)) * round +
+                        (rest == 0 ? 0.0 : rest <= kCus ? half_round : round);
+  return medium < large ? GemmTile::kMedium : GemmTile::kLarge;
+}
+
+}  // namespace
+
 int launch_projection_gemm(GemmParams p, hipStream_t stream) {
-  p.m_tiles_per_sample = (int)((p.rows_per_sample + kBM - 1) / kBM);
-  if (!allow_full_lds<norm_linear_gemm_kernel>()) return -1;
-  // two operand stages; the epilogue reuses them as eight 128 x 144-byte staging regions
-  constexpr size_t kSmem = kGemmWaves * 128 * 144 > 2 * kStageBytes ? kGemmWaves * 128 * 144
-                                                                    : 2 * kStageBytes;
-  return launch_kernel(norm_linear_gemm_kernel, dim3(gemm_grid(p)), dim3(kGemmWaves * 64), kSmem,
-                       stream, p);
+  GemmParams large = p, medium = p, small = p;
+  if (!gemm_tiles<GemmLarge>(large)) return -1;
+  // a count that does not fit a launch rules the finer tiles out
+  constexpr long long kNone = 1LL << 40;
+  auto tiles = [](bool fits, const GemmParams& q) { return fits ? (long long)q.m_tiles * q.n_tiles : kNone; };
+  switch (choose_gemm_tile(tiles(true, large), tiles(gemm_tiles<GemmMedium>(medium), medium),
+                           tiles(gemm_tiles<GemmSmall>(small), small), p.K / kBK)) {
+    case GemmTile::kSmall: return launch_gemm_shape<GemmSmall>(small, stream);
+    case GemmTile::kMedium: return launch_gemm_shape<GemmMedium>(medium, stream);
+    default: return launch_gemm_shape<GemmLarge>(large, stream);
+  }
 }
 
 namespace {
@@ -415,11 +536,10 @@ int norm_projection(const void* x, const float* w, const float* gamma, const flo
   p.y = static_cast<bf16_t*>(y);
   p.g = static_cast<bf16_t*>(g);
   p.rows_per_sample = rows_per_sample;
-  p.m_tiles = (int)(n_samples * ((rows_per_sample + kBM - 1) / kBM));
+  p.n_samples = n_samples;
   p.K = channels;
   p.F = features;
   p.swiglu = swiglu ? 1 : 0;
-  p.n_tiles = swiglu ? (features / 2 + kBN / 2 - 1) / (kBN / 2) : (features + kBN - 1) / kBN;
   return launch_projection_gemm(p, st) == 0 ? AERIS_OK : AERIS_ERR_HIP_LAUNCH;
 }
 
@@ -467,9 +587,8 @@ extern "C" int aeris_linear_fwd(const void* x, const void* weight, int64_t n_row
   p.w = static_cast<const bf16_t*>(weight);
   p.y = static_cast<bf16_t*>(y);
   p.rows_per_sample = n_rows;
-  p.m_tiles = (int)((n_rows + kBM - 1) / kBM);
+  p.n_samples = 1;
   p.K = channels;
   p.F = out_features;
-  p.n_tiles = (out_features + kBN - 1) / kBN;
   return launch_projection_gemm(p, static_cast<hipStream_t>(hip_stream)) == 0 ? AERIS_OK : AERIS_ERR_HIP_LAUNCH;
 }

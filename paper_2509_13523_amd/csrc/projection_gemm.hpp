@@ -16,9 +16,11 @@ struct GemmParams {
   bf16_t* y;                   // [n_rows, F]: the projection (plain), or uv (SwiGLU, may be null)
   bf16_t* g;                   // SwiGLU: [n_rows, F / 2]
   long long rows_per_sample;
-  int m_tiles_per_sample;      // filled in by the launch
+  long long n_samples;
+  int m_tiles_per_sample;      // filled in by the launch, as the next three
   int m_tiles;                 // n_samples * tiles per sample
   int n_tiles;
+  int interleave;              // how token tiles are dealt to the XCDs
   int K, F;
   int swiglu;
 };

@@ -84,6 +84,14 @@ __host__ __device__ inline int grid_blocks(const KParams& p) {
   return 8 * ((p.n_pairs + 7) / 8) * p.n_tiles;
 }
 
+// Work item of this workgroup in a list of `total` items = gridDim.x: consecutive workgroup ids
+// go to the eight XCDs in turn; XCD x gets the x-th of eight contiguous pieces of the list.
+__device__ __forceinline__ int xcd_contiguous(int total) {
+  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+  const int share = total >> 3, extra = total & 7;
+  return xcd * share + (xcd < extra ? xcd : extra) + slot;
+}
+
 // One (batch, window, head) and how its tokens are enumerated.
 //
 // Tokens of a window are enumerated region by region (at most a 2x2 split of

@@ -147,6 +147,20 @@ def test_linear_fwd(n, channels, features):
     close("y", y, ref, 1e-5 * (np.abs(x) @ np.abs(weight).T))
 
 
+@pytest.mark.parametrize("n_samples,rows,channels,features", [
+    (1, 65, 64, 80),          # 64 x 64 tiles, one row and one 8-feature group past a tile: one step,
+    (1, 63, 128, 64),         # two steps (as many as prologue stages less one),
+    (1, 129, 192, 128),       # three,
+    (1, 64, 320, 208),        # five: the stages wrap around
+    (3, 695, 192, 1104),      # 128 x 128 tiles, ragged both ways, three samples
+    (1, 4070, 512, 4080),     # 256 x 256 tiles, ragged both ways, eight steps
+])
+def test_projections_with_every_tile_shape(n_samples, rows, channels, features):
+    test_linear_fwd(n_samples * rows, channels, features)
+    test_norm_linear_fwd(n_samples, rows, channels, features)
+    test_norm_linear_swiglu_fwd(n_samples, rows, channels, features // 2)
+
+
 def test_qkv_projection_at_the_headline_size_on_sampled_rows():
     """4 x 720 x 1440 token rows x 2048 channels -> 6144 features (the QKV projection of the
     headline workload, in the launch configuration bench.py times): sampled rows against the
