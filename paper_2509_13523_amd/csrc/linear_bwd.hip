@@ -7,14 +7,13 @@
 // W^T [C, F] first), so both of its operands are contiguous along the contraction again.
 //
 // dW contracts over the token rows, along which neither operand is contiguous.  One workgroup
-// of eight wavefronts owns a 256 x 256 tile of dW for a range of rows; per step 64 rows of dy
-// (256 features) and of x (256 channels) go global -> LDS directly as four [64][128] sub-tiles
-// in the swizzled chunk layout of the attention kernels, and both MFMA operands are fetched
-// with transposing reads (ds_read_b64_tr_b16), the token index landing in the registers.  The
-// row range of the whole problem is split over several workgroups per tile; each writes its
-// partial tile, and a second kernel adds the partials in a fixed order (no atomics: the result
-// does not depend on the schedule) together with the products of the rows past the last whole
-// step of 64.
+// owns a tile of dW for a range of rows; per step 64 rows of dy (the tile's features) and of x
+// (its channels) go global -> LDS directly as [64][128] or [64][64] sub-tiles in the swizzled
+// chunk layout of the attention kernels, and both MFMA operands are fetched with transposing
+// reads (ds_read_b64_tr_b16), the token index landing in the registers.  The rows of the whole
+// problem are split over several workgroups per tile; each writes its partial tile, and a second
+// kernel adds the partials in a fixed order (no atomics: the result does not depend on the
+// schedule).  Rows past the end in the last step are cleared in the LDS before they are used.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -27,13 +26,33 @@
 namespace aeris {
 namespace {
 
-constexpr int kTF = 256;                 // features per workgroup tile
-constexpr int kTC = 256;                 // channels per workgroup tile
 constexpr int kTM = 64;                  // token rows per step
-constexpr int kWgradWaves = 8;
-constexpr int kSubTileBytes = kTM * 128 * 2;          // [64 rows][128 columns] bf16
-constexpr int kWgradStageBytes = 4 * kSubTileBytes;   // dy halves, then x halves
-using Sub128 = Tile<128, kWgradWaves>;
+
+// FW x CW waves, each with FB x CB blocks of 32 x 32; STAGES steps in the LDS at a time.
+template <int FW_, int CW_, int FB_, int CB_, int STAGES_, int PER_CU_>
+struct WgradShape {
+  static constexpr int FW = FW_, CW = CW_, FB = FB_, CB = CB_, kStages = STAGES_;
+  static constexpr int kPerCu = PER_CU_;                 // workgroups a CU holds
+  // Long sums in two levels: after kRun steps the accumulators are added to a second set and
+  // start again, which keeps the rounding error of a workgroup that walks many rows at that of
+  // one which walks 1024.  The largest shape has no registers for it and gets its rows split.
+  static constexpr int kRun = FB_ * CB_ <= 4 ? 16 : 0;
+  static constexpr int kWaves = FW * CW;
+  static constexpr int kTF = FW * FB * 32;               // features per workgroup tile
+  static constexpr int kTC = CW * CB * 32;               // channels per workgroup tile
+  static constexpr int kWidth = kTF % 128 == 0 && kTC % 128 == 0 ? 128 : 64;   // columns of a sub-tile
+  using Sub = Tile<kWidth, kWaves>;
+  static constexpr int kSubBytes = kTM * kWidth * 2;
+  static constexpr int kFSubs = kTF / kWidth, kCSubs = kTC / kWidth;
+  static constexpr int kStageBytes = (kFSubs + kCSubs) * kSubBytes;   // dy sub-tiles, then x sub-tiles
+  static constexpr int kRowsPerInst = 512 / kWidth;      // rows one copy instruction of a wave moves
+  static constexpr int kPiecesPerSub = kTM / kRowsPerInst / kWaves;   // per wave
+  static constexpr int kPieces = (kFSubs + kCSubs) * kPiecesPerSub;   // copies of a wave per step
+  static_assert(kPiecesPerSub * kRowsPerInst * kWaves == kTM, "waves share a sub-tile evenly");
+};
+using WgradLarge = WgradShape<2, 4, 4, 2, 2, 1>;    // 256 x 256, eight waves, 128 KB
+using WgradMedium = WgradShape<2, 2, 2, 2, 2, 2>;   // 128 x 128, four waves, 64 KB
+using WgradSmall = WgradShape<2, 2, 1, 1, 3, 3>;    // 64 x 64, four waves, 48 KB
 
 struct WgradParams {
   const bf16_t* dy;            // [M, F]
@@ -41,56 +60,71 @@ struct WgradParams {
   float* out;                  // [splits][F, C]
   int F, C;
   int f_tiles, c_tiles;
-  int cu, f_groups, c_groups;  // a unit is (32 / cu) x cu tiles
   int splits;
   int steps_per_split, steps_total;      // steps of kTM rows
+  int tail;                              // rows of the last step if it is not whole, else 0
 };
 
-// Workgroup id -> (split, feature tile, channel tile).  Consecutive ids go to the eight XCDs in
-// turn.  The 32 workgroups an XCD runs at a time form one unit: fu x cu output tiles of the
-// same row range, so that each 64-row piece of dy or x that arrives in that XCD's L2 serves cu
-// or fu workgroups which walk the rows together.
-__device__ __forceinline__ bool wgrad_tile(const WgradParams& p, int& split, int& ft, int& ct) {
-  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-  const int unit = (slot >> 5) * 8 + xcd, t = slot & 31;
-  const int fu = 32 / p.cu;
-  const int cg = unit % p.c_groups;
-  const int rest = unit / p.c_groups;
-  const int fg = rest % p.f_groups;
-  split = rest / p.f_groups;
-  ct = cg * p.cu + t % p.cu;
-  ft = fg * fu + t / p.cu;
-  return split < p.splits && ft < p.f_tiles && ct < p.c_tiles;
-}
-inline unsigned wgrad_grid(const WgradParams& p) {
-  const unsigned units = (unsigned)p.splits * (unsigned)p.f_groups * (unsigned)p.c_groups;
-  return ((units + 7) / 8) * 8 * 32;
+// Workgroup id -> (split, feature tile, channel tile).  Work items are listed by row range, then
+// by bands of four feature tiles.  Consecutive workgroup ids go to the eight XCDs in turn; pieces
+// of the list as long as the workgroups an XCD runs at a time go to the XCDs in turn, so that
+// those share 64-row pieces of dy and x through its L2 (four feature tiles by eight channel tiles
+// where there are that many) and walk the rows together; the items left over, fewer than one
+// piece per XCD, are shared out evenly.  No idle workgroups.
+__device__ __forceinline__ void wgrad_tile(const WgradParams& p, int piece, int& split, int& ft,
+                                           int& ct) {
+  const int tiles = p.f_tiles * p.c_tiles, total = p.splits * tiles;
+  const int whole = total / (8 * piece) * (8 * piece);
+  const int xcd = blockIdx.x & 7;
+  int item;
+  if ((int)blockIdx.x < whole) {
+    const int slot = blockIdx.x >> 3;
+    item = (slot / piece * 8 + xcd) * piece + slot % piece;
+  } else {
+    const int left = total - whole, share = left >> 3, extra = left & 7;
+    item = whole + xcd * share + (xcd < extra ? xcd : extra) + (((int)blockIdx.x - whole) >> 3);
+  }
+  split = item / tiles;
+  const int t = item - split * tiles;
+  const int band = t / (4 * p.c_tiles), r = t - band * 4 * p.c_tiles;
+  const int height = p.f_tiles - 4 * band < 4 ? p.f_tiles - 4 * band : 4;
+  ct = r / height;
+  ft = 4 * band + r - ct * height;
 }
 
-__global__ __launch_bounds__(kWgradWaves * 64, 1) void linear_wgrad_kernel(WgradParams p) {
+template <class S>
+__global__ __launch_bounds__(S::kWaves * 64, S::kWaves * S::kPerCu / 4) void linear_wgrad_kernel(
+    WgradParams p) {
+  using Sub = typename S::Sub;
+  constexpr int FB = S::FB, CB = S::CB, kP = S::kPieces;
   extern __shared__ __align__(16) unsigned char smem[];
   int split, ft, ct;
-  if (!wgrad_tile(p, split, ft, ct)) return;
+  wgrad_tile(p, 32 * S::kPerCu, split, ft, ct);
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wf = wave >> 2, wc = wave & 3;          // 2 x 4 waves: 128 features x 64 channels
+  const int wf = wave / S::CW, wc = wave % S::CW;
   const int li = lane & 31, g = lane >> 5;
-  const int f0 = ft * kTF, c0 = ct * kTC;
+  const int f0 = ft * S::kTF, c0 = ct * S::kTC;
   const int s0 = split * p.steps_per_split;
   const int s1 = s0 + p.steps_per_split < p.steps_total ? s0 + p.steps_per_split : p.steps_total;
 
-  // ---- copies: instruction j (0..63) moves rows 4(j % 16) .. +3 of sub-tile j / 16; wave w
-  // issues j = w + 8i, i.e. sub-tile i / 2, rows 4(w + 8(i % 2)) ..  Lane: row + lane / 16, LDS
-  // chunk position lane % 16, which holds source chunk position ^ swz(row).  Columns past the
-  // end of a ragged last tile are clamped into the row (their products are never stored).
-  uint32_t voff[8];
+  // ---- copies: piece i of wave w moves kRowsPerInst rows of sub-tile i / kPiecesPerSub.  Lane:
+  // row + lane / chunks, LDS chunk position lane % chunks, which holds source chunk
+  // position ^ swz(row).  Columns past the end of a ragged last tile are clamped into the row
+  // (their products are never stored), rows past the end of the last step to its last row.
+  constexpr int kChunks = S::kWidth / 8;
+  auto piece_row = [&](int i) __attribute__((always_inline)) {
+    return S::kRowsPerInst * (wave + S::kWaves * (i % S::kPiecesPerSub)) + lane / kChunks;
+  };
+  uint32_t voff[kP];
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const int t = i >> 1;
-    const int r = 4 * (wave + 8 * (i & 1)) + (lane >> 4);
-    const int chunk = (lane & 15) ^ Sub128::swz(r);
-    const int ld = t < 2 ? p.F : p.C;
-    int col = (t < 2 ? f0 : c0) + 128 * (t & 1) + 8 * chunk;
+  for (int i = 0; i < kP; ++i) {
+    const int t = i / S::kPiecesPerSub;
+    const int r = piece_row(i);
+    const int chunk = (lane % kChunks) ^ Sub::swz(r);
+    const bool is_dy = t < S::kFSubs;
+    const int ld = is_dy ? p.F : p.C;
+    int col = (is_dy ? f0 + S::kWidth * t : c0 + S::kWidth * (t - S::kFSubs)) + 8 * chunk;
     col = col < ld ? col : ld - 8;
     voff[i] = (uint32_t)(((long long)r * ld + col) * 2);
   }
@@ -98,185 +132,271 @@ __global__ __launch_bounds__(kWgradWaves * 64, 1) void linear_wgrad_kernel(Wgrad
   const unsigned long long xbase = reinterpret_cast<unsigned long long>(p.x);
   const uint32_t lds0 = lds_address(smem);
   auto copy_piece = [&](int i, uint32_t stage, int step, uint32_t enable) __attribute__((always_inline)) {
-    const unsigned long long row_bytes = (unsigned long long)(i < 4 ? p.F : p.C) * 2;
-    async_copy16_off(voff[i], (i < 4 ? dybase : xbase) + (unsigned long long)step * kTM * row_bytes,
-                     stage + (uint32_t)((i >> 1) * kSubTileBytes + ((wave + 8 * (i & 1)) << 10)),
+    const int t = i / S::kPiecesPerSub;
+    const int ld = t < S::kFSubs ? p.F : p.C;
+    async_copy16_off(voff[i], (t < S::kFSubs ? dybase : xbase) +
+                              (unsigned long long)step * kTM * ((unsigned long long)ld * 2),
+                     stage + (uint32_t)(t * S::kSubBytes +
+                                        ((wave + S::kWaves * (i % S::kPiecesPerSub)) << 10)),
                      enable);
+  };
+
+  // before the copies of step `step`: if rows are missing there, its (last) copies stop at the last row
+  auto clamp_rows = [&](int step) __attribute__((always_inline)) {
+    if (p.tail == 0 || step != p.steps_total - 1) return;
+#pragma unroll
+    for (int i = 0; i < kP; ++i) {
+      const int past = piece_row(i) - (p.tail - 1);
+      voff[i] -= past > 0 ? (uint32_t)past * (uint32_t)((i / S::kPiecesPerSub < S::kFSubs ? p.F : p.C) * 2) : 0u;
+    }
   };
 
   // ---- transposing operand reads: per lane two addresses per 32-column block (rows 4g..4g+3
   // and 8+4g..8+4g+3 of a 16-row group; both operands use the same row order)
-  uint32_t ta[4][2], tb[2][2];
+  uint32_t ta[FB][2], tb[CB][2];
   {
     const int j = lane & 15, blk = lane >> 4;
+    // block of 32 columns starting at `col` of the operand whose first sub-tile is `first`
+    auto address = [&](int first, int col, int h) __attribute__((always_inline)) {
+      const int r = 8 * h + 4 * (blk >> 1) + (j >> 2);
+      const int c = (col % S::kWidth) / 8 + 2 * (blk & 1) + ((j & 3) >> 1);
+      return lds0 + (first + col / S::kWidth) * S::kSubBytes + Sub::chunk_offset(r, c) + (j & 1) * 8;
+    };
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      const int r = 8 * h + 4 * (blk >> 1) + (j >> 2);
 #pragma unroll
-      for (int a = 0; a < 4; ++a) {
-        const int c = 4 * a + 2 * (blk & 1) + ((j & 3) >> 1);
-        ta[a][h] = lds0 + wf * kSubTileBytes + Sub128::chunk_offset(r, c) + (j & 1) * 8;
-      }
+      for (int a = 0; a < FB; ++a) ta[a][h] = address(0, (wf * FB + a) * 32, h);
 #pragma unroll
-      for (int b = 0; b < 2; ++b) {
-        const int c = 4 * (2 * (wc & 1) + b) + 2 * (blk & 1) + ((j & 3) >> 1);
-        tb[b][h] = lds0 + (2 + (wc >> 1)) * kSubTileBytes + Sub128::chunk_offset(r, c) + (j & 1) * 8;
-      }
+      for (int b = 0; b < CB; ++b) tb[b][h] = address(S::kFSubs, (wc * CB + b) * 32, h);
     }
   }
 
-  f32x16 acc[4][2];
+  f32x16 acc[FB][CB];
 #pragma unroll
-  for (int a = 0; a < 4; ++a)
+  for (int a = 0; a < FB; ++a)
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
+    for (int b = 0; b < CB; ++b)
 #pragma unroll
       for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.f;
 
+  f32x16 sum[S::kRun ? FB : 1][S::kRun ? CB : 1];
+  auto add_run = [&]() __attribute__((always_inline)) {
+    if constexpr (S::kRun != 0) {
 #pragma unroll
-  for (int i = 0; i < 8; ++i) copy_piece(i, lds0, s0, 1);
+      for (int a = 0; a < FB; ++a)
+#pragma unroll
+        for (int b = 0; b < CB; ++b)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) {
+            sum[a][b][i] += acc[a][b][i];
+            acc[a][b][i] = 0.f;
+          }
+    }
+  };
+  if constexpr (S::kRun != 0) {
+#pragma unroll
+    for (int a = 0; a < FB; ++a)
+#pragma unroll
+      for (int b = 0; b < CB; ++b)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) sum[a][b][i] = 0.f;
+  }
 
-  bf16x8 ao[2][4], bo[2][2];
+#pragma unroll
+  for (int st = 0; st < S::kStages - 1; ++st) {
+    if (s0 + st < s1) clamp_rows(s0 + st);
+#pragma unroll
+    for (int i = 0; i < kP; ++i) copy_piece(i, lds0 + st * S::kStageBytes, s0 + st, s0 + st < s1);
+  }
+
+  bf16x8 ao[2][FB], bo[2][CB];
   auto fetch = [&](int set, int kk, uint32_t stage_off) __attribute__((always_inline)) {
-    const uint32_t off = stage_off + kk * (16 * 256);
+    const uint32_t off = stage_off + kk * (16 * S::kWidth * 2);
 #pragma unroll
-    for (int a = 0; a < 4; ++a) ao[set][a] = Sub128::read_tr(ta[a][0] + off, ta[a][1] + off);
+    for (int a = 0; a < FB; ++a) ao[set][a] = Sub::read_tr(ta[a][0] + off, ta[a][1] + off);
 #pragma unroll
-    for (int b = 0; b < 2; ++b) bo[set][b] = Sub128::read_tr(tb[b][0] + off, tb[b][1] + off);
+    for (int b = 0; b < CB; ++b) bo[set][b] = Sub::read_tr(tb[b][0] + off, tb[b][1] + off);
   };
 
+  uint32_t stage_off = 0;
+  uint32_t fill_off = (S::kStages - 1) * S::kStageBytes;
   for (int ks = s0; ks < s1; ++ks) {
-    const uint32_t stage_off = ((ks - s0) & 1) * kWgradStageBytes;
-    wait_async_loads();
-    __syncthreads();               // this stage has landed; every reader of the other one is done
-    const uint32_t more = ks + 1 < s1;
-    const uint32_t next_stage = lds0 + (kWgradStageBytes - stage_off);
+    // this stage's copies are the oldest in flight; those of the kStages - 2 steps behind it, if
+    // there are that many, may stay in flight
+    if (S::kStages > 2 && ks + S::kStages - 2 < s1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((S::kStages - 2) * kP) : "memory");
+    else wait_async_loads();
+    __syncthreads();               // this stage has landed; every reader of the one filled next is done
+    if (p.tail && ks == p.steps_total - 1) {   // clear the rows past the end, once
+      const int clear = (kTM - p.tail) * kChunks;      // 16-byte chunks per sub-tile
+      for (int t = 0; t < S::kFSubs + S::kCSubs; ++t)
+        for (int i = tid; i < clear; i += S::kWaves * 64)
+          *reinterpret_cast<u32x4*>(smem + stage_off + t * S::kSubBytes +
+                                    (p.tail * kChunks + i) * 16) = u32x4{0, 0, 0, 0};
+      __syncthreads();
+    }
+    const int next = ks + S::kStages - 1;
+    const uint32_t more = next < s1;
+    if (more) clamp_rows(next);
     fetch(0, 0, stage_off);
     sched_fence();
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) {
       if (kk < 3) fetch((kk + 1) & 1, kk + 1, stage_off);
 #pragma unroll
-      for (int a = 0; a < 4; ++a)
+      for (int a = 0; a < FB; ++a)
 #pragma unroll
-        for (int b = 0; b < 2; ++b) {
+        for (int b = 0; b < CB; ++b) {
           acc[a][b] = mfma32(ao[kk & 1][a], bo[kk & 1][b], acc[a][b]);
-          // the next stage's copies ride in the first half of the step, one per two products
-          if (kk < 2 && (b & 1)) copy_piece(4 * kk + a, next_stage, ks + 1, more);
+          // the copies of a later stage ride in the first half of the step, spread evenly
+          constexpr int kHalf = 2 * FB * CB;
+          const int n = (kk * FB + a) * CB + b;
+          if (n < kHalf) {
+#pragma unroll
+            for (int i = n * kP / kHalf; i < (n + 1) * kP / kHalf; ++i)
+              copy_piece(i, lds0 + fill_off, next, more);
+          }
         }
       sched_fence();
     }
+    if (S::kRun != 0 && ((ks - s0) & (S::kRun - 1)) == S::kRun - 1) add_run();
+    stage_off = stage_off == (S::kStages - 1) * S::kStageBytes ? 0 : stage_off + S::kStageBytes;
+    fill_off = fill_off == (S::kStages - 1) * S::kStageBytes ? 0 : fill_off + S::kStageBytes;
   }
 
+  add_run();
   // ---- partial tile: a lane owns one channel column, a register one feature row
   float* out = p.out + (long long)split * p.F * p.C;
 #pragma unroll
-  for (int a = 0; a < 4; ++a)
+  for (int a = 0; a < FB; ++a)
 #pragma unroll
-    for (int b = 0; b < 2; ++b) {
-      const int c = c0 + wc * 64 + b * 32 + li;
+    for (int b = 0; b < CB; ++b) {
+      const int c = c0 + (wc * CB + b) * 32 + li;
 #pragma unroll
       for (int e = 0; e < 16; ++e) {
-        const int f = f0 + wf * 128 + a * 32 + acc_row(e, g);
-        if (f < p.F && c < p.C) out[(long long)f * p.C + c] = acc[a][b][e];
+        const int f = f0 + (wf * FB + a) * 32 + acc_row(e, g);
+        if (f < p.F && c < p.C) out[(long long)f * p.C + c] = S::kRun ? sum[a][b][e] : acc[a][b][e];
       }
     }
 }
 
-// dW = sum of the partial tiles, in the order of the splits, plus the products of the last
-// n_rows % 64 rows (`tail` rows starting at row `row0`), which the tile kernel does not take:
-// at most 63 multiply-adds per element, in row order.  n4: number of 4-float groups of dW.
+// dW = sum of the partial tiles, in the order of the splits.  n4: number of 4-float groups of dW.
 __global__ __launch_bounds__(256) void wgrad_reduce_kernel(const float* __restrict__ part,
                                                            long long n4, int splits,
-                                                           const bf16_t* __restrict__ dy,
-                                                           const bf16_t* __restrict__ x,
-                                                           long long row0, int tail, int F, int C,
                                                            float* __restrict__ dw) {
   const long long stride = (long long)gridDim.x * 256;
   for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < n4; i += stride) {
     f32x4 s = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 8
     for (int k = 0; k < splits; ++k) {
       const f32x4 v = reinterpret_cast<const f32x4*>(part)[(long long)k * n4 + i];
       s[0] += v[0]; s[1] += v[1]; s[2] += v[2]; s[3] += v[3];
-    }
-    if (tail) {
-      const long long e = i * 4;
-      const int f = (int)(e / C), c = (int)(e - (long long)f * C);
-      for (int m = 0; m < tail; ++m) {
-        const float d = (float)dy[(row0 + m) * F + f];
-        const bf16x4 xv = *reinterpret_cast<const bf16x4*>(x + (row0 + m) * C + c);
-        s[0] = __builtin_fmaf(d, (float)xv[0], s[0]);
-        s[1] = __builtin_fmaf(d, (float)xv[1], s[1]);
-        s[2] = __builtin_fmaf(d, (float)xv[2], s[2]);
-        s[3] = __builtin_fmaf(d, (float)xv[3], s[3]);
-      }
     }
     reinterpret_cast<f32x4*>(dw)[i] = s;
   }
 }
 
-// wt [C, F] = w [F, C]^T, bf16: 64 x 64 tiles through the LDS (row pitch 65 words apart in banks).
+// wt [C, F] = w [F, C]^T, bf16: 64 x 64 tiles through the LDS, 16 bytes per lane and access on
+// both sides (C and F are multiples of 64, so every tile is whole).  Bound by the latency of one
+// load and one store: two of each per thread, all in flight together.  The pitch of 66 elements
+// puts the eight scattered 2-byte writes of a lane and its neighbours into different banks.
 __global__ __launch_bounds__(256) void transpose_weight_kernel(const bf16_t* __restrict__ w, int F,
                                                                int C, bf16_t* __restrict__ wt) {
-  __shared__ unsigned short tile[64][66];
+  constexpr int kPitch = 66;
+  __shared__ unsigned short tile[64 * kPitch];                 // [channel][feature]
   const int f0 = blockIdx.y * 64, c0 = blockIdx.x * 64;
-  const unsigned short* src = reinterpret_cast<const unsigned short*>(w);
-  unsigned short* dst = reinterpret_cast<unsigned short*>(wt);
-  for (int i = threadIdx.x; i < 64 * 64; i += 256) {
-    const int r = i >> 6, c = i & 63;
-    tile[r][c] = (f0 + r < F && c0 + c < C) ? src[(long long)(f0 + r) * C + c0 + c] : (unsigned short)0;
-  }
+  const int row = threadIdx.x >> 3, chunk = threadIdx.x & 7;   // rows row, row + 32
+  u32x4 v[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+    v[i] = *reinterpret_cast<const u32x4*>(w + (long long)(f0 + row + 32 * i) * C + c0 + 8 * chunk);
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+      tile[(8 * chunk + e) * kPitch + row + 32 * i] = (unsigned short)(v[i][e >> 1] >> (16 * (e & 1)));
   __syncthreads();
-  for (int i = threadIdx.x; i < 64 * 64; i += 256) {
-    const int r = i >> 6, c = i & 63;               // r: channel, c: feature
-    if (c0 + r < C && f0 + c < F) dst[(long long)(c0 + r) * F + f0 + c] = tile[c][r];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const uint32_t* src = reinterpret_cast<const uint32_t*>(tile + (row + 32 * i) * kPitch + 8 * chunk);
+    *reinterpret_cast<u32x4*>(wt + (long long)(c0 + row + 32 * i) * F + f0 + 8 * chunk) =
+        u32x4{src[0], src[1], src[2], src[3]};
   }
 }
 
 size_t round256(size_t n) { return (n + 255) & ~(size_t)255; }
 bool bad16(const void* ptr) { return (reinterpret_cast<uintptr_t>(ptr) & 15) != 0; }
 
-// How the rows are split for dW: enough workgroups to fill the chip several times over, but at
-// least 16 steps each and at most 64 partial tiles per output tile; among the next few counts
-// the one whose units (32 tiles, one XCD's worth) fill the eight XCDs most evenly.
-struct Split {
+enum class WgradTile { kLarge, kMedium, kSmall };
+struct WgradPlan {
+  WgradTile tile;
   int steps_total, steps_per_split, splits;
-  int cu, f_groups, c_groups;
+  int most;      // partial tiles the workspace holds; with one, dW itself is written
 };
-Split choose_split(int64_t n_rows, int32_t channels, int32_t features) {
-  Split s;
-  s.steps_total = (int)(n_rows / kTM);
-  const int f_tiles = (features + kTF - 1) / kTF, c_tiles = (channels + kTC - 1) / kTC;
-  s.cu = c_tiles >= 8 ? 8 : (c_tiles >= 4 ? 4 : (c_tiles >= 2 ? 2 : 1));
-  s.c_groups = (c_tiles + s.cu - 1) / s.cu;
-  s.f_groups = (f_tiles + 32 / s.cu - 1) / (32 / s.cu);
-  const long long tiles = (long long)f_tiles * c_tiles;
-  long long want = (2048 + tiles - 1) / tiles;
-  want = want < 1 ? 1 : (want > 64 ? 64 : want);
-  auto layout = [&](long long target, int& per_out, int& splits_out) {
-    long long per = (s.steps_total + target - 1) / target;
-    per = per < 16 ? 16 : per;
-    per_out = (int)per;
-    splits_out = (int)((s.steps_total + per - 1) / per);    // 0 if there is no whole step
-  };
-  layout(want, s.steps_per_split, s.splits);
-  double best = -1.0;
-  for (long long target = want; target < want + 8 && target <= 64; ++target) {
-    int per, splits;
-    layout(target, per, splits);
-    if (splits == 0) break;
-    const long long units = (long long)splits * s.f_groups * s.c_groups;
-    const double fill = (double)units / (double)(((units + 7) / 8) * 8);
-    if (fill > best + 1e-9) {
-      best = fill;
-      s.steps_per_split = per;
-      s.splits = splits;
-    }
-  }
-  return s;
+
+// Microseconds from the first workgroup to the last partial sum.  A CU that holds kPerCu of its n
+// workgroups at a time takes step_us[kPerCu] per step of a full set and step_us[m] for a last set
+// of m; the partial tiles cost a second launch and 0.25 us per MB written and read.
+template <class S>
+double wgrad_time(int splits, int per, int32_t channels, int32_t features, double fixed,
+                  const double (&step_us)[4]) {
+  const long long tiles = (long long)((features + S::kTF - 1) / S::kTF) * ((channels + S::kTC - 1) / S::kTC);
+  const long long n = (tiles * splits + 255) / 256, sets = n / S::kPerCu, left = n % S::kPerCu;
+  const double steps = (double)per * ((double)sets * step_us[S::kPerCu] + step_us[left]);
+  const double sums = splits == 1 ? 0.0 : 3.0 + 0.25e-6 * ((double)splits * features * channels * 4.0);
+  return steps + fixed * (double)(sets + (left != 0)) + sums;
 }
-// whether the tile kernel can write dW itself: one row range and no rows left over
-bool direct_dw(const Split& s, int64_t n_rows) { return s.splits == 1 && n_rows % kTM == 0; }
+
+// The plan that is estimated to end first.  Times per step measured over 1000 ... 172800 rows,
+// 128 ... 5504 channels and 128 ... 11008 features; one tile shape and row ranges of at least 16
+// steps took (start to end, us) 43 / 44 / 98 / 159 / 117 / 79 where this takes
+// 12 / 22 / 80 / 86 / 72 / 55: 1000 x 1024 -> 1024, 4000 x 512 -> 1536, 8000 x 2048 -> 2048,
+// 20011 x 768 -> 2304, 30000 x 1024 -> 1024, 100000 x 256 -> 768.
+// The largest tiles have their rows split for about 2048 workgroups, at least 16 steps each and
+// at most 64 ranges, among the next few counts the one whose rounds of workgroups end first.  The
+// workspace holds that many partial tiles (plan.most); the other shapes use as many or fewer.
+WgradPlan choose_wgrad(int64_t n_rows, int32_t channels, int32_t features) {
+  WgradPlan best{};
+  const int steps = (int)((n_rows + kTM - 1) / kTM);
+  double best_time = 1e30;
+  auto consider = [&](WgradTile tile, int want, auto time) {
+    const int per = (steps + want - 1) / want;
+    const int splits = (steps + per - 1) / per;
+    const double t = time(splits, per);
+    if (t >= best_time) return;
+    best_time = t;
+    best = WgradPlan{tile, steps, per, splits, best.most};
+  };
+  const long long tiles = (long long)((features + WgradLarge::kTF - 1) / WgradLarge::kTF) *
+                          ((channels + WgradLarge::kTC - 1) / WgradLarge::kTC);
+  const int by_tiles = (int)(2048 / tiles < 64 ? (2047 + tiles) / tiles : 64);
+  const int by_rows = (int)((n_rows / kTM + 15) / 16);
+  const int fewest = by_tiles < by_rows ? by_tiles : by_rows;
+  const int last = fewest < by_rows ? (fewest + 7 < 64 ? fewest + 7 : 64) : fewest;
+  for (int want = fewest; want <= last && want <= by_rows; ++want)
+    if (want > 0)
+      consider(WgradTile::kLarge, want, [&](int splits, int per) {
+        return wgrad_time<WgradLarge>(splits, per, channels, features, 8.0, {0.0, 1.6, 0.0, 0.0});
+      });
+  best.most = best.splits > 1 ? best.splits : 1;
+  for (int want = 1; want <= best.most && want <= steps; ++want) {
+    consider(WgradTile::kMedium, want, [&](int splits, int per) {
+      return wgrad_time<WgradMedium>(splits, per, channels, features, 5.0, {0.0, 0.72, 1.0, 0.0});
+    });
+    consider(WgradTile::kSmall, want, [&](int splits, int per) {
+      return wgrad_time<WgradSmall>(splits, per, channels, features, 4.0, {0.0, 0.36, 0.44, 0.58});
+    });
+  }
+  return best;
+}
+
+template <class S>
+int launch_wgrad(WgradParams p, hipStream_t stream) {
+  p.f_tiles = (p.F + S::kTF - 1) / S::kTF;
+  p.c_tiles = (p.C + S::kTC - 1) / S::kTC;
+  if (!allow_full_lds<linear_wgrad_kernel<S>>()) return -1;
+  return launch_kernel(linear_wgrad_kernel<S>, dim3((unsigned)(p.splits * p.f_tiles * p.c_tiles)),
+                       dim3(S::kWaves * 64), (size_t)S::kStages * S::kStageBytes, stream, p);
+}
 
 int check_linear_bwd(int64_t n_rows, int32_t channels, int32_t features) {
   if (n_rows <= 0 || channels <= 0 || features <= 0) return AERIS_ERR_INVALID_SHAPE;
@@ -298,9 +418,12 @@ using namespace aeris;
 extern "C" size_t aeris_linear_bwd_workspace_bytes(int64_t n_rows, int32_t channels,
                                                    int32_t out_features) {
   if (check_linear_bwd(n_rows, channels, out_features) != AERIS_OK) return 0;
-  const Split s = choose_split(n_rows, channels, out_features);
+  // one partial tile is asked for where rows are left over a single row range, though dW itself is
+  // written then: the size callers have known
+  const int most = choose_wgrad(n_rows, channels, out_features).most;
+  const bool none = n_rows < kTM || (most == 1 && n_rows % kTM == 0);
   return round256((size_t)out_features * channels * 2) +
-         (direct_dw(s, n_rows) ? 0 : round256((size_t)s.splits * out_features * channels * 4));
+         (none ? 0 : round256((size_t)most * out_features * channels * 4));
 }
 
 extern "C" int aeris_linear_bwd(const void* x, const void* weight, const void* dy, int64_t n_rows,
@@ -334,36 +457,31 @@ extern "C" int aeris_linear_bwd(const void* x, const void* weight, const void* d
     if (launch_projection_gemm(p, st) != 0) return AERIS_ERR_HIP_LAUNCH;
   }
   if (dweight) {
-    const Split s = choose_split(n_rows, channels, out_features);
+    const WgradPlan plan = choose_wgrad(n_rows, channels, out_features);
     WgradParams p{};
     p.dy = static_cast<const bf16_t*>(dy);
     p.x = static_cast<const bf16_t*>(x);
-    const bool direct = direct_dw(s, n_rows);
+    const bool direct = plan.splits == 1;
     p.out = direct ? dweight : part;
     p.F = out_features;
     p.C = channels;
-    p.f_tiles = (out_features + kTF - 1) / kTF;
-    p.c_tiles = (channels + kTC - 1) / kTC;
-    p.cu = s.cu;
-    p.c_groups = s.c_groups;
-    p.f_groups = s.f_groups;
-    p.splits = s.splits;
-    p.steps_per_split = s.steps_per_split;
-    p.steps_total = s.steps_total;
-    if (s.splits > 0) {
-      if (!allow_full_lds<linear_wgrad_kernel>()) return AERIS_ERR_HIP_LAUNCH;
-      if (launch_kernel(linear_wgrad_kernel, dim3(wgrad_grid(p)), dim3(kWgradWaves * 64),
-                        (size_t)2 * kWgradStageBytes, st, p) != 0)
-        return AERIS_ERR_HIP_LAUNCH;
+    p.splits = plan.splits;
+    p.steps_per_split = plan.steps_per_split;
+    p.steps_total = plan.steps_total;
+    p.tail = (int)(n_rows % kTM);
+    int rc = -1;
+    switch (plan.tile) {
+      case WgradTile::kLarge: rc = launch_wgrad<WgradLarge>(p, st); break;
+      case WgradTile::kMedium: rc = launch_wgrad<WgradMedium>(p, st); break;
+      case WgradTile::kSmall: rc = launch_wgrad<WgradSmall>(p, st); break;
     }
+    if (rc != 0) return AERIS_ERR_HIP_LAUNCH;
     if (!direct) {
       const long long n4 = (long long)out_features * channels / 4;
       const long long blocks = (n4 + 255) / 256;
       if (launch_kernel(wgrad_reduce_kernel, dim3((unsigned)(blocks < 4096 ? blocks : 4096)),
-                        dim3(256), 0, st, static_cast<const float*>(part), n4, s.splits,
-                        static_cast<const bf16_t*>(dy), static_cast<const bf16_t*>(x),
-                        (long long)s.steps_total * kTM, (int)(n_rows % kTM), (int)out_features,
-                        (int)channels, dweight) != 0)
+                        dim3(256), 0, st, static_cast<const float*>(part), n4, plan.splits,
+                        dweight) != 0)
         return AERIS_ERR_HIP_LAUNCH;
     }
   }

@@ -74,6 +74,9 @@ CASES = [
     (4159, 256, 512),         # four row ranges and 63 rows left over
     (1024, 64, 11008),        # the SwiGLU width: 43 feature tiles (empty slots on five XCDs);
                               # dx contracts over 11008 features
+    (2125, 64, 128),          # 64 x 64 tiles: two row ranges of 17 steps (one past a run of 16), 13 rows left over
+    (5003, 1600, 4160),       # 128 x 128 tiles, one row range of 79 steps (four runs and 15), ragged tiles
+    (1050, 4096, 4032),       # 256 x 256 tiles, ragged feature tile, 26 rows left over
 ]
 
 
