@@ -482,38 +482,57 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 1 : 2) void winattn_dkdv_kerne
     constexpr uint32_t kOff = decltype(off)::value;
     constexpr uint32_t kStatOff = decltype(stat_off)::value;
     if (rg.skip(sub_lo)) return;
-    // operand reads first, products after: LDS latency hides behind the MFMA pipeline
-    bf16x8 qa[D / 16], doa[D / 16], qta[D / 32][2], dota[D / 32][2];
-#pragma unroll
-    for (int kk = 0; kk < D / 16; ++kk) {
+    // head_dim 64: every operand is read first, products after, so that LDS latency hides behind
+    // the MFMA pipeline (232 registers, two waves per SIMD).  head_dim 32 has too few products per
+    // block for that and is bound by latency: operands are read one block of products ahead, the
+    // statistics four rows at a time, in fenced order, which takes 120 registers instead of 160,
+    // four waves per SIMD instead of three (65,000 tokens, 8 heads, windows of 144 / 256 / 400 / 900
+    // tokens: 73 / 58 / 100 / 167 -> 67 / 53 / 93 / 162 us; the same order at head_dim 64, where it
+    // fits 168 registers: 160 / 119 / 195 / 303 -> 165 / 127 / 187 / 297, and 126 -> 159 at 64).
+    constexpr bool kLean = D == 32;
+    constexpr int kNK = D / 16;
+    bf16x8 qa[kNK], doa[kNK], dota[kNK], qta[kNK];
+    f32x4 l4[4], d4[4];
+    auto fetch_rows = [&](int kk) __attribute__((always_inline)) {
       qa[kk] = Tl::read_rm(la.rm[kk] + kOff);
       doa[kk] = Tl::read_rm(la.rm[kk] + kOff + Tl::kBytes);
-    }
-    f32x4 l4[4], d4[4];
-#pragma unroll
-    for (int vq = 0; vq < 4; ++vq) {
+    };
+    auto fetch_stat = [&](int vq) __attribute__((always_inline)) {
       l4[vq] = *reinterpret_cast<const AERIS_LDS f32x4*>(stat_lane + kStatOff + vq * 32);
       d4[vq] = *reinterpret_cast<const AERIS_LDS f32x4*>(stat_lane + kStatOff + vq * 32 +
                                                          kStream * 4);
+    };
+    // channel block j / 2, 16-query group j % 2
+    auto fetch_tr = [&](int j) __attribute__((always_inline)) {
+      const uint32_t off = kOff + (j & 1) * Tl::kGroupBytes;
+      dota[j] = Tl::read_tr(la.tr[j >> 1][0] + off + Tl::kBytes, la.tr[j >> 1][1] + off + Tl::kBytes);
+      qta[j] = Tl::read_tr(la.tr[j >> 1][0] + off, la.tr[j >> 1][1] + off);
+    };
+    auto fence = [&]() __attribute__((always_inline)) {
+      if constexpr (kLean) sched_fence();
+    };
+#pragma unroll
+    for (int kk = 0; kk < (kLean ? 1 : kNK); ++kk) fetch_rows(kk);
+    if constexpr (!kLean) {
+#pragma unroll
+      for (int vq = 0; vq < 4; ++vq) fetch_stat(vq);
     }
     // S[query, key] = Q K^T,  dP[query, key] = dO V^T: rows = streamed queries
     f32x16 s, dp;
 #pragma unroll
     for (int i = 0; i < 16; ++i) { s[i] = 0.f; dp[i] = 0.f; }
+    fence();
 #pragma unroll
-    for (int kk = 0; kk < D / 16; ++kk) {
+    for (int kk = 0; kk < kNK; ++kk) {
+      if (kLean && kk + 1 < kNK) fetch_rows(kk + 1);
       s = mfma32(qa[kk], kreg[kk], s);
       dp = mfma32(doa[kk], vreg[kk], dp);
+      fence();
     }
+    if constexpr (!kLean) {
 #pragma unroll
-    for (int cb = 0; cb < D / 32; ++cb)
-#pragma unroll
-      for (int c = 0; c < 2; ++c) {
-        dota[cb][c] = Tl::read_tr(la.tr[cb][0] + kOff + Tl::kBytes + c * Tl::kGroupBytes,
-                                  la.tr[cb][1] + kOff + Tl::kBytes + c * Tl::kGroupBytes);
-        qta[cb][c] = Tl::read_tr(la.tr[cb][0] + kOff + c * Tl::kGroupBytes,
-                                 la.tr[cb][1] + kOff + c * Tl::kGroupBytes);
-      }
+      for (int j = 0; j < kNK; ++j) fetch_tr(j);
+    }
     if (!rg.mask_free(sub_lo)) {
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
@@ -521,27 +540,32 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 1 : 2) void winattn_dkdv_kerne
         if (qidx < lo_k || qidx >= hi_k) s[i] = -INFINITY;
       }
     }
-    float pr[16], ds[16];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      pr[i] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[i], p.scale_log2, -l4[i >> 2][i & 3]));
-      ds[i] = pr[i] * (dp[i] - d4[i >> 2][i & 3]);
-    }
     union { u32x4 u; bf16x8 h; } pb[2], dsb[2];
+    if (kLean) fetch_stat(0);
 #pragma unroll
-    for (int c = 0; c < 2; ++c)
+    for (int vq = 0; vq < 4; ++vq) {
+      if (kLean && vq < 3) fetch_stat(vq + 1);
+      float pr[4], ds[4];
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        pb[c].u[e] = pack_bf16(pr[8 * c + 2 * e], pr[8 * c + 2 * e + 1]);
-        dsb[c].u[e] = pack_bf16(ds[8 * c + 2 * e], ds[8 * c + 2 * e + 1]);
+        pr[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[4 * vq + e], p.scale_log2, -l4[vq][e]));
+        ds[e] = pr[e] * (dp[4 * vq + e] - d4[vq][e]);
       }
 #pragma unroll
-    for (int cb = 0; cb < D / 32; ++cb)
-#pragma unroll
-      for (int c = 0; c < 2; ++c) {
-        dvacc[cb] = mfma32(dota[cb][c], pb[c].h, dvacc[cb]);
-        dkacc[cb] = mfma32(qta[cb][c], dsb[c].h, dkacc[cb]);
+      for (int e = 0; e < 2; ++e) {
+        pb[vq >> 1].u[2 * (vq & 1) + e] = pack_bf16(pr[2 * e], pr[2 * e + 1]);
+        dsb[vq >> 1].u[2 * (vq & 1) + e] = pack_bf16(ds[2 * e], ds[2 * e + 1]);
       }
+      fence();
+    }
+    if (kLean) fetch_tr(0);
+#pragma unroll
+    for (int j = 0; j < kNK; ++j) {
+      if (kLean && j + 1 < kNK) fetch_tr(j + 1);
+      dvacc[j >> 1] = mfma32(dota[j], pb[j & 1].h, dvacc[j >> 1]);
+      dkacc[j >> 1] = mfma32(qta[j], dsb[j & 1].h, dkacc[j >> 1]);
+      fence();
+    }
   };
 
   auto tile_step = [&](auto parity, int qt) __attribute__((always_inline)) {

@@ -65,19 +65,45 @@ struct KParams {
 __host__ __device__ inline int table_bytes(int T) { return ((T + kStream - 1) / kStream) * kStream * 4; }
 
 // ----------------------------------------------------------------------------
-// Workgroup id -> (pair, tile).  Hardware deals consecutive workgroup ids to
-// the eight XCDs in turn.  Pairs (batch, window, head) are dealt to XCDs
-// round-robin (pair % 8), which balances seam windows -- they carry less work
-// -- across XCDs, and all tiles of one pair run on that one XCD, so the K/V
-// (or Q/dO) rows they all stream are shared through its L2.
-// Grid size: 8 * ceil(n_pairs / 8) * n_tiles.  Returns false for padding.
+// Workgroup id -> (pair, tile).  Hardware deals consecutive workgroup ids to the eight XCDs in
+// turn.  All tiles of one pair (batch, window, head) run on one XCD, so the K/V (or Q/dO) rows
+// they all stream are shared through its L2.
+//
+// Long windows, bound by matrix products: pairs are dealt to XCDs round-robin (pair % 8), which
+// balances seam windows -- they carry less work -- across XCDs.
+// Short windows (32 to kGroupHeadsTokens tokens), bound by memory: whole windows are dealt to
+// XCDs and the heads of a window follow each other there, so that the pieces of a token's row
+// (2 * head_dim bytes per head, next to each other in memory) are fetched at about the same time
+// through the same L2; round-robin pairs put them on different XCDs, where 64-byte pieces
+// (head_dim 32) fetch every 128-byte line twice.  Which XCD a window goes to turns with the digits
+// of its index, so that a column of seam windows does not fall on one XCD; the last n % 8 windows
+// are dealt pair by pair.  Measured over 65,000 to 86,000 tokens, 8 heads (forward / dQ / dK-dV,
+// us): 64 tokens, head_dim 64: 99 / 152 / 135 -> 86 / 127 / 126; 144: 82 / 165 / 186 -> 82 / 139 /
+// 160; 256: 55 / 113 / 128 -> 57 / 99 / 119, head_dim 32: 42 / 59 / 61 -> 37 / 51 / 58; 576,
+// head_dim 64: 112 / 167 / 215 -> 114 / 164 / 218 (16 heads: 240 / 337 / 424 -> 224 / 320 / 414).
+// Outside: 900 tokens 162 / 225 / 272 -> 167 / 228 / 277, 16 tokens 197 / 301 -> 213 / 307.
+// Grid size: grid_blocks().  Returns false for padding.
 // ----------------------------------------------------------------------------
+constexpr int kGroupHeadsTokens = 640;
+
+// Windows dealt whole; the pairs of the others, if any, are dealt round-robin.
+__host__ __device__ inline int grouped_windows(const KParams& p) {
+  return p.T >= 32 && p.T <= kGroupHeadsTokens ? (p.B * p.n_win) & ~7 : 0;
+}
 __device__ __forceinline__ bool block_to_work(const KParams& p, int& pair, int& tile) {
   const int id = blockIdx.x;
   const int xcd = id & 7, slot = id >> 3;
-  const int pair_local = slot / p.n_tiles;
-  tile = slot - pair_local * p.n_tiles;
-  pair = pair_local * 8 + xcd;
+  const int local = slot / p.n_tiles;
+  tile = slot - local * p.n_tiles;
+  const int whole = grouped_windows(p);
+  const int grouped = (whole >> 3) * p.nh;     // pairs of whole windows per XCD
+  if (local < grouped) {
+    const int w = local / p.nh;
+    const int turn = w + (w >> 3) + (w >> 6) + (w >> 9);
+    pair = (w * 8 + ((xcd + turn) & 7)) * p.nh + (local - w * p.nh);
+    return true;
+  }
+  pair = whole * p.nh + (local - grouped) * 8 + xcd;
   return pair < p.n_pairs;
 }
 __host__ __device__ inline int grid_blocks(const KParams& p) {

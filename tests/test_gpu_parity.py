@@ -204,6 +204,18 @@ def test_small_and_non_square_windows(win, shift):
     run_case((2, H, W, 3, 64), win, shift, B.AERIS_MASK_SWIN, seed=51)
 
 
+@pytest.mark.parametrize("shape,win", [
+    ((1, 31, 11, 5, 32), (31, 1)),        # 31 tokens: pairs dealt one by one
+    ((1, 8, 44, 5, 32), (8, 4)),          # 32 tokens: eight windows dealt whole, three pair by pair
+    ((3, 16, 24, 3, 128), (8, 8)),        # 18 windows over three batch members
+    ((1, 16, 360, 3, 64), (16, 40)),      # 640 tokens, nine windows
+    ((1, 16, 369, 2, 64), (16, 41)),      # 656 tokens: pairs dealt one by one again
+])
+def test_every_pair_has_one_workgroup(shape, win):
+    """Both ways of dealing (window, head) pairs to workgroups, at their edges and remainders."""
+    run_case(shape, win, (win[0] // 2, win[1] // 2), B.AERIS_MASK_SWIN, seed=55)
+
+
 @pytest.mark.parametrize("shift", [(0, 0), (5, 7)])
 def test_one_window_is_global_attention(shift):
     run_case((1, 24, 40, 2, 64), (24, 40), shift, B.AERIS_MASK_NONE, seed=61)
