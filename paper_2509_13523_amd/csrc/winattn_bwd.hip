@@ -396,7 +396,7 @@ constexpr size_t dkdv_smem_bytes(int T) {
 }
 
 template <int D, typename OutT>
-__global__ __launch_bounds__(kThreads, D == 128 ? 1 : 2) void winattn_dkdv_kernel(
+__global__ __launch_bounds__(kThreads, 2) void winattn_dkdv_kernel(
     KParams p, const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
     const bf16_t* __restrict__ v, const bf16_t* __restrict__ d_o,
     const float* __restrict__ delta, const float* __restrict__ lse2v, OutT* __restrict__ dk,
@@ -483,13 +483,14 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 1 : 2) void winattn_dkdv_kerne
     constexpr uint32_t kStatOff = decltype(stat_off)::value;
     if (rg.skip(sub_lo)) return;
     // head_dim 64: every operand is read first, products after, so that LDS latency hides behind
-    // the MFMA pipeline (232 registers, two waves per SIMD).  head_dim 32 has too few products per
-    // block for that and is bound by latency: operands are read one block of products ahead, the
-    // statistics four rows at a time, in fenced order, which takes 120 registers instead of 160,
+    // the MFMA pipeline (228 registers, two waves per SIMD).  The others read operands one block of
+    // products ahead and the statistics four rows at a time, in fenced order.  head_dim 32 has too
+    // few products per block for the former and is bound by latency: 118 registers instead of 160,
     // four waves per SIMD instead of three (65,000 tokens, 8 heads, windows of 144 / 256 / 400 / 900
     // tokens: 73 / 58 / 100 / 167 -> 67 / 53 / 93 / 162 us; the same order at head_dim 64, where it
     // fits 168 registers: 160 / 119 / 195 / 303 -> 165 / 127 / 187 / 297, and 126 -> 159 at 64).
-    constexpr bool kLean = D == 32;
+    // head_dim 128 fits two waves per SIMD only this way.
+    constexpr bool kLean = D != 64;
     constexpr int kNK = D / 16;
     bf16x8 qa[kNK], doa[kNK], dota[kNK], qta[kNK];
     f32x4 l4[4], d4[4];
@@ -605,6 +606,13 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 1 : 2) void winattn_dkdv_kerne
     }
 }
 
+// head_dim 128: windows of at most this many tokens run the generic dK/dV kernel, two workgroups per
+// CU; longer ones the software-pipelined kernel, whose one workgroup per CU needs a loop of several
+// tiles to pay for its prologue and epilogue.  Pipelined against generic, 8 heads, 32,000 to 86,000
+// tokens, us: 4 tokens 1460 / 773, 16: 1033 / 659, 36: 539 / 432, 64: 394 / 334, 100: 304 / 284,
+// 144: 425 / 391, 192: 287 / 278; 256: 265 / 280, 289: 394 / 402, 576: 473 / 490, 900: 635 / 658.
+constexpr int kPipeAboveTokens = 192;
+
 template <int D, typename OutT>
 static int launch_bwd_t(const KParams& kp, const void* q, const void* k, const void* v,
                         const void* o, const float* lse, const void* d_o, void* dq, void* dk,
@@ -636,18 +644,18 @@ static int launch_bwd_t(const KParams& kp, const void* q, const void* k, const v
                       fused_stats ? 1 : 0) != 0)
       return -1;
   }
-  if constexpr (D == 128) {   // software-pipelined kernel; the generic one is not built for it
-    if ((stages & 4u) && launch_dkdv_pipe128(kp, std::is_same<OutT, float>::value, q, k, v, d_o,
-                                             delta, lse2, dk, dv, stream) != 0)
-      return -1;
-  } else if (stages & 4u) {
+  if (stages & 4u) {
+    if constexpr (D == 128) {
+      if (kp.T > kPipeAboveTokens)
+        return launch_dkdv_pipe128(kp, std::is_same<OutT, float>::value, q, k, v, d_o, delta, lse2,
+                                   dk, dv, stream);
+    }
     const size_t smem = dkdv_smem_bytes<D>(kp.T);
     auto kern = winattn_dkdv_kernel<D, OutT>;
     if (!allow_full_lds<winattn_dkdv_kernel<D, OutT>>()) return -1;
-    if (launch_kernel(kern, dim3(n_blocks), dim3(kThreads), smem, stream, kp, qp, kp_, vp, dop,
-                      static_cast<const float*>(delta), static_cast<const float*>(lse2),
-                      static_cast<OutT*>(dk), static_cast<OutT*>(dv)) != 0)
-      return -1;
+    return launch_kernel(kern, dim3(n_blocks), dim3(kThreads), smem, stream, kp, qp, kp_, vp, dop,
+                         static_cast<const float*>(delta), static_cast<const float*>(lse2),
+                         static_cast<OutT*>(dk), static_cast<OutT*>(dv));
   }
   return 0;
 }

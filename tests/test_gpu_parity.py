@@ -216,6 +216,13 @@ def test_every_pair_has_one_workgroup(shape, win):
     run_case(shape, win, (win[0] // 2, win[1] // 2), B.AERIS_MASK_SWIN, seed=55)
 
 
+@pytest.mark.parametrize("win", [(2, 2), (12, 16), (13, 15)])
+def test_head_dim_128_dkdv_by_window_size(win):
+    """4 and 192 tokens: the generic dK/dV kernel; 195: the software-pipelined one."""
+    run_case((1, win[0] * 2, win[1] * 3, 2, 128), win, (win[0] // 2, win[1] // 2), B.AERIS_MASK_SWIN,
+             seed=56)
+
+
 @pytest.mark.parametrize("shift", [(0, 0), (5, 7)])
 def test_one_window_is_global_attention(shift):
     run_case((1, 24, 40, 2, 64), (24, 40), shift, B.AERIS_MASK_NONE, seed=61)
