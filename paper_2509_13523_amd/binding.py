@@ -175,8 +175,10 @@ def aeris_winattn_bwd_workspace_bytes(params):
 
 
 def _stream():
+    """Handle of the current stream of the current device, without a Stream object around it (which
+    costs about as much host time as the rest of a call's argument handling)."""
     import torch
-    return torch.cuda.current_stream().cuda_stream
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _torch_out_dtype(out_dtype):
