@@ -30,22 +30,41 @@ __host__ __device__ inline long long stat_entries(const KParams& p) {
 // delta and LSE*log2e in window order.  One thread per 8 channels of one token
 // of one (batch, window, head); the D/8 threads of a token reduce by shuffles.
 // ----------------------------------------------------------------------------
-__device__ __forceinline__ void load8(const bf16_t* src, float* out) {
-  const u32x4 r = *reinterpret_cast<const u32x4*>(src);
+// Eight channels as they lie in memory, and their values.
+template <typename T>
+struct Raw8;
+template <>
+struct Raw8<bf16_t> {
+  u32x4 r;
+  __device__ __forceinline__ void load(const bf16_t* src) { r = *reinterpret_cast<const u32x4*>(src); }
+  __device__ __forceinline__ void values(float* out) const {
 #pragma unroll
-  for (int w = 0; w < 4; ++w) {
-    out[2 * w] = __uint_as_float(r[w] << 16);
-    out[2 * w + 1] = __uint_as_float(r[w] & 0xffff0000u);
+    for (int w = 0; w < 4; ++w) {
+      out[2 * w] = __uint_as_float(r[w] << 16);
+      out[2 * w + 1] = __uint_as_float(r[w] & 0xffff0000u);
+    }
   }
-}
-__device__ __forceinline__ void load8(const float* src, float* out) {
-  const f32x4 a = *reinterpret_cast<const f32x4*>(src);
-  const f32x4 b = *reinterpret_cast<const f32x4*>(src + 4);
+};
+template <>
+struct Raw8<float> {
+  f32x4 a, b;
+  __device__ __forceinline__ void load(const float* src) {
+    a = *reinterpret_cast<const f32x4*>(src);
+    b = *reinterpret_cast<const f32x4*>(src + 4);
+  }
+  __device__ __forceinline__ void values(float* out) const {
 #pragma unroll
-  for (int w = 0; w < 4; ++w) {
-    out[w] = a[w];
-    out[4 + w] = b[w];
+    for (int w = 0; w < 4; ++w) {
+      out[w] = a[w];
+      out[4 + w] = b[w];
+    }
   }
+};
+template <typename T>
+__device__ __forceinline__ void load8(const T* src, float* out) {
+  Raw8<T> raw;
+  raw.load(src);
+  raw.values(out);
 }
 
 template <int D, typename OT>
@@ -179,12 +198,21 @@ __global__ __launch_bounds__(kThreads, 2) void winattn_dq_kernel(
     // delta = sum_c dO*O with the summation tree of winattn_delta_kernel: an fma chain over
     // the 8 channels of a chunk, then pairwise over the chunk index (bit 0 first).  This lane
     // holds chunks 2*kk + g; the partner lane (l ^ 32) holds the other chunk of every pair.
+    // Every load is issued before the first value is used.  Short windows are bound by round trips
+    // to memory, and left to itself the compiler may take the chunks and the log-sum-exp one after
+    // the other, each behind the chain of the one before (head_dim 32, 8 heads, dQ, us: 4 tokens
+    // 237 -> 221, 16: 175 -> 163, 25: 79 -> 74, 144: 74 -> 67; head_dim 128, 16 tokens: 600 -> 562).
     const OutT* orow = o + o_base + (long long)q_grid * p.o_tok + 8 * g;
+    Raw8<OutT> o8[D / 16];
+#pragma unroll
+    for (int kk = 0; kk < D / 16; ++kk) o8[kk].load(orow + kk * 16);
+    lse2 = lse[((long long)win.b * p.nh + win.head) * plane + q_grid];
+    sched_fence();
     float part[D / 16];
 #pragma unroll
     for (int kk = 0; kk < D / 16; ++kk) {
       float a[8];
-      load8(orow + kk * 16, a);
+      o8[kk].values(a);
       float acc1 = 0.f;
 #pragma unroll
       for (int i = 0; i < 8; ++i) acc1 = __builtin_fmaf(a[i], (float)doreg[kk][i], acc1);
@@ -197,7 +225,7 @@ __global__ __launch_bounds__(kThreads, 2) void winattn_dq_kernel(
 #pragma unroll
       for (int kk = 0; kk < D / 16; kk += 2 * s2) part[kk] += part[kk + s2];
     delta_q = part[0];
-    lse2 = lse[((long long)win.b * p.nh + win.head) * plane + q_grid] * kLog2e;
+    lse2 *= kLog2e;
     if (rg.valid && g == 0) {
       delta[(long long)pair * p.T + rg.tok] = delta_q;
       lse2v[(long long)pair * p.T + rg.tok] = lse2;
