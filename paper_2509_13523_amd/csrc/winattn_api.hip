@@ -72,6 +72,7 @@ aeris::KParams derive(const aeris_winattn_params* p, const Strides& s) {
   k.n_win = k.nWy * k.nWx;
   k.win_list = nullptr;
   k.n_pairs = k.B * k.n_win * k.nh;
+  k.n_whole = 0;
   k.scale = p->softmax_scale > 0.f ? p->softmax_scale : 1.f / sqrtf((float)p->head_dim);
   k.scale_log2 = k.scale * 1.4426950408889634f;
   k.qkv_tok = k.q_tok = k.k_tok = s.qkv_tok;

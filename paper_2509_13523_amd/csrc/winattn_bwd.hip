@@ -207,7 +207,7 @@ __global__ __launch_bounds__(kThreads, 2) void winattn_dq_kernel(
 #pragma unroll
     for (int kk = 0; kk < D / 16; ++kk) o8[kk].load(orow + kk * 16);
     lse2 = lse[((long long)win.b * p.nh + win.head) * plane + q_grid];
-    sched_fence();
+    __builtin_amdgcn_sched_barrier(0x7);   // arithmetic may cross, the loads may not
     float part[D / 16];
 #pragma unroll
     for (int kk = 0; kk < D / 16; ++kk) {
@@ -642,7 +642,7 @@ __global__ __launch_bounds__(kThreads, 2) void winattn_dkdv_kernel(
 constexpr int kPipeAboveTokens = 192;
 
 template <int D, typename OutT>
-static int launch_bwd_t(const KParams& kp, const void* q, const void* k, const void* v,
+static int launch_bwd_t(KParams kp, const void* q, const void* k, const void* v,
                         const void* o, const float* lse, const void* d_o, void* dq, void* dk,
                         void* dv, float* workspace, hipStream_t stream, unsigned stages) {
   const bf16_t* qp = static_cast<const bf16_t*>(q);
@@ -665,6 +665,7 @@ static int launch_bwd_t(const KParams& kp, const void* q, const void* k, const v
   const int n_blocks = grid_blocks(kp);
   if (stages & 2u) {
     const size_t smem = dq_smem_bytes<D>(kp.T);
+    kp.n_whole = whole_windows(kp, AttnKernel::kDq, D);
     auto kern = winattn_dq_kernel<D, OutT>;
     if (!allow_full_lds<winattn_dq_kernel<D, OutT>>()) return -1;
     if (launch_kernel(kern, dim3(n_blocks), dim3(kThreads), smem, stream, kp, qp, kp_, vp, dop,
@@ -673,6 +674,7 @@ static int launch_bwd_t(const KParams& kp, const void* q, const void* k, const v
       return -1;
   }
   if (stages & 4u) {
+    kp.n_whole = whole_windows(kp, AttnKernel::kDkDv, D);
     if constexpr (D == 128) {
       if (kp.T > kPipeAboveTokens)
         return launch_dkdv_pipe128(kp, std::is_same<OutT, float>::value, q, k, v, d_o, delta, lse2,

@@ -45,6 +45,8 @@ struct KParams {
   int T;               // tokens per window
   int n_tiles;         // resident-side tiles per window = ceil(T / kResident)
   int n_pairs;         // B * n_win * nh
+  int n_whole;         // windows (over the batch) whose heads are dealt to one XCD together, a multiple
+                       // of 8 (0: none); set per kernel by its launch
   float scale;         // softmax scale
   float scale_log2;    // scale * log2(e)
   long long qkv_tok, qkv_head;  // element strides of v and of dq, dk, dv
@@ -69,41 +71,71 @@ __host__ __device__ inline int table_bytes(int T) { return ((T + kStream - 1) / 
 // turn.  All tiles of one pair (batch, window, head) run on one XCD, so the K/V (or Q/dO) rows
 // they all stream are shared through its L2.
 //
-// Long windows, bound by matrix products: pairs are dealt to XCDs round-robin (pair % 8), which
-// balances seam windows -- they carry less work -- across XCDs.
-// Short windows (32 to kGroupHeadsTokens tokens), bound by memory: whole windows are dealt to
-// XCDs and the heads of a window follow each other there, so that the pieces of a token's row
-// (2 * head_dim bytes per head, next to each other in memory) are fetched at about the same time
-// through the same L2; round-robin pairs put them on different XCDs, where 64-byte pieces
-// (head_dim 32) fetch every 128-byte line twice.  Which XCD a window goes to turns with the digits
-// of its index, so that a column of seam windows does not fall on one XCD; the last n % 8 windows
-// are dealt pair by pair.  Measured over 65,000 to 86,000 tokens, 8 heads (forward / dQ / dK-dV,
-// us): 64 tokens, head_dim 64: 99 / 152 / 135 -> 86 / 127 / 126; 144: 82 / 165 / 186 -> 82 / 139 /
-// 160; 256: 55 / 113 / 128 -> 57 / 99 / 119, head_dim 32: 42 / 59 / 61 -> 37 / 51 / 58; 576,
-// head_dim 64: 112 / 167 / 215 -> 114 / 164 / 218 (16 heads: 240 / 337 / 424 -> 224 / 320 / 414).
-// Outside: 900 tokens 162 / 225 / 272 -> 167 / 228 / 277, 16 tokens 197 / 301 -> 213 / 307.
+// As a rule pairs are dealt to XCDs round-robin (pair % 8), which balances seam windows -- they
+// carry less work -- across XCDs.  Two kinds of rows suffer from it while windows are short enough
+// to be bound by memory:
+//  - head_dim 32: a head's piece of a token row is half a 128-byte line, and neighbouring heads on
+//    different XCDs fetch every line twice;
+//  - rows of a multiple of 1 KB: an XCD's pairs then read pieces that all lie multiples of 1 KB
+//    apart (8 heads of 64: always the same head) and crowd a few channels of its L2 and of memory.
+// There, whole windows are dealt to XCDs and the heads of a window follow each other on one.
+// Which XCD a window goes to turns with the digits of its index, so that a column of seam windows
+// does not fall on one XCD; the last n % 8 windows are dealt pair by pair.
 // Grid size: grid_blocks().  Returns false for padding.
+//
+// Ratio of times, whole windows to round-robin (1 to 16 heads, 65,000 and 300,000 tokens; a single
+// point repeats to 2 %):
+//   head_dim 32, 2 to 16 heads  49-121 tokens  144-256    324-400    529-640    900
+//     forward                   0.75-1.00      0.82-1.05  0.97-1.04  0.98-1.04  0.99-1.05
+//     dQ                        0.68-0.92      0.77-0.97  0.89-1.00  0.91-1.02  0.94-1.07
+//     dK/dV                     0.69-0.95      0.74-1.00  0.94-1.01  0.96-1.04  0.98-1.06
+//   head_dim 64, 8 and 16 heads 49-121         144-256    324-400    529-784    900
+//     forward                   0.87-1.00      0.87-1.01  0.93-1.00  0.97-1.04  1.00-1.06
+//     dQ                        0.83-0.91      0.83-0.90  0.88-0.94  0.91-0.97  0.96-1.02
+//     dK/dV                     0.87-0.97      0.86-0.95  0.91-0.95  0.95-1.01  0.97-1.02
+//   head_dim 128, 4, 8, 12, 16  49-121         144-256    324-400    529-784    900
+//     forward                   0.93-1.10      0.94-1.02  0.94-1.00  0.95-1.02  0.99-1.03
+//     dQ                        0.97-1.06      0.94-1.02  0.93-0.98  0.96-1.00  0.97-1.03
+//   other head counts at 64 and 128, and one head of 32: 0.97-1.05 everywhere.
 // ----------------------------------------------------------------------------
-constexpr int kGroupHeadsTokens = 640;
+struct WholeWindows {
+  int from, to;   // tokens of a window
+};
+enum class AttnKernel { kForward, kDq, kDkDv };
+// The ranges in which the ratios above are below 1 but for single points.  Below, workgroups live for
+// a few microseconds and the longer way to the work item shows; above, products take over from
+// memory; at head_dim 128 windows of a single resident tile (up to kResident tokens) have nothing to
+// share between workgroups.
+constexpr WholeWindows whole_window_range(AttnKernel kernel, int head_dim) {
+  if (head_dim == 128) return {kResident + 1, 784};
+  if (head_dim == 64) return kernel == AttnKernel::kForward ? WholeWindows{36, 400} : WholeWindows{36, 784};
+  return kernel == AttnKernel::kForward ? WholeWindows{40, 256} : WholeWindows{32, 576};
+}
 
 // Windows dealt whole; the pairs of the others, if any, are dealt round-robin.
-__host__ __device__ inline int grouped_windows(const KParams& p) {
-  return p.T >= 32 && p.T <= kGroupHeadsTokens ? (p.B * p.n_win) & ~7 : 0;
+inline int whole_windows(const KParams& p, AttnKernel kernel, int head_dim) {
+  const WholeWindows range = whole_window_range(kernel, head_dim);
+  const bool shared_lines = head_dim == 32 && p.nh > 1;
+  const bool crowded = (long long)p.nh * head_dim * 2 % 1024 == 0;
+  return (shared_lines || crowded) && p.T >= range.from && p.T <= range.to ? (p.B * p.n_win) & ~7 : 0;
 }
 __device__ __forceinline__ bool block_to_work(const KParams& p, int& pair, int& tile) {
   const int id = blockIdx.x;
   const int xcd = id & 7, slot = id >> 3;
   const int local = slot / p.n_tiles;
   tile = slot - local * p.n_tiles;
-  const int whole = grouped_windows(p);
-  const int grouped = (whole >> 3) * p.nh;     // pairs of whole windows per XCD
+  if (p.n_whole == 0) {   // first, and cheap: workgroups of the shortest windows live for 3 us
+    pair = local * 8 + xcd;
+    return pair < p.n_pairs;
+  }
+  const int grouped = (p.n_whole >> 3) * p.nh;     // pairs of whole windows per XCD
   if (local < grouped) {
     const int w = local / p.nh;
     const int turn = w + (w >> 3) + (w >> 6) + (w >> 9);
     pair = (w * 8 + ((xcd + turn) & 7)) * p.nh + (local - w * p.nh);
     return true;
   }
-  pair = whole * p.nh + (local - grouped) * 8 + xcd;
+  pair = p.n_whole * p.nh + (local - grouped) * 8 + xcd;
   return pair < p.n_pairs;
 }
 __host__ __device__ inline int grid_blocks(const KParams& p) {

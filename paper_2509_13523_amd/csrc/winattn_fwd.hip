@@ -295,6 +295,7 @@ template <int D, typename OutT, int W>
 static int launch_fwd_w(KParams kp, const void* q, const void* k, const void* v, void* o,
                         float* lse, hipStream_t stream) {
   kp.n_tiles = (kp.T + W * 32 - 1) / (W * 32);
+  kp.n_whole = whole_windows(kp, AttnKernel::kForward, D);
   const int n_blocks = grid_blocks(kp);
   const size_t smem = fwd_smem_bytes<D>(kp.T);
   auto kern = winattn_fwd_kernel<D, OutT, W>;

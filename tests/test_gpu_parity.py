@@ -216,6 +216,24 @@ def test_every_pair_has_one_workgroup(shape, win):
     run_case(shape, win, (win[0] // 2, win[1] // 2), B.AERIS_MASK_SWIN, seed=55)
 
 
+@pytest.mark.parametrize("heads,d,win", [
+    (2, 32, (31, 1)), (2, 32, (8, 4)),        # from 32 tokens: dQ and dK/dV
+    (2, 32, (13, 3)), (3, 32, (8, 5)),        # from 40: the forward kernel too
+    (3, 32, (16, 16)), (3, 32, (13, 20)),     # up to 256: the forward kernel
+    (2, 32, (24, 24)), (2, 32, (20, 29)),     # up to 576: the others
+    (1, 32, (8, 8)),                          # one head: never
+    (16, 32, (8, 8)),
+    (8, 64, (5, 7)), (8, 64, (6, 6)),         # rows of a multiple of 1 KB: from 36 tokens
+    (8, 64, (20, 20)), (8, 64, (18, 23)),     # up to 400: the forward kernel
+    (8, 64, (28, 28)), (8, 64, (28, 29)),     # up to 784: the others
+    (4, 128, (8, 16)), (4, 128, (43, 3)),     # from 129 tokens
+    (4, 128, (28, 28)), (4, 128, (28, 29)),   # up to 784
+])
+def test_whole_windows_dealt_to_an_xcd(heads, d, win):
+    """The edges of the ranges in which whole windows, eight of these nine, are dealt to XCDs."""
+    run_case((1, win[0], win[1] * 9, heads, d), win, (win[0] // 2, win[1] // 2), B.AERIS_MASK_SWIN, seed=57)
+
+
 @pytest.mark.parametrize("win", [(2, 2), (12, 16), (13, 15)])
 def test_head_dim_128_dkdv_by_window_size(win):
     """4 and 192 tokens: the generic dK/dV kernel; 195: the software-pipelined one."""
