@@ -416,11 +416,25 @@ __global__ __launch_bounds__(kThreads, 2) void winattn_dq_kernel(
 
 // ----------------------------------------------------------------------------
 // dK, dV: keys resident (one per lane pair), queries streamed.
-// LDS: table + 2 buffers x (Q tile, dO tile, 64 x LSE*log2e, 64 x delta).
+// LDS: table + 2 buffers x (Q tile, dO tile, 64 x LSE*log2e, 64 x delta) + parked rows.
+//
+// Registers bound this kernel.  At head_dim 128 two accumulators of 64, 64 for the resident rows and
+// 48 for logits and operands in flight leave about 20 of the 256 that two waves per SIMD have, so
+// there it keeps one LDS address per kind of operand read (LeanLanes), tensor origins in scalar
+// registers (LeanFiller), and the first contraction block of the resident K and V rows parked in the
+// LDS.  With all of that in registers it spilled 21 and read 64 bytes per lane back from scratch in
+// every block of 32 queries, each time behind the copies in flight: 13 heads, 380,000 tokens, us: 64
+// tokens 2268 -> 1596, 100: 2495 -> 1741, 144: 3624 -> 2583, 900: 6197 -> 4984.
 // ----------------------------------------------------------------------------
+
+// Contraction blocks parked, and the bytes of one (16 per lane).
+template <int D>
+constexpr int kParkedBlocks = D == 128 ? 1 : 0;
+constexpr int kParkBytes = kThreads * 16;
+
 template <int D>
 constexpr size_t dkdv_smem_bytes(int T) {
-  return table_bytes(T) + 2 * (2 * Tile<D>::kBytes + 2 * kStream * 4);
+  return table_bytes(T) + 2 * (2 * Tile<D>::kBytes + 2 * kStream * 4) + kParkedBlocks<D> * 2 * kParkBytes;
 }
 
 template <int D, typename OutT>
@@ -459,16 +473,16 @@ __global__ __launch_bounds__(kThreads, 2) void winattn_dkdv_kernel(
 
   // one streamed tile: Q, dO (all waves), LSE*log2e (wave 0), delta (wave 1)
   typename Tl::Rows rows;
-  typename Tl::Filler qfill, dofill;
+  typename std::conditional<D == 128, typename Tl::LeanFiller, typename Tl::Filler>::type qfill, dofill;
   rows.init(table, wave, lane);
   qfill.init(q + ((long long)win.b * plane) * p.q_tok + (long long)win.head * p.q_head, p.q_tok, wave, lane);
   dofill.init(d_o + o_base, p.o_tok, wave, lane);
-  const float* stat_src = (wave == 0 ? lse2v : delta) + (long long)pair * p.T + lane;
+  const float* stat_src = (wave == 0 ? lse2v : delta) + (long long)pair * p.T;
   // launches the fill of tile t0, whose table entries `rows` holds
   auto fill = [&](uint32_t buf, int t0) __attribute__((always_inline)) {
     qfill.issue(buf, rows);
     dofill.issue(buf + Tl::kBytes, rows);
-    if (wave < 2) async_copy4(stat_src + t0, buf + kStat + wave * (kStream * 4));
+    if (wave < 2) async_copy4(stat_src + (t0 + lane), buf + kStat + wave * (kStream * 4));
   };
 
   const int qt_begin = rg.wg_lo / kStream;
@@ -488,12 +502,19 @@ __global__ __launch_bounds__(kThreads, 2) void winattn_dkdv_kernel(
       vreg[kk] = *reinterpret_cast<const bf16x8*>(vrow + kk * 16);
     }
   }
-  typename Tl::Lanes la;
+  typename std::conditional<D == 128, typename Tl::LeanLanes, typename Tl::Lanes>::type la;
   la.init(tiles, lane);
+  constexpr int kParked = kParkedBlocks<D>;   // K, then V; a lane reads only what it wrote: no barrier
+  uint32_t park = tiles + 2 * kBuf + tid * 16;
+#pragma unroll
+  for (int kk = 0; kk < kParked; ++kk) {
+    *reinterpret_cast<AERIS_LDS bf16x8*>(park + 2 * kk * kParkBytes) = kreg[kk];
+    *reinterpret_cast<AERIS_LDS bf16x8*>(park + (2 * kk + 1) * kParkBytes) = vreg[kk];
+  }
   uint32_t stat_lane = tiles + kStat + 4 * g * 4;   // rows 8*vq + 4*g + (0..3) of a sub-block
   settle(stat_lane);
 #pragma unroll
-  for (int kk = 0; kk < D / 16; ++kk) {
+  for (int kk = kParked; kk < D / 16; ++kk) {
     settle(kreg[kk]);
     settle(vreg[kk]);
   }
@@ -510,6 +531,7 @@ __global__ __launch_bounds__(kThreads, 2) void winattn_dkdv_kernel(
     constexpr uint32_t kOff = decltype(off)::value;
     constexpr uint32_t kStatOff = decltype(stat_off)::value;
     if (rg.skip(sub_lo)) return;
+    la.begin_block();
     // head_dim 64: every operand is read first, products after, so that LDS latency hides behind
     // the MFMA pipeline (228 registers, two waves per SIMD).  The others read operands one block of
     // products ahead and the statistics four rows at a time, in fenced order.  head_dim 32 has too
@@ -517,14 +539,15 @@ __global__ __launch_bounds__(kThreads, 2) void winattn_dkdv_kernel(
     // four waves per SIMD instead of three (65,000 tokens, 8 heads, windows of 144 / 256 / 400 / 900
     // tokens: 73 / 58 / 100 / 167 -> 67 / 53 / 93 / 162 us; the same order at head_dim 64, where it
     // fits 168 registers: 160 / 119 / 195 / 303 -> 165 / 127 / 187 / 297, and 126 -> 159 at 64).
-    // head_dim 128 fits two waves per SIMD only this way.
+    // head_dim 128 has no registers for the former.
     constexpr bool kLean = D != 64;
     constexpr int kNK = D / 16;
     bf16x8 qa[kNK], doa[kNK], dota[kNK], qta[kNK];
     f32x4 l4[4], d4[4];
     auto fetch_rows = [&](int kk) __attribute__((always_inline)) {
-      qa[kk] = Tl::read_rm(la.rm[kk] + kOff);
-      doa[kk] = Tl::read_rm(la.rm[kk] + kOff + Tl::kBytes);
+      const uint32_t rm = la.row_major(kk);
+      qa[kk] = Tl::read_rm(rm + kOff);
+      doa[kk] = Tl::read_rm(rm + kOff + Tl::kBytes);
     };
     auto fetch_stat = [&](int vq) __attribute__((always_inline)) {
       l4[vq] = *reinterpret_cast<const AERIS_LDS f32x4*>(stat_lane + kStatOff + vq * 32);
@@ -534,12 +557,22 @@ __global__ __launch_bounds__(kThreads, 2) void winattn_dkdv_kernel(
     // channel block j / 2, 16-query group j % 2
     auto fetch_tr = [&](int j) __attribute__((always_inline)) {
       const uint32_t off = kOff + (j & 1) * Tl::kGroupBytes;
-      dota[j] = Tl::read_tr(la.tr[j >> 1][0] + off + Tl::kBytes, la.tr[j >> 1][1] + off + Tl::kBytes);
-      qta[j] = Tl::read_tr(la.tr[j >> 1][0] + off, la.tr[j >> 1][1] + off);
+      const uint32_t t0 = la.transposed(j >> 1, 0), t1 = la.transposed(j >> 1, 1);
+      dota[j] = Tl::read_tr(t0 + off + Tl::kBytes, t1 + off + Tl::kBytes);
+      qta[j] = Tl::read_tr(t0 + off, t1 + off);
     };
     auto fence = [&]() __attribute__((always_inline)) {
       if constexpr (kLean) sched_fence();
     };
+    bf16x8 kpark[kParked + 1], vpark[kParked + 1];
+    if constexpr (kParked != 0) {
+      settle(park);   // read again in every block, not kept
+#pragma unroll
+      for (int kk = 0; kk < kParked; ++kk) {
+        kpark[kk] = Tl::read_rm(park + 2 * kk * kParkBytes);
+        vpark[kk] = Tl::read_rm(park + (2 * kk + 1) * kParkBytes);
+      }
+    }
 #pragma unroll
     for (int kk = 0; kk < (kLean ? 1 : kNK); ++kk) fetch_rows(kk);
     if constexpr (!kLean) {
@@ -554,8 +587,8 @@ __global__ __launch_bounds__(kThreads, 2) void winattn_dkdv_kernel(
 #pragma unroll
     for (int kk = 0; kk < kNK; ++kk) {
       if (kLean && kk + 1 < kNK) fetch_rows(kk + 1);
-      s = mfma32(qa[kk], kreg[kk], s);
-      dp = mfma32(doa[kk], vreg[kk], dp);
+      s = mfma32(qa[kk], kk < kParked ? kpark[kk] : kreg[kk], s);
+      dp = mfma32(doa[kk], kk < kParked ? vpark[kk] : vreg[kk], dp);
       fence();
     }
     if constexpr (!kLean) {
@@ -634,12 +667,14 @@ __global__ __launch_bounds__(kThreads, 2) void winattn_dkdv_kernel(
     }
 }
 
-// head_dim 128: windows of at most this many tokens run the generic dK/dV kernel, two workgroups per
-// CU; longer ones the software-pipelined kernel, whose one workgroup per CU needs a loop of several
-// tiles to pay for its prologue and epilogue.  Pipelined against generic, 8 heads, 32,000 to 86,000
-// tokens, us: 4 tokens 1460 / 773, 16: 1033 / 659, 36: 539 / 432, 64: 394 / 334, 100: 304 / 284,
-// 144: 425 / 391, 192: 287 / 278; 256: 265 / 280, 289: 394 / 402, 576: 473 / 490, 900: 635 / 658.
-constexpr int kPipeAboveTokens = 192;
+// head_dim 128: windows run the generic dK/dV kernel as long as two of its workgroups, token tables
+// included, fit the LDS of a CU (up to 1792 tokens), longer ones the software-pipelined kernel, whose
+// one workgroup per CU must overlap everything by itself.  Generic / pipelined, 65,000 tokens with 1,
+// 3, 8, 16 heads, 380,000 with 4, 13, 16 and 1,036,800 with 16: 4 tokens 0.42, 64: 0.66-0.72, 100:
+// 0.67-0.77, 144: 0.63-0.68, 256: 0.71-0.82, 400: 0.66-0.79, 576: 0.73-0.83, 900: 0.74-0.83, 1296:
+// 0.78-0.84, 1600: 0.79-0.87; 2025: 1.03-1.04, 2304: 1.04-1.07, 2500: 1.02-1.04, 2916: 1.03-1.05, 3249:
+// 1.04-1.06, 3600: 1.03-1.04, 4096: 1.04-1.06.  Same bits from both.
+constexpr size_t kLdsOfCu = 160 * 1024;
 
 template <int D, typename OutT>
 static int launch_bwd_t(KParams kp, const void* q, const void* k, const void* v,
@@ -676,7 +711,7 @@ static int launch_bwd_t(KParams kp, const void* q, const void* k, const void* v,
   if (stages & 4u) {
     kp.n_whole = whole_windows(kp, AttnKernel::kDkDv, D);
     if constexpr (D == 128) {
-      if (kp.T > kPipeAboveTokens)
+      if (2 * dkdv_smem_bytes<D>(kp.T) > kLdsOfCu)
         return launch_dkdv_pipe128(kp, std::is_same<OutT, float>::value, q, k, v, d_o, delta, lse2,
                                    dk, dv, stream);
     }

@@ -96,6 +96,7 @@ __host__ __device__ inline int table_bytes(int T) { return ((T + kStream - 1) / 
 //   head_dim 128, 4, 8, 12, 16  49-121         144-256    324-400    529-784    900
 //     forward                   0.93-1.10      0.94-1.02  0.94-1.00  0.95-1.02  0.99-1.03
 //     dQ                        0.97-1.06      0.94-1.02  0.93-0.98  0.96-1.00  0.97-1.03
+//     dK/dV                     0.96-1.02      0.95-0.99  0.94-0.98  0.97-1.01  0.98-1.05
 //   other head counts at 64 and 128, and one head of 32: 0.97-1.05 everywhere.
 // ----------------------------------------------------------------------------
 struct WholeWindows {
@@ -545,6 +546,25 @@ struct Tile {
     }
   };
 
+  // The same copies with the tensor's origin in scalar registers and one 32-bit lane offset for all
+  // tensors, for kernels without registers to spare.
+  struct LeanFiller {
+    unsigned long long origin;       // wave-uniform
+    uint32_t dst, stride_bytes, chunk;
+    __device__ __forceinline__ void init(const bf16_t* org, long long tok_stride, int wave, int lane) {
+      origin = reinterpret_cast<unsigned long long>(org);
+      stride_bytes = (uint32_t)(tok_stride * 2);
+      dst = wave * 1024;
+      chunk = ((lane % NC) ^ swz(wave * kRowsPerInst + lane / NC)) * 16;
+    }
+    __device__ __forceinline__ void issue(uint32_t tile, const Rows& rows) const {
+#pragma unroll
+      for (int i = 0; i < kFillPerWave; ++i)
+        async_copy16(reinterpret_cast<const char*>(origin + ((unsigned long long)rows.g[i] * stride_bytes + chunk)),
+                     tile + dst + i * kInstStep);
+    }
+  };
+
   // Per-lane LDS byte addresses (buffer 0, sub-block 0) of the operand reads.
   struct Lanes {
     uint32_t rm[D / 16];        // row-major: contraction block kk
@@ -571,6 +591,35 @@ struct Tile {
         settle(tr[cb][0]);
         settle(tr[cb][1]);
       }
+    }
+    __device__ __forceinline__ uint32_t row_major(int kk) const { return rm[kk]; }
+    __device__ __forceinline__ uint32_t transposed(int cb, int h) const { return tr[cb][h]; }
+    __device__ __forceinline__ void begin_block() {}
+  };
+
+  // The same addresses from one base each, for kernels without registers to spare: the chunk index
+  // is XORed into the address, so contraction blocks and channel blocks differ in single bits of it.
+  // Needs tile0 to be a multiple of the row length, so that no carry reaches those bits: the dynamic
+  // LDS starts at 0 and the token table in front of the tiles is a multiple of 256 bytes.
+  struct LeanLanes {
+    uint32_t rm0, tr0;
+    __device__ __forceinline__ void init(uint32_t tile0, int lane) {
+      const int row = lane & 31, g = lane >> 5;
+      rm0 = tile0 + chunk_offset(row, g);
+      const int j = lane & 15, blk = lane >> 4;
+      tr0 = tile0 + chunk_offset(4 * (blk >> 1) + (j >> 2), 2 * (blk & 1) + ((j & 3) >> 1)) + (j & 1) * 8;
+      settle(rm0);
+      settle(tr0);
+    }
+    __device__ __forceinline__ uint32_t row_major(int kk) const { return rm0 ^ (uint32_t)(kk << 5); }
+    // once per block of tokens: keeps the compiler from working all addresses out ahead of the loop
+    __device__ __forceinline__ void begin_block() {
+      settle(rm0);
+      settle(tr0);
+    }
+    // second four tokens: eight rows on, where swz() differs in bit 1
+    __device__ __forceinline__ uint32_t transposed(int cb, int h) const {
+      return (tr0 ^ (uint32_t)((cb << 6) | (h << 5))) + h * 8 * D * 2;
     }
   };
 

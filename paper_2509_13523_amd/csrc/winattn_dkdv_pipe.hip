@@ -1,6 +1,6 @@
-// dK/dV kernel, software-pipelined variant (used for head_dim 128 and windows of more than 192
-// tokens: the two 128x32 accumulators and the operands in flight leave room for only one wave per
-// SIMD, so nothing but the instruction order inside the wave can overlap matrix and vector work).
+// dK/dV kernel, software-pipelined variant (used for head_dim 128 and windows of more than 1792
+// tokens, of which the generic kernel fits only one workgroup into a CU: with one wave per SIMD
+// nothing but the instruction order inside the wave can overlap matrix and vector work).
 //
 // Same mathematics and data flow as winattn_dkdv_kernel (see winattn_bwd.hip):
 // keys resident, queries streamed through LDS tiles, S = Q K^T and dP = dO V^T

@@ -234,9 +234,9 @@ def test_whole_windows_dealt_to_an_xcd(heads, d, win):
     run_case((1, win[0], win[1] * 9, heads, d), win, (win[0] // 2, win[1] // 2), B.AERIS_MASK_SWIN, seed=57)
 
 
-@pytest.mark.parametrize("win", [(2, 2), (12, 16), (13, 15)])
+@pytest.mark.parametrize("win", [(2, 2), (12, 16), (13, 15), (28, 64), (33, 55)])
 def test_head_dim_128_dkdv_by_window_size(win):
-    """4 and 192 tokens: the generic dK/dV kernel; 195: the software-pipelined one."""
+    """Up to 1792 tokens the generic dK/dV kernel; 1815: the software-pipelined one."""
     run_case((1, win[0] * 2, win[1] * 3, 2, 128), win, (win[0] // 2, win[1] // 2), B.AERIS_MASK_SWIN,
              seed=56)
 

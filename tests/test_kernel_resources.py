@@ -1,0 +1,50 @@
+"""No kernel of the built library keeps registers in scratch memory: a reload inside a main loop waits
+behind the copies in flight and undoes their overlap with the products.  Read from the metadata that
+the compiler writes into the code objects of this library."""
+import struct
+
+import pytest
+
+from paper_2509_13523_amd import build
+
+msgpack = pytest.importorskip("msgpack")
+MAGIC = b"__CLANG_OFFLOAD_BUNDLE__"
+
+
+def code_objects(blob):
+    """The gfx950 ELF images of every offload bundle in a shared library."""
+    at = blob.find(MAGIC)
+    while at >= 0:
+        (count,) = struct.unpack_from("<Q", blob, at + len(MAGIC))
+        pos = at + len(MAGIC) + 8
+        for _ in range(count):
+            offset, size, name_len = struct.unpack_from("<QQQ", blob, pos)
+            name = blob[pos + 24:pos + 24 + name_len]
+            pos += 24 + name_len
+            if b"gfx950" in name and size:
+                yield blob[at + offset:at + offset + size]
+        at = blob.find(MAGIC, at + 1)
+
+
+def kernel_metadata(elf):
+    (shoff,) = struct.unpack_from("<Q", elf, 0x28)
+    entry, number = struct.unpack_from("<HH", elf, 0x3A)
+    for i in range(number):
+        kind, _, _, offset, size = struct.unpack_from("<IQQQQ", elf, shoff + i * entry + 4)
+        pos, end = offset, offset + size
+        while kind == 7 and pos < end:                       # SHT_NOTE
+            name_size, desc_size, note = struct.unpack_from("<III", elf, pos)
+            desc = pos + 12 + (name_size + 3) // 4 * 4
+            if elf[pos + 12:pos + 18] == b"AMDGPU" and note == 32:
+                yield from msgpack.unpackb(elf[desc:desc + desc_size])["amdhsa.kernels"]
+            pos = desc + (desc_size + 3) // 4 * 4
+
+
+def test_no_kernel_uses_scratch_memory():
+    with open(build.LIB, "rb") as f:
+        blob = f.read()
+    kernels = [k for elf in code_objects(blob) for k in kernel_metadata(elf)]
+    assert sum("winattn_dkdv" in k[".name"] for k in kernels) == 8    # generic at 32, 64, 128, pipelined
+    bad = {k[".name"]: (k[".private_segment_fixed_size"], k[".vgpr_spill_count"]) for k in kernels
+           if k[".private_segment_fixed_size"] or k[".vgpr_spill_count"]}
+    assert not bad
