@@ -1,8 +1,6 @@
 /*
- * aeris_probe.h -- measurement aid shipped with the shifted-window attention library; not part
- * of the attention path and not needed by its callers.  bench.py uses it to report, next to the
- * fraction of the published MFMA peak, the fraction of the MFMA rate this machine sustains under
- * its power limit.
+ * aeris_probe.h -- aids for measuring and testing shipped with the shifted-window attention
+ * library; not part of its paths and not needed by its callers.
  */
 #ifndef AERIS_PROBE_H
 #define AERIS_PROBE_H
@@ -14,6 +12,8 @@ extern "C" {
 #endif
 
 /*
+ * bench.py uses this one to report, next to the fraction of the published MFMA peak, the fraction
+ * of the MFMA rate this machine sustains under its power limit.
  * Launches `blocks` workgroups of 256 threads, each wave issuing
  * 8 * iters v_mfma_f32_32x32x16_bf16 on register operands (32768 FLOP each) and nothing else.
  * random_operands != 0 fills the operands with pseudo-random bf16 values of unit scale, else
@@ -22,6 +22,14 @@ extern "C" {
  */
 int aeris_mfma_loop_probe(int32_t blocks, int32_t iters, int32_t random_operands, float* sink,
                           void* hip_stream);
+
+/*
+ * How aeris_linear_bwd computes dweight at a size it accepts (else its error code): *tile, the
+ * sides of its square workgroup tiles (256, 128 or 64); *ranges, the row ranges whose partial
+ * results are added; *steps, the steps of 64 rows in each but the last.  Launches nothing.
+ */
+int aeris_linear_bwd_plan(int64_t n_rows, int32_t channels, int32_t out_features, int32_t* tile,
+                          int32_t* ranges, int32_t* steps);
 
 #ifdef __cplusplus
 }

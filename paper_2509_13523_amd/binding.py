@@ -20,7 +20,7 @@ EXPORTS = ("aeris_winattn_fwd", "aeris_winattn_bwd", "aeris_winattn_bwd_stages",
            "aeris_winattn_bwd_workspace_bytes", "aeris_winattn_bwd_static",
            "aeris_winattn_validate", "aeris_winattn_strerror", "aeris_winattn_version",
            "aeris_winattn_fwd_windows", "aeris_winattn_bwd_windows",
-           "aeris_mfma_loop_probe", "aeris_rope2d_apply", "aeris_winattn_rope_fwd_workspace_bytes",
+           "aeris_mfma_loop_probe", "aeris_linear_bwd_plan", "aeris_rope2d_apply", "aeris_winattn_rope_fwd_workspace_bytes",
            "aeris_winattn_rope_bwd_workspace_bytes", "aeris_winattn_rope_fwd",
            "aeris_winattn_rope_bwd", "aeris_winattn_rope_fwd_windows",
            "aeris_winattn_rope_bwd_windows",
@@ -94,6 +94,9 @@ def load():
     lib.aeris_winattn_bwd_windows.restype = ctypes.c_int
     lib.aeris_mfma_loop_probe.argtypes = [ctypes.c_int32, ctypes.c_int32, ctypes.c_int32, vp, vp]
     lib.aeris_mfma_loop_probe.restype = ctypes.c_int
+    pi32 = ctypes.POINTER(ctypes.c_int32)
+    lib.aeris_linear_bwd_plan.argtypes = [ctypes.c_int64, ctypes.c_int32, ctypes.c_int32, pi32, pi32, pi32]
+    lib.aeris_linear_bwd_plan.restype = ctypes.c_int
     R = ctypes.POINTER(aeris_rope_params)
     lib.aeris_rope2d_apply.argtypes = [P, R, vp, vp, ctypes.c_int32, vp]
     lib.aeris_rope2d_apply.restype = ctypes.c_int
@@ -428,6 +431,15 @@ def aeris_winattn_rope_bwd_windows(q, k, v, o, lse, d_o, win, shift, base, posit
     if rc != 0:
         raise AerisError(rc, "aeris_winattn_rope_bwd_windows")
     return dq, dk, dv
+
+
+def aeris_linear_bwd_plan(n_rows, channels, out_features):
+    """(sides of a workgroup tile, row ranges, 64-row steps per range) of dweight at this size."""
+    out = [ctypes.c_int32() for _ in range(3)]
+    rc = load().aeris_linear_bwd_plan(n_rows, channels, out_features, *[ctypes.byref(v) for v in out])
+    if rc != 0:
+        raise AerisError(rc, "aeris_linear_bwd_plan")
+    return tuple(v.value for v in out)
 
 
 def aeris_mfma_loop_probe(blocks, iters, random_operands, sink):

@@ -18,6 +18,7 @@
 #include <stdint.h>
 
 #include "aeris_layer_ops.h"
+#include "aeris_probe.h"
 #include "aeris_winattn.h"
 #include "projection_gemm.hpp"
 #include "winattn_common.hpp"
@@ -346,14 +347,42 @@ double wgrad_time(int splits, int per, int32_t channels, int32_t features, doubl
   return steps + fixed * (double)(sets + (left != 0)) + sums;
 }
 
+// Row ranges of the largest tiles, 0 if there is no whole step: enough for about 2048 workgroups, at
+// least 16 steps each and at most 64; among the next few counts the one whose units of 32 tiles (the
+// workgroups an XCD runs at a time) share out to the eight XCDs most evenly.  Fixed by size alone:
+// callers hold workspaces for this many partial tiles, and fewer ranges would be longer chains of
+// additions, which this shape does not break up (23434 x 2112 -> 10560 in 6 ranges of 62 steps instead
+// of 8 of 46: error of dW 2.9e-7 instead of 2.5e-7).
+int large_ranges(int whole_steps, int32_t channels, int32_t features) {
+  const int f_tiles = (features + WgradLarge::kTF - 1) / WgradLarge::kTF;
+  const int c_tiles = (channels + WgradLarge::kTC - 1) / WgradLarge::kTC;
+  const int unit_c = c_tiles >= 8 ? 8 : c_tiles >= 4 ? 4 : c_tiles >= 2 ? 2 : 1, unit_f = 32 / unit_c;
+  const long long units_per_range =
+      (long long)((f_tiles + unit_f - 1) / unit_f) * ((c_tiles + unit_c - 1) / unit_c);
+  const long long tiles = (long long)f_tiles * c_tiles;
+  const int want = (int)(2048 / tiles < 64 ? (2047 + tiles) / tiles : 64);
+  int best = 0;
+  double best_fill = -1.0;
+  for (int target = want; target < want + 8 && target <= 64; ++target) {
+    int per = (whole_steps + target - 1) / target;
+    per = per < 16 ? 16 : per;
+    const int ranges = (whole_steps + per - 1) / per;
+    const long long units = ranges * units_per_range;
+    const double fill = (double)units / (double)((units + 7) / 8 * 8);
+    if (ranges > 0 && fill > best_fill + 1e-9) {
+      best_fill = fill;
+      best = ranges;
+    }
+  }
+  return best;
+}
+
 // The plan that is estimated to end first.  Times per step measured over 1000 ... 172800 rows,
-// 128 ... 5504 channels and 128 ... 11008 features; one tile shape and row ranges of at least 16
-// steps took (start to end, us) 43 / 44 / 98 / 159 / 117 / 79 where this takes
-// 12 / 22 / 80 / 86 / 72 / 55: 1000 x 1024 -> 1024, 4000 x 512 -> 1536, 8000 x 2048 -> 2048,
-// 20011 x 768 -> 2304, 30000 x 1024 -> 1024, 100000 x 256 -> 768.
-// The largest tiles have their rows split for about 2048 workgroups, at least 16 steps each and
-// at most 64 ranges, among the next few counts the one whose rounds of workgroups end first.  The
-// workspace holds that many partial tiles (plan.most); the other shapes use as many or fewer.
+// 128 ... 5504 channels and 128 ... 11008 features; the 256 x 256 shape alone took (start to end, us)
+// 43 / 44 / 98 / 159 / 117 / 79 where this takes 12 / 22 / 80 / 86 / 72 / 55: 1000 x 1024 -> 1024,
+// 4000 x 512 -> 1536, 8000 x 2048 -> 2048, 20011 x 768 -> 2304, 30000 x 1024 -> 1024,
+// 100000 x 256 -> 768.  The smaller shapes take as many ranges as the largest has, or fewer: the
+// workspace holds that many partial tiles (plan.most), and their chains of additions are broken up.
 WgradPlan choose_wgrad(int64_t n_rows, int32_t channels, int32_t features) {
   WgradPlan best{};
   const int steps = (int)((n_rows + kTM - 1) / kTM);
@@ -366,18 +395,12 @@ WgradPlan choose_wgrad(int64_t n_rows, int32_t channels, int32_t features) {
     best_time = t;
     best = WgradPlan{tile, steps, per, splits, best.most};
   };
-  const long long tiles = (long long)((features + WgradLarge::kTF - 1) / WgradLarge::kTF) *
-                          ((channels + WgradLarge::kTC - 1) / WgradLarge::kTC);
-  const int by_tiles = (int)(2048 / tiles < 64 ? (2047 + tiles) / tiles : 64);
-  const int by_rows = (int)((n_rows / kTM + 15) / 16);
-  const int fewest = by_tiles < by_rows ? by_tiles : by_rows;
-  const int last = fewest < by_rows ? (fewest + 7 < 64 ? fewest + 7 : 64) : fewest;
-  for (int want = fewest; want <= last && want <= by_rows; ++want)
-    if (want > 0)
-      consider(WgradTile::kLarge, want, [&](int splits, int per) {
-        return wgrad_time<WgradLarge>(splits, per, channels, features, 8.0, {0.0, 1.6, 0.0, 0.0});
-      });
-  best.most = best.splits > 1 ? best.splits : 1;
+  const int ranges = large_ranges((int)(n_rows / kTM), channels, features);
+  best.most = ranges > 1 ? ranges : 1;
+  if (ranges > 0)
+    consider(WgradTile::kLarge, ranges, [&](int splits, int per) {
+      return wgrad_time<WgradLarge>(splits, per, channels, features, 8.0, {0.0, 1.6, 0.0, 0.0});
+    });
   for (int want = 1; want <= best.most && want <= steps; ++want) {
     consider(WgradTile::kMedium, want, [&](int splits, int per) {
       return wgrad_time<WgradMedium>(splits, per, channels, features, 5.0, {0.0, 0.72, 1.0, 0.0});
@@ -424,6 +447,17 @@ extern "C" size_t aeris_linear_bwd_workspace_bytes(int64_t n_rows, int32_t chann
   const bool none = n_rows < kTM || (most == 1 && n_rows % kTM == 0);
   return round256((size_t)out_features * channels * 2) +
          (none ? 0 : round256((size_t)most * out_features * channels * 4));
+}
+
+extern "C" int aeris_linear_bwd_plan(int64_t n_rows, int32_t channels, int32_t out_features,
+                                     int32_t* tile, int32_t* ranges, int32_t* steps) {
+  if (!tile || !ranges || !steps) return AERIS_ERR_NULL_POINTER;
+  if (const int rc = check_linear_bwd(n_rows, channels, out_features)) return rc;
+  const WgradPlan plan = choose_wgrad(n_rows, channels, out_features);
+  *tile = plan.tile == WgradTile::kLarge ? 256 : plan.tile == WgradTile::kMedium ? 128 : 64;
+  *ranges = plan.splits;
+  *steps = plan.steps_per_split;
+  return AERIS_OK;
 }
 
 extern "C" int aeris_linear_bwd(const void* x, const void* weight, const void* dy, int64_t n_rows,

@@ -2,6 +2,7 @@
 header declares, and rejects bad arguments before launching anything."""
 import ctypes
 import os
+import random
 import re
 
 import pytest
@@ -260,6 +261,44 @@ def test_projections_reject_bad_arguments_before_launching():
     lin = lambda **kw: lib.aeris_linear_fwd(kw.get("x", a), a, kw.get("n", 512), kw.get("c", 128),
                                             kw.get("f", 384), kw.get("y", a), None)
     assert lin(x=None) == -1 and lin(c=100) == -3 and lin(f=4) == -2 and lin(y=odd) == -7
+
+
+def known_row_ranges(n_rows, channels, features):
+    """Row ranges of 256 x 256 tiles that callers' workspaces are sized for: about 2048 workgroups, at
+    least 16 whole steps of 64 rows each, at most 64 ranges; among the next few counts the first whose
+    units of 32 tiles divide best by eight."""
+    steps, up = n_rows // 64, lambda a, b: -(-a // b)
+    ft, ct = up(features, 256), up(channels, 256)
+    side = 8 if ct >= 8 else 4 if ct >= 4 else 2 if ct >= 2 else 1
+    units = up(ft, 32 // side) * up(ct, side)
+    want = min(64, up(2048, ft * ct))
+    best, best_fill = 0, -1.0
+    for target in range(want, min(want + 8, 65)):
+        ranges = up(steps, max(16, up(steps, target)))
+        if ranges and ranges * units / (8 * up(ranges * units, 8)) > best_fill + 1e-9:
+            best, best_fill = ranges, ranges * units / (8 * up(ranges * units, 8))
+    return best
+
+
+def test_linear_bwd_needs_the_workspace_callers_have_known_and_no_longer_chains():
+    lib = B.load()
+    rng = random.Random(5)
+    tiles = set()
+    sizes = [(172800, 5504, 2048), (23434, 2112, 10560), (352366, 896, 2240), (63, 64, 64), (64, 64, 64),
+             (1088, 64, 64), (1089, 4096, 4096)]
+    for _ in range(4000):
+        c, f = 64 * int(2 ** rng.uniform(0, 7)), 64 * int(2 ** rng.uniform(0, 8))
+        sizes.append((int(2 ** rng.uniform(0, 22)), c, f))
+    for n, c, f in sizes:
+        known = known_row_ranges(n, c, f)
+        partials = 0 if known == 1 and n % 64 == 0 else known
+        assert lib.aeris_linear_bwd_workspace_bytes(n, c, f) == 2 * c * f + 4 * partials * c * f, (n, c, f)
+        tile, ranges, steps = B.aeris_linear_bwd_plan(n, c, f)
+        tiles.add(tile)
+        assert 1 <= ranges <= max(known, 1) and (ranges - 1) * steps < -(-n // 64) <= ranges * steps, (n, c, f)
+        if tile == 256:      # sums of one level: no range longer than the known ones, but for a step that
+            assert steps <= -(-(n // 64) // known) + 1, (n, c, f)     # is not whole
+    assert tiles == {64, 128, 256}
 
 
 def test_linear_bwd_rejects_bad_arguments_before_launching():
