@@ -60,36 +60,39 @@ using GemmSmall = GemmShape<2, 1, 1, 4>;   // 64 x 64, two workgroups per CU, th
 // serves 4 or 8 workgroups.  Which token tiles an XCD owns: see interleave_tiles.
 __device__ __forceinline__ bool gemm_tile(const GemmParams& p, int& mt, int& nt) {
   const int per_group = 8 * p.n_tiles;
+  int slot, m_tiles;
   if (p.interleave) {          // every eighth
-    const int slot = blockIdx.x >> 3;
-    const int group = slot / per_group, rem = slot - group * per_group;
-    nt = rem >> 3;
-    mt = ((group * 8 + (rem & 7)) << 3) + (blockIdx.x & 7);
-    return mt < p.m_tiles;
+    slot = blockIdx.x >> 3;
+    m_tiles = (p.m_tiles + 7 - (int)(blockIdx.x & 7)) >> 3;
+    if (slot >= m_tiles * p.n_tiles) return false;
+  } else {
+    slot = xcd_contiguous(p.m_tiles * p.n_tiles);
+    m_tiles = p.m_tiles;
   }
-  const int id = xcd_contiguous(p.m_tiles * p.n_tiles);
-  const int group = id / per_group, rem = id - group * per_group;
-  const int left = p.m_tiles - group * 8, gm = left < 8 ? left : 8;
+  const int group = slot / per_group, rem = slot - group * per_group;
+  const int left = m_tiles - group * 8, gm = left < 8 ? left : 8;
   nt = rem / gm;
   mt = group * 8 + (rem - nt * gm);
+  if (p.interleave) mt = mt * 8 + (blockIdx.x & 7);
   return true;
 }
 
-// Whether the XCDs take the token tiles in turn (the grid is then padded to 64 token tiles), or
-// each a contiguous range of them (no padding).  Padding hurts small grids out of proportion:
-// workgroups are dealt to the shader engines of an XCD in turn, idle ones included, and 237 tiles
-// (20011 x 2304 -> 768) left 9 workgroups on engines of 8 CUs while others had 6: 104 us with a
-// second round, 63 without padding.  Where it is no issue, contiguous ranges are faster for
-// medium contractions (172800 x 2048 -> 6144: 3481 us against 3661; -> 2 x 5504 gated: 6869
-// against 7336) and slower for long and short ones (6144 -> 2048: 3691 against 3577,
-// 32400 x 1024 -> 2 x 2752 gated: 401 against 392).
-bool interleave_tiles(long long m_tiles, int K) {
-  const long long padding = (m_tiles + 63) / 64 * 64 - m_tiles;
-  return padding * 16 <= m_tiles && (K < 1536 || K > 4096);
+// Whether the XCDs take the token tiles in turn, or each a contiguous range of the list of all tiles.
+// In turn is the faster one (time over that of ranges 0.92-1.03, mean 0.98, over 2000 ... 172800 rows,
+// 192 ... 8192 channels, 192 ... 6144 features; never above 1.02 of that of groups padded to eight
+// token tiles, whose idle workgroups unbalance the shader engines: 20011 x 2304 -> 768 104 us padded,
+// 63 without), but for two cases: where an XCD's whole token tiles make one round of workgroups more
+// than a range would (18000 x 192 -> 4608 1.09, 86400 x 8192 -> 768 1.14), and with weights of 8192
+// rows or more and up to 4096 channels (86400 x 512 -> 11008 1.13, 172800 x 1536 -> 8192 1.05,
+// 172800 x 2048 -> 8192 1.03; 86400 x 5504 -> 8192 0.93).
+bool interleave_tiles(long long m_tiles, long long n_tiles, int K, int F) {
+  if (F >= 8192 && K <= 4096) return false;
+  auto rounds = [](long long tiles_of_an_xcd) { return (tiles_of_an_xcd + 31) / 32; };
+  return rounds((m_tiles + 7) / 8 * n_tiles) == rounds((m_tiles * n_tiles + 7) / 8);
 }
 inline unsigned gemm_grid(const GemmParams& p) {
   const unsigned m = (unsigned)p.m_tiles;
-  return (p.interleave ? (m + 63) / 64 * 64 : m) * (unsigned)p.n_tiles;
+  return (p.interleave ? (m + 7) / 8 * 8 : m) * (unsigned)p.n_tiles;
 }
 
 __device__ __forceinline__ float silu(float u) {
@@ -432,7 +435,7 @@ bool gemm_tiles(GemmParams& p) {
   if ((m_tiles + 63) / 64 * 64 * p.n_tiles >= (1LL << 31)) return false;
   p.m_tiles_per_sample = (int)per_sample;
   p.m_tiles = (int)m_tiles;
-  p.interleave = Sh::NB == 4 && interleave_tiles(m_tiles, p.K);
+  p.interleave = Sh::NB == 4 && interleave_tiles(m_tiles, p.n_tiles, p.K, p.F);
   return true;
 }
 
