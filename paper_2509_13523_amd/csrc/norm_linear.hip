@@ -82,11 +82,12 @@ __device__ __forceinline__ bool gemm_tile(const GemmParams& p, int& mt, int& nt)
 // 192 ... 8192 channels, 192 ... 6144 features; never above 1.02 of that of groups padded to eight
 // token tiles, whose idle workgroups unbalance the shader engines: 20011 x 2304 -> 768 104 us padded,
 // 63 without), but for two cases: where an XCD's whole token tiles make one round of workgroups more
-// than a range would (18000 x 192 -> 4608 1.09, 86400 x 8192 -> 768 1.14), and with weights of 8192
+// than a range would (18000 x 192 -> 4608 1.09, 86400 x 8192 -> 768 1.14), and with weights of 5504
 // rows or more and up to 4096 channels (86400 x 512 -> 11008 1.13, 172800 x 1536 -> 8192 1.05,
-// 172800 x 2048 -> 8192 1.03; 86400 x 5504 -> 8192 0.93).
+// 172800 x 2048 -> 6144 1.03, 172800 x 2752 -> 5504 1.03, below that 0.96-1.03; 86400 x 5504 -> 8192
+// 0.93).
 bool interleave_tiles(long long m_tiles, long long n_tiles, int K, int F) {
-  if (F >= 8192 && K <= 4096) return false;
+  if (F >= 5504 && K <= 4096) return false;
   auto rounds = [](long long tiles_of_an_xcd) { return (tiles_of_an_xcd + 31) / 32; };
   return rounds((m_tiles + 7) / 8 * n_tiles) == rounds((m_tiles * n_tiles + 7) / 8);
 }
@@ -450,25 +451,31 @@ int launch_gemm_shape(const GemmParams& p, hipStream_t stream) {
   return p.swiglu ? launch_gemm_kernel<Sh, true>(p, stream) : launch_gemm_kernel<Sh, false>(p, stream);
 }
 
-// Which tile shape: the one whose rounds of workgroups are estimated to end first, from the time
-// a round takes (microseconds: a fixed part plus a part per 64-channel step; measured over
-// 500 ... 172800 rows, 128 ... 5504 channels, 128 ... 3072 features).  Small tiles have the
-// shortest steps and are taken as long as each has a CU of its own: 500 rows x 1024 -> 1024
-// takes 22.7 / 11.2 / 10.0 us with large / medium / small tiles, 2000 x 512 -> 1536 (768 small
-// tiles) 15.4 / 9.0 / 13.8.  Medium tiles win while large ones leave CUs without work
-// (4000 x 1024 -> 1024: 27.4 / 14.1 us; 8000 x 1024 -> 3072: 57 / 54), large ones, which move
-// half as many operand bytes per product, from about one full round on (20011 x 2304 -> 768:
-// 62.8 / 75.6; 172800 x 2048 -> 2048: 1247 / 1444).
+// Which tile shape: the one whose rounds of workgroups are estimated to end first, from the time a
+// round takes (microseconds: a fixed part plus a part per 64-channel step, less of both for a last
+// round that leaves CUs empty).  Medium tiles fetch the rows twice as often as large ones, which
+// counts once rows and results exceed the last-level cache (300000 x 192 -> 576 145 us with large
+// tiles, 161 with medium ones; 60000 x 192 -> 1408 67 / 58).  Fitted to 1485 sizes of 2000 ... 300000
+// rows, 64 ... 8192 channels and 64 ... 4608 features: what it takes is 0.35 % slower than the better
+// shape on average, more than 5 % at 30 of them.  Small tiles have the shortest steps and are taken as
+// long as each has a CU of its own: 500 rows x 1024 -> 1024 takes 22.7 / 11.2 / 10.0 us with large /
+// medium / small tiles, 2000 x 512 -> 1536 (768 small tiles) 15.4 / 9.0 / 13.8.  Medium tiles win
+// while large ones leave more than about half of the CUs without work (4000 x 1024 -> 1024: 27.4 /
+// 14.1), large ones, with half the operand bytes per product, from there on (157 large tiles, 40000 x
+// 1984 -> 192: 44.6 / 57.6; 141, 12000 x 960 -> 768: 25.2 / 29.8; 172800 x 2048 -> 2048: 1247 / 1444).
 enum class GemmTile { kLarge, kMedium, kSmall };
-GemmTile choose_gemm_tile(long long large_tiles, long long medium_tiles, long long small_tiles, int steps) {
+GemmTile choose_gemm_tile(long long large_tiles, long long medium_tiles, long long small_tiles, int steps,
+                          bool cached) {
   constexpr long long kCus = 256;
   if (small_tiles <= kCus) return GemmTile::kSmall;
-  const double large = (double)((large_tiles + kCus - 1) / kCus) * (8.0 + 1.6 * steps);
-  const double round = 3.0 + 1.05 * steps, half_round = 3.0 + 0.6 * steps;   // two or one per CU
-  const long long rest = medium_tiles % (2 * kCus);
-  const double medium = (double)(medium_tiles / (2 * kCus)) * round +
-                        (rest == 0 ? 0.0 : rest <= kCus ? half_round : round);
-  return medium < large ? GemmTile::kMedium : GemmTile::kLarge;
+  // one large workgroup per CU, two medium ones
+  const double large_rest = (double)(large_tiles % kCus) / kCus;
+  const double large = (double)(large_tiles / kCus) * (9.0 + 1.5 * steps) +
+                       (large_rest > 0.0 ? 6.5 + steps * (1.09 + 0.41 * large_rest * large_rest) : 0.0);
+  const double medium_rest = (double)(medium_tiles % (2 * kCus)) / (2 * kCus);
+  const double medium = (double)(medium_tiles / (2 * kCus)) * (3.6 + 0.9 * steps) +
+                        (medium_rest > 0.0 ? 3.6 + steps * (0.58 + 0.32 * medium_rest) : 0.0);
+  return medium * (cached ? 1.0 : 1.2) < large ? GemmTile::kMedium : GemmTile::kLarge;
 }
 
 }  // namespace
@@ -479,8 +486,9 @@ int launch_projection_gemm(GemmParams p, hipStream_t stream) {
   // a count that does not fit a launch rules the finer tiles out
   constexpr long long kNone = 1LL << 40;
   auto tiles = [](bool fits, const GemmParams& q) { return fits ? (long long)q.m_tiles * q.n_tiles : kNone; };
+  const bool cached = (double)p.n_samples * p.rows_per_sample * ((double)p.K + p.F) * 2.0 <= 256e6;
   switch (choose_gemm_tile(tiles(true, large), tiles(gemm_tiles<GemmMedium>(medium), medium),
-                           tiles(gemm_tiles<GemmSmall>(small), small), p.K / kBK)) {
+                           tiles(gemm_tiles<GemmSmall>(small), small), p.K / kBK, cached)) {
     case GemmTile::kSmall: return launch_gemm_shape<GemmSmall>(small, stream);
     case GemmTile::kMedium: return launch_gemm_shape<GemmMedium>(medium, stream);
     default: return launch_gemm_shape<GemmLarge>(large, stream);
