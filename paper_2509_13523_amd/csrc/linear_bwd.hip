@@ -294,13 +294,17 @@ __global__ __launch_bounds__(S::kWaves * 64, S::kWaves * S::kPerCu / 4) void lin
 }
 
 // dW = sum of the partial tiles, in the order of the splits.  n4: number of 4-float groups of dW.
+// kInFlight loads of a thread at a time: eight where few threads have to cover the latency (65536 x 4
+// bytes, 48 ranges: 30 us with one, 23 with eight); one where a full grid does and more streams only
+// spread over more pages (2048 x 2048, 32 ranges: 123 us with eight, 101 with one).
+template <int kInFlight>
 __global__ __launch_bounds__(256) void wgrad_reduce_kernel(const float* __restrict__ part,
                                                            long long n4, int splits,
                                                            float* __restrict__ dw) {
   const long long stride = (long long)gridDim.x * 256;
   for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < n4; i += stride) {
     f32x4 s = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll 8
+#pragma unroll kInFlight
     for (int k = 0; k < splits; ++k) {
       const f32x4 v = reinterpret_cast<const f32x4*>(part)[(long long)k * n4 + i];
       s[0] += v[0]; s[1] += v[1]; s[2] += v[2]; s[3] += v[3];
@@ -526,9 +530,9 @@ extern "C" int aeris_linear_bwd(const void* x, const void* weight, const void* d
     if (!direct) {
       const long long n4 = (long long)out_features * channels / 4;
       const long long blocks = (n4 + 255) / 256;
-      if (launch_kernel(wgrad_reduce_kernel, dim3((unsigned)(blocks < 4096 ? blocks : 4096)),
-                        dim3(256), 0, st, static_cast<const float*>(part), n4, plan.splits,
-                        dweight) != 0)
+      if (launch_kernel(blocks < 4096 ? wgrad_reduce_kernel<8> : wgrad_reduce_kernel<1>,
+                        dim3((unsigned)(blocks < 4096 ? blocks : 4096)), dim3(256), 0, st,
+                        static_cast<const float*>(part), n4, plan.splits, dweight) != 0)
         return AERIS_ERR_HIP_LAUNCH;
     }
   }
