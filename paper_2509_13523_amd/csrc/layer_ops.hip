@@ -328,6 +328,63 @@ __global__ __launch_bounds__(1024) void column_sums_finish_kernel(
   }
 }
 
+// The same for many samples of few partial rows each (up to kFewRows): there the samples go side by
+// side.  Thread group g of 64 adds all rows of samples g, g + 64, ..., in order, and keeps the samples'
+// shares of dw in the order of the samples; the groups' shares are added by a butterfly, then by wave.
+// A workgroup that takes the samples one after the other pays a barrier and a butterfly for each
+// (RMSNorm / gate backward as a whole, us: 256 samples of 4 partial rows, 1024 channels 348 / 274, so
+// 28 / 18; 4096 of one row, 256 channels 5443 / 3917, so 120 / 43; 8 of 16 rows 18 / 13, so 10 / 9).
+constexpr int kFewRows = 16;
+
+template <int A>
+__global__ __launch_bounds__(256) void column_sums_finish_samples_kernel(
+    const float* __restrict__ partial, int n_samples, int cps, int C, const float* __restrict__ w,
+    const float* __restrict__ gamma, float* __restrict__ out0, float* __restrict__ out1,
+    float* __restrict__ out_w) {
+  __shared__ __align__(16) float red[4][kFinishCols];          // [wave][column]
+  const int quad = threadIdx.x & 3, group = threadIdx.x >> 2;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int c = blockIdx.x * kFinishCols + quad * 4;           // C is a multiple of 8: four valid or none
+  f32x4 dw = {0.f, 0.f, 0.f, 0.f};
+  if (c < C) {
+    f32x4 wv = {0.f, 0.f, 0.f, 0.f};
+    if (A == 2) wv = *reinterpret_cast<const f32x4*>(w + c);
+    for (int b = group; b < n_samples; b += 64) {
+      const float* base = partial + (int64_t)b * cps * A * C + c;
+      f32x4 a[A];
+#pragma unroll
+      for (int i = 0; i < A; ++i) a[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+      for (int k = 0; k < cps; ++k)
+#pragma unroll
+        for (int i = 0; i < A; ++i) a[i] += *reinterpret_cast<const f32x4*>(base + (int64_t)(k * A + i) * C);
+      const int64_t at = (int64_t)b * C + c;
+      if (A == 2) {
+        const f32x4 g = *reinterpret_cast<const f32x4*>(gamma + at);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          if (out1 != nullptr) out1[at + e] = a[A - 1][e];                    // dbeta
+          if (out0 != nullptr) out0[at + e] = wv[e] * a[0][e];                // dgamma
+          dw[e] = __builtin_fmaf(1.f + g[e], a[0][e], dw[e]);
+        }
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) out0[at + e] = a[0][e];                   // dalpha
+      }
+    }
+  }
+  if (A == 1 || out_w == nullptr) return;
+#pragma unroll
+  for (int m = 4; m < 64; m <<= 1)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) dw[e] += __shfl_xor(dw[e], m, 64);
+  if (lane < 4) *reinterpret_cast<f32x4*>(&red[wave][quad * 4]) = dw;
+  __syncthreads();
+  const int cf = blockIdx.x * kFinishCols + threadIdx.x;
+  if (threadIdx.x < kFinishCols && cf < C)
+    out_w[cf] = ((red[0][threadIdx.x] + red[1][threadIdx.x]) + red[2][threadIdx.x]) + red[3][threadIdx.x];
+}
+
 // ---------------------------------------------------------------------------------------
 // Gated residual.  The sample's alpha stays in registers.
 // ---------------------------------------------------------------------------------------
@@ -500,6 +557,8 @@ int vectors_per_lane(int channels) {
 dim3 finish_grid(int channels) { return dim3((channels + kFinishCols - 1) / kFinishCols); }
 // 256 rows in flight per group of columns where a sample has that many partial rows, else 64
 dim3 finish_block(int cps) { return dim3(cps > 64 ? 1024 : 256); }
+// Samples side by side from the third on: one or two samples of a few rows are one pass either way.
+bool finish_by_samples(int n_samples, int cps) { return n_samples > 2 && cps <= kFewRows; }
 
 int status(int launch_rc) { return launch_rc == 0 ? AERIS_OK : AERIS_ERR_HIP_LAUNCH; }
 
@@ -591,6 +650,9 @@ extern "C" int aeris_rmsnorm_adaln_bwd_residual(const void* x, const float* w, c
   });
   if (rc != 0) return AERIS_ERR_HIP_LAUNCH;
   if (dw || dgamma || dbeta) {
+    if (finish_by_samples(n_samples, cps))
+      return status(launch_kernel(column_sums_finish_samples_kernel<2>, finish_grid(channels), dim3(256),
+                                  0, st, partial, n_samples, cps, channels, w, gamma, dgamma, dbeta, dw));
     return status(launch_kernel(column_sums_finish_kernel, finish_grid(channels), finish_block(cps), 0,
                                 st, partial, n_samples, cps, channels, 0, w, gamma, dgamma, dbeta,
                                 dw));
@@ -650,6 +712,10 @@ extern "C" int aeris_gate_residual_bwd(const void* y, const float* alpha, const 
   });
   if (rc != 0) return AERIS_ERR_HIP_LAUNCH;
   if (dalpha) {
+    if (finish_by_samples(n_samples, cps))
+      return status(launch_kernel(column_sums_finish_samples_kernel<1>, finish_grid(channels), dim3(256),
+                                  0, st, partial, n_samples, cps, channels, nullptr, nullptr, dalpha,
+                                  nullptr, nullptr));
     return status(launch_kernel(column_sums_finish_kernel, finish_grid(channels), finish_block(cps), 0,
                                 st, partial, n_samples, cps, channels, 1, nullptr, nullptr, dalpha,
                                 nullptr, nullptr));

@@ -205,6 +205,11 @@ def test_gate_residual_forward_and_backward(nb, rps, C):
     (1, 260, 24),       # 65 partial rows: 256 row groups, most of them empty
     (3, 2733, 8),       # 683 partial rows per sample: a ragged third turn, half a column group
     (1, 9000, 72),      # the largest number of partial rows
+    (2, 64, 24),        # 16 partial rows each of two samples: one after the other
+    (3, 64, 24),        # of three: side by side
+    (3, 66, 24),        # 17 rows: one after the other
+    (65, 7, 40),        # two rows each, a second turn of one sample
+    (131, 30, 24),      # eight rows each, a ragged third turn
 ])
 def test_sums_over_tokens_at_the_edges_of_the_second_stage(nb, rps, C):
     test_rmsnorm_adaln_forward_and_backward(nb, rps, C)
