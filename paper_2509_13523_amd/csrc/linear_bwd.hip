@@ -320,7 +320,8 @@ __global__ __launch_bounds__(256) void wgrad_reduce_kernel(const float* __restri
 __global__ __launch_bounds__(256) void transpose_weight_kernel(const bf16_t* __restrict__ w, int F,
                                                                int C, bf16_t* __restrict__ wt) {
   constexpr int kPitch = 66;
-  __shared__ unsigned short tile[64 * kPitch];                 // [channel][feature]
+  typedef uint32_t __attribute__((may_alias)) pair_t;          // two features, read as one word
+  __shared__ __align__(4) unsigned short tile[64 * kPitch];    // [channel][feature]
   const int f0 = blockIdx.y * 64, c0 = blockIdx.x * 64;
   const int row = threadIdx.x >> 3, chunk = threadIdx.x & 7;   // rows row, row + 32
   u32x4 v[2];
@@ -335,7 +336,7 @@ __global__ __launch_bounds__(256) void transpose_weight_kernel(const bf16_t* __r
   __syncthreads();
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
-    const uint32_t* src = reinterpret_cast<const uint32_t*>(tile + (row + 32 * i) * kPitch + 8 * chunk);
+    const pair_t* src = reinterpret_cast<const pair_t*>(tile + (row + 32 * i) * kPitch + 8 * chunk);
     *reinterpret_cast<u32x4*>(wt + (long long)(c0 + row + 32 * i) * F + f0 + 8 * chunk) =
         u32x4{src[0], src[1], src[2], src[3]};
   }
