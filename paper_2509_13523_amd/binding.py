@@ -179,9 +179,13 @@ def aeris_winattn_bwd_workspace_bytes(params):
 
 def _stream():
     """Handle of the current stream of the current device, without a Stream object around it (which
-    costs about as much host time as the rest of a call's argument handling)."""
+    costs about as much host time as the rest of a call's argument handling) where this torch has the
+    accessor that its own generated code uses; it is not part of torch's documented interface."""
     import torch
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is None:
+        return torch.cuda.current_stream().cuda_stream
+    return raw(torch.cuda.current_device())
 
 
 def _torch_out_dtype(out_dtype):

@@ -327,3 +327,13 @@ def test_linear_bwd_rejects_bad_arguments_before_launching():
     assert call(n=0) == -2 and call(c=0) == -2
     assert call(dx=odd) == -7 and call(dy=odd) == -7
     assert call(ws=need - 1) == -8
+
+
+def test_stream_handle_with_and_without_the_raw_accessor(monkeypatch):
+    torch = pytest.importorskip("torch")
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: type("S", (), {"cuda_stream": 11}))
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 100 + device, raising=False)
+    assert B._stream() == 103
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream")
+    assert B._stream() == 11
