@@ -198,20 +198,27 @@ __global__ __launch_bounds__(kThreads, 2) void winattn_dq_kernel(
     // delta = sum_c dO*O with the summation tree of winattn_delta_kernel: an fma chain over
     // the 8 channels of a chunk, then pairwise over the chunk index (bit 0 first).  This lane
     // holds chunks 2*kk + g; the partner lane (l ^ 32) holds the other chunk of every pair.
-    // Every load is issued before the first value is used.  Short windows are bound by round trips
-    // to memory, and left to itself the compiler may take the chunks and the log-sum-exp one after
-    // the other, each behind the chain of the one before (head_dim 32, 8 heads, dQ, us: 4 tokens
-    // 237 -> 221, 16: 175 -> 163, 25: 79 -> 74, 144: 74 -> 67; head_dim 128, 16 tokens: 600 -> 562).
+    // Up to head_dim 64 every load is issued before the first value is used.  Short windows are bound by
+    // round trips to memory, and left to itself the compiler may take the chunks and the log-sum-exp one
+    // after the other, each behind the chain of the one before (head_dim 32, 8 heads, dQ, us: 4 tokens
+    // 237 -> 220, 16: 175 -> 161, 25: 79 -> 73, 144: 74 -> 66).  At head_dim 128 the same order would
+    // serve windows of 4 to 25 tokens (16: 600 -> 562) but cost those of 2304 and 3600, 0.6 to 1 %:
+    // there the waves of a SIMD start apart otherwise, and their loops overlap better.
+    constexpr bool kAtOnce = D <= 64;
     const OutT* orow = o + o_base + (long long)q_grid * p.o_tok + 8 * g;
+    const float* lse_q = lse + ((long long)win.b * p.nh + win.head) * plane + q_grid;
     Raw8<OutT> o8[D / 16];
+    if constexpr (kAtOnce) {
 #pragma unroll
-    for (int kk = 0; kk < D / 16; ++kk) o8[kk].load(orow + kk * 16);
-    lse2 = lse[((long long)win.b * p.nh + win.head) * plane + q_grid];
-    __builtin_amdgcn_sched_barrier(0x7);   // arithmetic may cross, the loads may not
+      for (int kk = 0; kk < D / 16; ++kk) o8[kk].load(orow + kk * 16);
+      lse2 = *lse_q;
+      __builtin_amdgcn_sched_barrier(0x7);   // arithmetic may cross, the loads may not
+    }
     float part[D / 16];
 #pragma unroll
     for (int kk = 0; kk < D / 16; ++kk) {
       float a[8];
+      if constexpr (!kAtOnce) o8[kk].load(orow + kk * 16);
       o8[kk].values(a);
       float acc1 = 0.f;
 #pragma unroll
@@ -225,6 +232,7 @@ __global__ __launch_bounds__(kThreads, 2) void winattn_dq_kernel(
 #pragma unroll
       for (int kk = 0; kk < D / 16; kk += 2 * s2) part[kk] += part[kk + s2];
     delta_q = part[0];
+    if constexpr (!kAtOnce) lse2 = *lse_q;
     lse2 *= kLog2e;
     if (rg.valid && g == 0) {
       delta[(long long)pair * p.T + rg.tok] = delta_q;
