@@ -445,7 +445,8 @@ constexpr size_t dkdv_smem_bytes(int T) {
   return table_bytes(T) + 2 * (2 * Tile<D>::kBytes + 2 * kStream * 4) + kParkedBlocks<D> * 2 * kParkBytes;
 }
 
-template <int D, typename OutT>
+// kLean: the order of reads, see sub_block
+template <int D, typename OutT, bool kLean>
 __global__ __launch_bounds__(kThreads, 2) void winattn_dkdv_kernel(
     KParams p, const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
     const bf16_t* __restrict__ v, const bf16_t* __restrict__ d_o,
@@ -540,15 +541,10 @@ __global__ __launch_bounds__(kThreads, 2) void winattn_dkdv_kernel(
     constexpr uint32_t kStatOff = decltype(stat_off)::value;
     if (rg.skip(sub_lo)) return;
     la.begin_block();
-    // head_dim 64: every operand is read first, products after, so that LDS latency hides behind
-    // the MFMA pipeline (228 registers, two waves per SIMD).  The others read operands one block of
-    // products ahead and the statistics four rows at a time, in fenced order.  head_dim 32 has too
-    // few products per block for the former and is bound by latency: 118 registers instead of 160,
-    // four waves per SIMD instead of three (65,000 tokens, 8 heads, windows of 144 / 256 / 400 / 900
-    // tokens: 73 / 58 / 100 / 167 -> 67 / 53 / 93 / 162 us; the same order at head_dim 64, where it
-    // fits 168 registers: 160 / 119 / 195 / 303 -> 165 / 127 / 187 / 297, and 126 -> 159 at 64).
-    // head_dim 128 has no registers for the former.
-    constexpr bool kLean = D != 64;
+    // Not kLean: every operand is read first, products after, so that LDS latency hides behind the
+    // MFMA pipeline (head_dim 64: 228 registers, two waves per SIMD; 32: 160, three).  kLean: operands
+    // are read one block of products ahead and the statistics four rows at a time, in fenced order
+    // (head_dim 32: 118 registers, four waves per SIMD; head_dim 128 has no registers for the former).
     constexpr int kNK = D / 16;
     bf16x8 qa[kNK], doa[kNK], dota[kNK], qta[kNK];
     f32x4 l4[4], d4[4];
@@ -684,6 +680,16 @@ __global__ __launch_bounds__(kThreads, 2) void winattn_dkdv_kernel(
 // 1.04-1.06, 3600: 1.03-1.04, 4096: 1.04-1.06.  Same bits from both.
 constexpr size_t kLdsOfCu = 160 * 1024;
 
+// head_dim 32: grids of more than this many workgroups, the three per CU that the other order has
+// registers for, run the lean dK/dV kernel, and so do windows of a single streamed tile, which have
+// little to overlap.  Other / lean, 4 heads, us: 3600 tokens 116 workgroups 44.1 / 46.3, 464 95.3 /
+// 100.1, 928 153 / 148, 4060 511 / 499; 256 tokens 128 8.7 / 9.1, 720 15.0 / 14.8, 968 20.6 / 18.9, 4048
+// 62.8 / 56.0; 144 tokens 968 16.1 / 13.0; 16 tokens 728 6.0 / 5.6, 4096 19.2 / 16.1.  At head_dim 64 the
+// lean order would fit 168 registers, three waves per SIMD instead of two, but loses below 400 tokens
+// (65,000 tokens, 8 heads, windows of 64 / 144 / 256 / 400 / 529 / 900 / 3600 tokens: 126 / 160 / 119 /
+// 195 / 221 / 294 / 796 -> 159 / 165 / 127 / 187 / 205 / 270 / 750) and is not built for it.
+constexpr int kLeanAboveBlocks = 768;
+
 template <int D, typename OutT>
 static int launch_bwd_t(KParams kp, const void* q, const void* k, const void* v,
                         const void* o, const float* lse, const void* d_o, void* dq, void* dk,
@@ -724,11 +730,19 @@ static int launch_bwd_t(KParams kp, const void* q, const void* k, const void* v,
                                    dk, dv, stream);
     }
     const size_t smem = dkdv_smem_bytes<D>(kp.T);
-    auto kern = winattn_dkdv_kernel<D, OutT>;
-    if (!allow_full_lds<winattn_dkdv_kernel<D, OutT>>()) return -1;
-    return launch_kernel(kern, dim3(n_blocks), dim3(kThreads), smem, stream, kp, qp, kp_, vp, dop,
-                         static_cast<const float*>(delta), static_cast<const float*>(lse2),
-                         static_cast<OutT*>(dk), static_cast<OutT*>(dv));
+    auto launch = [&](auto lean) {
+      constexpr bool kLean = decltype(lean)::value != 0;
+      if (!allow_full_lds<winattn_dkdv_kernel<D, OutT, kLean>>()) return -1;
+      return launch_kernel(winattn_dkdv_kernel<D, OutT, kLean>, dim3(n_blocks), dim3(kThreads), smem,
+                           stream, kp, qp, kp_, vp, dop, static_cast<const float*>(delta),
+                           static_cast<const float*>(lse2), static_cast<OutT*>(dk),
+                           static_cast<OutT*>(dv));
+    };
+    if constexpr (D == 32) {
+      return n_blocks > kLeanAboveBlocks || kp.T <= kStream ? launch(Const<1>{}) : launch(Const<0>{});
+    } else {
+      return launch(Const<(D == 128)>{});
+    }
   }
   return 0;
 }

@@ -234,6 +234,17 @@ def test_whole_windows_dealt_to_an_xcd(heads, d, win):
     run_case((1, win[0], win[1] * 9, heads, d), win, (win[0] // 2, win[1] // 2), B.AERIS_MASK_SWIN, seed=57)
 
 
+@pytest.mark.parametrize("shape,win", [
+    ((1, 16, 16, 3, 32), (8, 8)),           # one streamed tile
+    ((1, 26, 15, 3, 32), (13, 5)),          # 65 tokens, 18 workgroups
+    ((1, 104, 160, 3, 32), (13, 5)),        # 768 workgroups
+    ((1, 104, 170, 3, 32), (13, 5)),        # 816
+])
+def test_head_dim_32_dkdv_by_window_and_grid_size(shape, win):
+    """Both orders of reads of the dK/dV kernel, at the edges of their rule."""
+    run_case(shape, win, (win[0] // 2, win[1] // 2), B.AERIS_MASK_SWIN, seed=58)
+
+
 @pytest.mark.parametrize("win", [(2, 2), (12, 16), (13, 15), (28, 64), (33, 55)])
 def test_head_dim_128_dkdv_by_window_size(win):
     """Up to 1792 tokens the generic dK/dV kernel; 1815: the software-pipelined one."""
