@@ -24,6 +24,15 @@ int aeris_mfma_loop_probe(int32_t blocks, int32_t iters, int32_t random_operands
                           void* hip_stream);
 
 /*
+ * How the projections (aeris_linear_fwd; with several samples aeris_norm_linear_fwd, gated != 0
+ * aeris_norm_linear_swiglu_fwd, features = rows of the weight) are computed at a size they accept,
+ * else their error code: *tile, the sides of the workgroup tiles (256, 128 or 64); *in_turn, whether
+ * the XCDs take the token tiles in turn (1) or contiguous ranges of all tiles (0).
+ */
+int aeris_projection_plan(int64_t n_rows, int64_t rows_per_sample, int32_t channels, int32_t features,
+                          int32_t gated, int32_t* tile, int32_t* in_turn);
+
+/*
  * How aeris_linear_bwd computes dweight at a size it accepts (else its error code): *tile, the
  * sides of its square workgroup tiles (256, 128 or 64); *ranges, the row ranges whose partial
  * results are added; *steps, the steps of 64 rows in each but the last.  Launches nothing.

@@ -20,7 +20,8 @@ EXPORTS = ("aeris_winattn_fwd", "aeris_winattn_bwd", "aeris_winattn_bwd_stages",
            "aeris_winattn_bwd_workspace_bytes", "aeris_winattn_bwd_static",
            "aeris_winattn_validate", "aeris_winattn_strerror", "aeris_winattn_version",
            "aeris_winattn_fwd_windows", "aeris_winattn_bwd_windows",
-           "aeris_mfma_loop_probe", "aeris_linear_bwd_plan", "aeris_rope2d_apply", "aeris_winattn_rope_fwd_workspace_bytes",
+           "aeris_mfma_loop_probe", "aeris_projection_plan", "aeris_linear_bwd_plan",
+           "aeris_rope2d_apply", "aeris_winattn_rope_fwd_workspace_bytes",
            "aeris_winattn_rope_bwd_workspace_bytes", "aeris_winattn_rope_fwd",
            "aeris_winattn_rope_bwd", "aeris_winattn_rope_fwd_windows",
            "aeris_winattn_rope_bwd_windows",
@@ -95,6 +96,9 @@ def load():
     lib.aeris_mfma_loop_probe.argtypes = [ctypes.c_int32, ctypes.c_int32, ctypes.c_int32, vp, vp]
     lib.aeris_mfma_loop_probe.restype = ctypes.c_int
     pi32 = ctypes.POINTER(ctypes.c_int32)
+    lib.aeris_projection_plan.argtypes = [ctypes.c_int64, ctypes.c_int64, ctypes.c_int32, ctypes.c_int32,
+                                          ctypes.c_int32, pi32, pi32]
+    lib.aeris_projection_plan.restype = ctypes.c_int
     lib.aeris_linear_bwd_plan.argtypes = [ctypes.c_int64, ctypes.c_int32, ctypes.c_int32, pi32, pi32, pi32]
     lib.aeris_linear_bwd_plan.restype = ctypes.c_int
     R = ctypes.POINTER(aeris_rope_params)
@@ -435,6 +439,16 @@ def aeris_winattn_rope_bwd_windows(q, k, v, o, lse, d_o, win, shift, base, posit
     if rc != 0:
         raise AerisError(rc, "aeris_winattn_rope_bwd_windows")
     return dq, dk, dv
+
+
+def aeris_projection_plan(n_rows, rows_per_sample, channels, features, gated=False):
+    """(sides of a workgroup tile, whether the XCDs take token tiles in turn) of a projection."""
+    out = [ctypes.c_int32() for _ in range(2)]
+    rc = load().aeris_projection_plan(n_rows, rows_per_sample, channels, features, int(gated),
+                                      *[ctypes.byref(v) for v in out])
+    if rc != 0:
+        raise AerisError(rc, "aeris_projection_plan")
+    return out[0].value, bool(out[1].value)
 
 
 def aeris_linear_bwd_plan(n_rows, channels, out_features):

@@ -23,6 +23,7 @@
 #include <stdint.h>
 
 #include "aeris_layer_ops.h"
+#include "aeris_probe.h"
 #include "aeris_winattn.h"
 #include "projection_gemm.hpp"
 #include "winattn_common.hpp"
@@ -480,18 +481,31 @@ GemmTile choose_gemm_tile(long long large_tiles, long long medium_tiles, long lo
 
 }  // namespace
 
-int launch_projection_gemm(GemmParams p, hipStream_t stream) {
+namespace {
+
+// Fills in p's tile counts for the shape that is taken, false if no shape fits a launch.
+bool plan_gemm(GemmParams& p, GemmTile& tile) {
   GemmParams large = p, medium = p, small = p;
-  if (!gemm_tiles<GemmLarge>(large)) return -1;
+  if (!gemm_tiles<GemmLarge>(large)) return false;
   // a count that does not fit a launch rules the finer tiles out
   constexpr long long kNone = 1LL << 40;
   auto tiles = [](bool fits, const GemmParams& q) { return fits ? (long long)q.m_tiles * q.n_tiles : kNone; };
   const bool cached = (double)p.n_samples * p.rows_per_sample * ((double)p.K + p.F) * 2.0 <= 256e6;
-  switch (choose_gemm_tile(tiles(true, large), tiles(gemm_tiles<GemmMedium>(medium), medium),
-                           tiles(gemm_tiles<GemmSmall>(small), small), p.K / kBK, cached)) {
-    case GemmTile::kSmall: return launch_gemm_shape<GemmSmall>(small, stream);
-    case GemmTile::kMedium: return launch_gemm_shape<GemmMedium>(medium, stream);
-    default: return launch_gemm_shape<GemmLarge>(large, stream);
+  tile = choose_gemm_tile(tiles(true, large), tiles(gemm_tiles<GemmMedium>(medium), medium),
+                          tiles(gemm_tiles<GemmSmall>(small), small), p.K / kBK, cached);
+  p = tile == GemmTile::kLarge ? large : tile == GemmTile::kMedium ? medium : small;
+  return true;
+}
+
+}  // namespace
+
+int launch_projection_gemm(GemmParams p, hipStream_t stream) {
+  GemmTile tile;
+  if (!plan_gemm(p, tile)) return -1;
+  switch (tile) {
+    case GemmTile::kSmall: return launch_gemm_shape<GemmSmall>(p, stream);
+    case GemmTile::kMedium: return launch_gemm_shape<GemmMedium>(p, stream);
+    default: return launch_gemm_shape<GemmLarge>(p, stream);
   }
 }
 
@@ -602,4 +616,22 @@ extern "C" int aeris_linear_fwd(const void* x, const void* weight, int64_t n_row
   p.K = channels;
   p.F = out_features;
   return launch_projection_gemm(p, static_cast<hipStream_t>(hip_stream)) == 0 ? AERIS_OK : AERIS_ERR_HIP_LAUNCH;
+}
+
+extern "C" int aeris_projection_plan(int64_t n_rows, int64_t rows_per_sample, int32_t channels,
+                                     int32_t features, int32_t gated, int32_t* tile, int32_t* in_turn) {
+  if (!tile || !in_turn) return AERIS_ERR_NULL_POINTER;
+  if (const int rc = check_projection(n_rows, rows_per_sample, channels, features)) return rc;
+  if (gated && features % 16 != 0) return AERIS_ERR_NOT_DIVISIBLE;
+  GemmParams p{};
+  p.rows_per_sample = rows_per_sample;
+  p.n_samples = n_rows / rows_per_sample;
+  p.K = channels;
+  p.F = features;
+  p.swiglu = gated ? 1 : 0;
+  GemmTile t;
+  if (!plan_gemm(p, t)) return AERIS_ERR_INVALID_SHAPE;
+  *tile = t == GemmTile::kLarge ? 256 : t == GemmTile::kMedium ? 128 : 64;
+  *in_turn = p.interleave;
+  return AERIS_OK;
 }

@@ -63,25 +63,29 @@ def close_dw(got, ref, mag, n_rows, rel_l2=1e-4):
 
 
 CASES = [
-    # rows, channels, out features
-    (64, 64, 64),             # one step, one tile that is mostly padding
-    (1024, 192, 320),         # ragged channel tile, ragged second feature tile, one row range
-    (4096, 256, 512),         # two feature tiles, four row ranges added by the second kernel
-    (2112, 2048, 448),        # the headline width; 33 steps: the last row range holds one step
-    (8256, 128, 6144),        # 24 feature tiles (three per XCD), nine row ranges
-    (1000, 192, 320),         # 15 whole steps and 40 rows left over
-    (40, 64, 128),            # fewer rows than one step: everything is "left over"
-    (4159, 256, 512),         # four row ranges and 63 rows left over
-    (1024, 64, 11008),        # the SwiGLU width: 43 feature tiles (empty slots on five XCDs);
-                              # dx contracts over 11008 features
-    (2125, 64, 128),          # 64 x 64 tiles: two row ranges of 17 steps (one past a run of 16), 13 rows left over
-    (5003, 1600, 4160),       # 128 x 128 tiles, one row range of 79 steps (four runs and 15), ragged tiles
-    (1050, 4096, 4032),       # 256 x 256 tiles, ragged feature tile, 26 rows left over
+    # rows, channels, out features, plan of dweight (sides of a tile, row ranges, steps of 64 rows in each)
+    (64, 64, 64, (64, 1, 1)),                # one step
+    (1024, 192, 320, (64, 1, 16)),           # one run of 16 steps
+    (4096, 256, 512, (64, 4, 16)),           # four row ranges added by the second kernel
+    (2112, 2048, 448, (64, 1, 33)),          # the headline width; two runs and one step
+    (8256, 128, 6144, (64, 4, 33)),          # a whole piece per XCD
+    (1000, 192, 320, (64, 1, 16)),           # 40 rows left over in the last step
+    (40, 64, 128, (64, 1, 1)),               # fewer rows than one step
+    (4159, 256, 512, (64, 4, 17)),           # 63 rows left over
+    (1024, 64, 11008, (64, 1, 16)),          # the SwiGLU width; dx contracts over 11008 features
+    (2125, 64, 128, (64, 3, 12)),            # 13 rows left over, the last range shorter
+    (9001, 512, 512, (64, 8, 18)),           # ranges that cross a run, 41 rows left over
+    (1102, 1600, 5056, (64, 1, 18)),         # a whole piece per XCD and 439 tiles shared out
+    (5003, 1600, 4160, (128, 1, 79)),        # four runs and 15 steps, ragged tiles
+    (3971, 576, 6656, (128, 3, 21)),         # ranges that cross a run, three rows left over, pieces and a rest
+    (1050, 4096, 4032, (256, 1, 17)),        # ragged feature tile, 26 rows left over
+    (6637, 1216, 3264, (256, 7, 15)),        # seven ranges, 45 rows left over, pieces and a rest
 ]
 
 
-@pytest.mark.parametrize("n,channels,features", CASES)
-def test_linear_bwd(n, channels, features):
+@pytest.mark.parametrize("n,channels,features,plan", CASES)
+def test_linear_bwd(n, channels, features, plan):
+    assert B.aeris_linear_bwd_plan(n, channels, features) == plan
     rng = np.random.default_rng(500 + features + n)
     gain = np.exp(0.5 * rng.standard_normal(channels))
     xb, x = bf16_pair(rng.standard_normal((n, channels)) * gain)

@@ -147,15 +147,20 @@ def test_linear_fwd(n, channels, features):
     close("y", y, ref, 1e-5 * (np.abs(x) @ np.abs(weight).T))
 
 
-@pytest.mark.parametrize("n_samples,rows,channels,features", [
-    (1, 65, 64, 80),          # 64 x 64 tiles, one row and one 8-feature group past a tile: one step,
-    (1, 63, 128, 64),         # two steps (as many as prologue stages less one),
-    (1, 129, 192, 128),       # three,
-    (1, 64, 320, 208),        # five: the stages wrap around
-    (3, 695, 192, 1104),      # 128 x 128 tiles, ragged both ways, three samples
-    (1, 4070, 512, 4080),     # 256 x 256 tiles, ragged both ways, eight steps
+@pytest.mark.parametrize("n_samples,rows,channels,features,plan", [
+    (1, 65, 64, 80, (64, False)),       # one row and one 8-feature group past a tile: one step,
+    (1, 63, 128, 64, (64, False)),      # two steps (as many as prologue stages less one),
+    (1, 129, 192, 128, (64, False)),    # three,
+    (1, 64, 320, 208, (64, False)),     # five: the stages wrap around
+    (3, 695, 192, 1104, (128, False)),  # ragged both ways, three samples
+    (1, 4070, 512, 4080, (256, True)),  # ragged both ways, eight steps
+    (2, 10921, 64, 272, (256, True)),   # 86 token tiles, the XCDs have ten or eleven: a short last group
+    (3, 559, 64, 4384, (256, False)),   # 9 token tiles: in turn would take a round more
+    (2, 642, 64, 5552, (256, False)),   # a wide weight
 ])
-def test_projections_with_every_tile_shape(n_samples, rows, channels, features):
+def test_projections_with_every_tile_shape(n_samples, rows, channels, features, plan):
+    assert B.aeris_projection_plan(n_samples * rows, rows, channels, features) == plan
+    assert B.aeris_projection_plan(n_samples * rows, rows, channels, features, gated=True) == plan
     test_linear_fwd(n_samples * rows, channels, features)
     test_norm_linear_fwd(n_samples, rows, channels, features)
     test_norm_linear_swiglu_fwd(n_samples, rows, channels, features // 2)
