@@ -118,10 +118,10 @@ class PowerSampler:
         return out
 
 
-def kernel_symbol(stage, head_dim):
-    """Name of the kernel the library launches for a stage (its dispatch rule: the dK/dV stage
-    has a software-pipelined kernel of its own at head_dim 128)."""
-    if stage == "dkdv" and head_dim == 128:
+def kernel_symbol(stage, head_dim, window_tokens):
+    """Name of the kernel the library launches for a stage (its dispatch rule: the dK/dV stage has a
+    software-pipelined kernel of its own at head_dim 128 for windows of more than 1792 tokens)."""
+    if stage == "dkdv" and head_dim == 128 and window_tokens > 1792:
         return "winattn_dkdv_pipe_kernel"
     return "winattn_%s_kernel" % stage
 
@@ -325,8 +325,9 @@ def main():
     dom = max((k for k in kern if kernel_flops[k]), key=lambda k: kern[k]["avg_ms"] * len(events[k]))
     dom_flops = kernel_flops[dom] * d * sum(U.values()) / len(U)
     achieved = dom_flops / (kern[dom]["avg_ms"] * 1e-3) / 1e12
-    dom_name = (kernel_symbol("dq", d) + " + " + kernel_symbol("dkdv", d) if dom == "bwd"
-                else kernel_symbol(dom, d))
+    tokens = win[0] * win[1]
+    dom_name = (kernel_symbol("dq", d, tokens) + " + " + kernel_symbol("dkdv", d, tokens)
+                if dom == "bwd" else kernel_symbol(dom, d, tokens))
     roofline = {"kernel": dom_name, "bound": "mfma", "achieved": round(achieved, 2),
                 "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
                 "frac": round(achieved / PEAK_BF16_TFLOPS, 4)}
