@@ -366,7 +366,8 @@ double wgrad_time(int splits, int per, int32_t channels, int32_t features, doubl
 }
 
 // Row ranges of the largest tiles, 0 if there is no whole step: enough for about 2048 workgroups, at
-// least 16 steps each and at most 64; among the next few counts the one whose units of 32 tiles (the
+// most 64 and no more than pieces of 16 steps give (the plan then makes them equally long: 17 steps
+// are cut 9 + 8); among the next few counts the one whose units of 32 tiles (the
 // workgroups an XCD runs at a time) share out to the eight XCDs most evenly.  Fixed by size alone:
 // callers hold workspaces for this many partial tiles, and fewer ranges would be longer chains of
 // additions, which this shape does not break up (23434 x 2112 -> 10560 in 6 ranges of 62 steps instead
