@@ -521,7 +521,7 @@ def bench_projections(args):
                                "(SwiGLU up, gated)" % (nb, rps, C, F, hidden), "kernels": per,
                    "vendor_gemm_qkv_shape_ms": round(vendor_ms, 3),
                    "vendor_gemm_qkv_shape_tflops": round(2.0 * n * C * F / (vendor_ms * 1e-3) / 1e12, 1)},
-        "roofline": {"kernel": "norm_linear_gemm_kernel (%s)" % slow[0], "bound": "mfma",
+        "roofline": {"kernel": "projection_gemm_kernel (%s)" % slow[0], "bound": "mfma",
                      "achieved": achieved, "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
                      "frac": round(achieved / PEAK_BF16_TFLOPS, 4),
                      **profiled_traffic("qkv_proj", slow[0],
@@ -603,7 +603,7 @@ def bench_projection_bwd(args):
                                "(bf16) and dW = dy^T x (fp32)" % (n, C, F), "kernels": per,
                    "vendor_gemm_same_products": ven},
         "roofline": {"kernel": "%s (%s)" % ("linear_wgrad_kernel" if slow == "dweight"
-                                            else "norm_linear_gemm_kernel", slow), "bound": "mfma",
+                                            else "projection_gemm_kernel", slow), "bound": "mfma",
                      "achieved": achieved, "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
                      "frac": round(achieved / PEAK_BF16_TFLOPS, 4),
                      **profiled_traffic("qkv_proj_bwd", slow,

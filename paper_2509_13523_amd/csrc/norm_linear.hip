@@ -11,10 +11,10 @@
 // per-sample bias beta_b W^T.  The SwiGLU gate is a second epilogue: a workgroup's tile holds
 // matching u and v columns, so g = silu(u) v is formed on the accumulators.
 //
-// GEMM kernel: one workgroup of eight wavefronts per 256 x 256 output tile (four per 128 x 128 or
-// two per 64 x 64 where there are too few rows for that, see choose_gemm_tile), 64 channels per
+// GEMM kernels: 256 x 256 output tiles of eight wavefronts (128 x 128 of four or 64 x 64 of two where
+// there are too few rows for that, see choose_gemm_tile), 64 channels per
 // step, both operands K-contiguous ("NT").  Operand tiles go global -> LDS directly
-// (global_load_lds_dwordx4), two stages of 64 KB, 16-byte chunks XOR-swizzled so that the
+// (global_load_lds_dwordx4), two stages or more, 16-byte chunks XOR-swizzled so that the
 // row-major ds_read_b128 operand fetches are conflict free; v_mfma_f32_32x32x16_bf16 with the
 // weight rows as the A operand and the token rows as the B operand, so that a lane owns one
 // token row of the output: the row scale is a per-lane scalar.  Results are staged through the
@@ -33,6 +33,7 @@ namespace aeris {
 namespace {
 
 constexpr int kBK = 64;                  // channels per step
+constexpr unsigned kCus = 256;           // of the chip
 using Sub = Tile<64, 8>;                 // chunk swizzle of rows of 64 channels
 
 // A workgroup tile of WM x WN wavefronts, each NB * 32 token rows x 64 features, and kStages
@@ -45,9 +46,10 @@ struct GemmShape {
   static constexpr int kBN = WN * 64;                  // weight rows (output features)
   static constexpr int kPartBytes = kBN * kBK * 2;     // weight rows of a stage
   static constexpr int kStageBytes = kPartBytes + kBM * kBK * 2;
-  static constexpr int kPitch = 144;                   // epilogue rows: 128 bytes, on different banks
-  static constexpr int kEpilogueBytes = kWaves * NB * 32 * kPitch;
-  static constexpr int kSmem = kStages * kStageBytes > kEpilogueBytes ? kStages * kStageBytes : kEpilogueBytes;
+  static constexpr int kSmem = kStages * kStageBytes;
+  static constexpr int kStoreBlocks = NB < 2 ? NB : 2; // 32-row blocks a wave stages at a time
+  static constexpr int kStoreBytes = kStoreBlocks * 32 * 128;   // ... in a region of this size
+  static_assert(kWaves * kStoreBytes <= kStageBytes, "results are staged in one operand stage");
   // every wave issues four weight-row and four token-row copies of a stage
   static_assert(kBN == 32 * kWaves && kBM == 32 * kWaves && kWaves % 2 == 0);
 };
@@ -55,26 +57,28 @@ using GemmLarge = GemmShape<2, 4, 4, 2>;   // 256 x 256, one workgroup per CU
 using GemmMedium = GemmShape<2, 2, 2, 2>;  // 128 x 128, two workgroups per CU
 using GemmSmall = GemmShape<2, 1, 1, 4>;   // 64 x 64, two workgroups per CU, three stages in flight
 
-// Workgroup id -> (token tile, feature tile); false if the id has no tile.  Tiles are walked in
+// Work item -> (token tile, feature tile); false if the item has no tile, nor has any later one of the
+// same workgroup.  Items go to the XCDs in turn, as workgroup ids do.  Tiles are walked in
 // groups of eight token tiles, feature tile by feature tile, so that the 32 tiles an XCD runs at a
 // time are 8 token tiles x 4 feature tiles and every operand tile that arrives in that XCD's L2
 // serves 4 or 8 workgroups.  Which token tiles an XCD owns: see interleave_tiles.
-__device__ __forceinline__ bool gemm_tile(const GemmParams& p, int& mt, int& nt) {
+__device__ __forceinline__ bool gemm_tile(const GemmParams& p, int item, int& mt, int& nt) {
   const int per_group = 8 * p.n_tiles;
   int slot, m_tiles;
   if (p.interleave) {          // every eighth
-    slot = blockIdx.x >> 3;
-    m_tiles = (p.m_tiles + 7 - (int)(blockIdx.x & 7)) >> 3;
+    slot = item >> 3;
+    m_tiles = (p.m_tiles + 7 - (item & 7)) >> 3;
     if (slot >= m_tiles * p.n_tiles) return false;
   } else {
-    slot = xcd_contiguous(p.m_tiles * p.n_tiles);
+    if (item >= p.m_tiles * p.n_tiles) return false;
+    slot = xcd_contiguous(item, p.m_tiles * p.n_tiles);
     m_tiles = p.m_tiles;
   }
   const int group = slot / per_group, rem = slot - group * per_group;
   const int left = m_tiles - group * 8, gm = left < 8 ? left : 8;
   nt = rem / gm;
   mt = group * 8 + (rem - nt * gm);
-  if (p.interleave) mt = mt * 8 + (blockIdx.x & 7);
+  if (p.interleave) mt = mt * 8 + (item & 7);
   return true;
 }
 
@@ -101,43 +105,195 @@ __device__ __forceinline__ float silu(float u) {
   return u * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(-u * kLog2e));
 }
 
+// Where a workgroup's tile lies.
+struct GemmTileAt {
+  int sample, nt;
+  int valid_rows;        // rows of the tile that exist
+  long long row0;        // its first row
+};
+template <class Sh>
+__device__ __forceinline__ bool gemm_tile_at(const GemmParams& p, int item, GemmTileAt& t) {
+  int mt;
+  if (!gemm_tile(p, item, mt, t.nt)) return false;
+  t.sample = mt / p.m_tiles_per_sample;
+  const int tile_in_sample = mt - t.sample * p.m_tiles_per_sample;
+  t.row0 = (long long)t.sample * p.rows_per_sample + (long long)tile_in_sample * Sh::kBM;
+  const long long rows_left = p.rows_per_sample - (long long)tile_in_sample * Sh::kBM;
+  t.valid_rows = rows_left < Sh::kBM ? (int)rows_left : Sh::kBM;
+  return true;
+}
+
+// Feature (weight row) of tile row R.  SwiGLU tiles pair kBN / 2 u-features with their
+// v-features: wave column wn holds u rows in its first 32 tile rows, v rows in the next 32.
 template <class Sh, bool kSwiglu>
-__global__ __launch_bounds__(Sh::kWaves * 64, Sh::NB == 4 ? 1 : 2) void norm_linear_gemm_kernel(GemmParams p) {
-  constexpr int kBM = Sh::kBM, kBN = Sh::kBN, NB = Sh::NB, W = Sh::kWaves, kStages = Sh::kStages;
+__device__ __forceinline__ int gemm_feature(const GemmParams& p, int nt, int R) {
+  if constexpr (kSwiglu) {
+    const int hidden = p.F >> 1;
+    int j = nt * (Sh::kBN / 2) + (R >> 6) * 32 + (R & 31);
+    j = j < hidden ? j : hidden - 1;
+    return ((R >> 5) & 1) ? hidden + j : j;
+  }
+  const int f = nt * Sh::kBN + R;
+  return f < p.F ? f : p.F - 1;
+}
+
+// Row scale, bias, (gate); results pass through the LDS so that they leave in 16-byte pieces, eight
+// lanes per 128-byte row segment.  Each wave stages its part, kStoreBlocks * 32 rows x 64 features at a
+// time, in a region of its own at `stage_w` (128-byte rows, 16-byte chunks XORed with the row so that
+// neither side meets a bank conflict).
+template <class Sh, bool kSwiglu>
+__device__ __forceinline__ void gemm_store(const GemmParams& p, const GemmTileAt& t, f32x16 (&acc)[2][Sh::NB],
+                                           uint32_t stage_w, int wm, int wn, int lane) {
+  constexpr int NB = Sh::NB, kBN = Sh::kBN, SB = Sh::kStoreBlocks;
+  settle(lane);   // addresses are worked out here, not kept through the caller's loop over tiles
+  const int li = lane & 31, g = lane >> 5;
+  const int hidden = p.F >> 1;
+  const float* bias = p.bias ? p.bias + (long long)t.sample * p.F : nullptr;
+  auto position = [](int row, int chunk) __attribute__((always_inline)) {
+    return (uint32_t)(row * 128 + ((chunk ^ ((row >> 1) & 7)) << 4));
+  };
+
+  // writes the wave's staged block (`chunks` 16-byte chunks per row), whose first row is block b0's, to
+  // `dst` (row pitch ld): chunk c of a row goes to column col_of(c)
+  auto flush = [&](bf16_t* dst, long long ld, int chunks, int b0, auto col_of, int limit)
+      __attribute__((always_inline)) {
+    const int rows_per_inst = 64 / chunks;
+    const int r_in = lane / chunks, c = lane % chunks;
+    const int col = col_of(c);
+#pragma unroll 4
+    for (int i = 0; i < SB * 32 / rows_per_inst; ++i) {
+      const int ml = i * rows_per_inst + r_in;
+      const int m = wm * (NB * 32) + b0 * 32 + ml;
+      const u32x4 v = *reinterpret_cast<const AERIS_LDS u32x4*>(stage_w + position(ml, c));
+      if (m < t.valid_rows && col < limit)
+        *reinterpret_cast<u32x4*>(dst + (t.row0 + m) * ld + col) = v;
+    }
+  };
+
+  float rs[NB];
+#pragma unroll
+  for (int b = 0; b < NB; ++b) {
+    int m = wm * (NB * 32) + b * 32 + li;
+    m = m < t.valid_rows ? m : t.valid_rows - 1;
+    rs[b] = p.r ? p.r[t.row0 + m] : 1.f;
+  }
+  // four features from column `col` (a multiple of 4) of the lane's row in staged block b
+  auto stage_store = [&](int b, int col, float o0, float o1, float o2, float o3)
+      __attribute__((always_inline)) {
+    u32x2 v = {pack_bf16(o0, o1), pack_bf16(o2, o3)};
+    *reinterpret_cast<AERIS_LDS u32x2*>(stage_w + position(b * 32 + li, col >> 3) + (col & 4) * 2) = v;
+  };
+
+  if constexpr (kSwiglu) {
+    const int jw = t.nt * (kBN / 2) + wn * 32;         // first gate column of this wave
+    // u and v in place of the products; the fences here and below keep the compiler from working
+    // on all of a wave's values at once, which spills
+#pragma unroll
+    for (int vq = 0; vq < 4; ++vq) {
+      int j = jw + 8 * vq + 4 * g;
+      j = j < hidden ? j : hidden - 4;
+      const f32x4 bu = bias ? *reinterpret_cast<const f32x4*>(bias + j) : f32x4{0.f, 0.f, 0.f, 0.f};
+      const f32x4 bv = bias ? *reinterpret_cast<const f32x4*>(bias + hidden + j) : f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          acc[0][b][4 * vq + e] = __builtin_fmaf(acc[0][b][4 * vq + e], rs[b], bu[e]);
+          acc[1][b][4 * vq + e] = __builtin_fmaf(acc[1][b][4 * vq + e], rs[b], bv[e]);
+        }
+      sched_fence();
+    }
+    if (p.y) {   // the optional uv output, staged as [u 32 | v 32]
+#pragma unroll
+      for (int b0 = 0; b0 < NB; b0 += SB) {
+#pragma unroll
+        for (int b = 0; b < SB; ++b)
+#pragma unroll
+          for (int vq = 0; vq < 4; ++vq) {
+            const f32x16 &u = acc[0][b0 + b], &v = acc[1][b0 + b];
+            stage_store(b, 8 * vq + 4 * g, u[4 * vq], u[4 * vq + 1], u[4 * vq + 2], u[4 * vq + 3]);
+            stage_store(b, 32 + 8 * vq + 4 * g, v[4 * vq], v[4 * vq + 1], v[4 * vq + 2], v[4 * vq + 3]);
+          }
+        // chunk c: c < 4 -> u columns jw + 8c, else v columns hidden + jw + 8(c - 4); a column
+        // past `hidden` (ragged last tile) is marked by F, which the limit rejects
+        flush(p.y, p.F, 8, b0, [&](int c) {
+          const int j = jw + 8 * (c & 3);
+          return j < hidden ? (c < 4 ? j : hidden + j) : p.F;
+        }, p.F);
+      }
+    }
+#pragma unroll
+    for (int b0 = 0; b0 < NB; b0 += SB) {
+#pragma unroll
+      for (int b = 0; b < SB; ++b)
+#pragma unroll
+        for (int vq = 0; vq < 4; ++vq) {
+          float o[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) o[e] = silu(acc[0][b0 + b][4 * vq + e]) * acc[1][b0 + b][4 * vq + e];
+          stage_store(b, 8 * vq + 4 * g, o[0], o[1], o[2], o[3]);
+          sched_fence();
+        }
+      flush(p.g, hidden, 4, b0, [&](int c) { return jw + 8 * c; }, hidden);
+    }
+  } else {
+    const int fw = t.nt * kBN + wn * 64;               // first feature of this wave
+#pragma unroll
+    for (int b0 = 0; b0 < NB; b0 += SB) {
+#pragma unroll
+      for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int vq = 0; vq < 4; ++vq) {
+          int f = fw + a * 32 + 8 * vq + 4 * g;
+          f = f < p.F ? f : p.F - 4;
+          const f32x4 b4 = bias ? *reinterpret_cast<const f32x4*>(bias + f) : f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int b = 0; b < SB; ++b) {
+            const f32x16& v = acc[a][b0 + b];
+            stage_store(b, a * 32 + 8 * vq + 4 * g, __builtin_fmaf(v[4 * vq], rs[b0 + b], b4[0]),
+                        __builtin_fmaf(v[4 * vq + 1], rs[b0 + b], b4[1]),
+                        __builtin_fmaf(v[4 * vq + 2], rs[b0 + b], b4[2]),
+                        __builtin_fmaf(v[4 * vq + 3], rs[b0 + b], b4[3]));
+          }
+        }
+      flush(p.y, p.F, 8, b0, [&](int c) { return fw + 8 * c; }, p.F);
+    }
+  }
+}
+
+template <class Sh>
+__device__ __forceinline__ void gemm_clear(f32x16 (&acc)[2][Sh::NB]) {
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int b = 0; b < Sh::NB; ++b)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.f;
+}
+
+// The two smaller shapes: one workgroup per tile, two per CU.  Bound by the latency of a step (copies,
+// one barrier, the first operand reads), which the CU's other workgroup covers in part.  The loop is
+// written out once per stage, so that every LDS offset is an immediate, with the order of products,
+// reads and copies fenced: the compiler's own order was 4 to 7 % slower (9522 x 2944 -> 704 42.8 us, now
+// 40.9; 4000 x 1024 -> 1024 11.9 / 11.5; 64 x 64 tiles 914 x 1600 -> 512 11.3 / 8.2).
+template <class Sh, bool kSwiglu>
+__global__ __launch_bounds__(Sh::kWaves * 64, 2) void norm_linear_gemm_kernel(GemmParams p) {
+  constexpr int kBN = Sh::kBN, NB = Sh::NB, W = Sh::kWaves, kStages = Sh::kStages;
   constexpr int kPartBytes = Sh::kPartBytes, kStageBytes = Sh::kStageBytes;
   extern __shared__ __align__(16) unsigned char smem[];
-  int mt, nt;
-  if (!gemm_tile(p, mt, nt)) return;
+  GemmTileAt at;
+  if (!gemm_tile_at<Sh>(p, blockIdx.x, at)) return;
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / Sh::WN, wn = wave % Sh::WN;
   const int li = lane & 31, g = lane >> 5;
 
-  const int sample = mt / p.m_tiles_per_sample;
-  const int tile_in_sample = mt - sample * p.m_tiles_per_sample;
-  const long long row0 = (long long)sample * p.rows_per_sample + (long long)tile_in_sample * kBM;
-  const long long rows_left = p.rows_per_sample - (long long)tile_in_sample * kBM;
-  const int valid_rows = rows_left < kBM ? (int)rows_left : kBM;
-  const int hidden = p.F >> 1;
-
-  // Feature (weight row) of tile row R.  SwiGLU tiles pair kBN / 2 u-features with their
-  // v-features: wave column wn holds u rows in its first 32 tile rows, v rows in the next 32.
-  auto feature = [&](int R) __attribute__((always_inline)) {
-    if constexpr (kSwiglu) {
-      int j = nt * (kBN / 2) + (R >> 6) * 32 + (R & 31);
-      j = j < hidden ? j : hidden - 1;
-      return ((R >> 5) & 1) ? hidden + j : j;
-    }
-    const int f = nt * kBN + R;
-    return f < p.F ? f : p.F - 1;
-  };
-
   // ---- copies: instruction j moves rows 8j..8j+7 of the stage; wave w issues
   // j = w + W i.  i < 4: weight rows, i >= 4: token rows.  Rows past the end repeat the last
   // valid row (never stored).  Lane: row j*8 + lane/8, LDS chunk position lane%8.
-  const bf16_t* wmat = p.w + (long long)sample * p.w_sample_stride;
+  const bf16_t* wmat = p.w + (long long)at.sample * p.w_sample_stride;
   const unsigned long long wbase = reinterpret_cast<unsigned long long>(wmat);
-  const unsigned long long xbase = reinterpret_cast<unsigned long long>(p.x + row0 * p.K);
+  const unsigned long long xbase = reinterpret_cast<unsigned long long>(p.x + at.row0 * p.K);
   uint32_t voff[8];
   {
     const int r_in = lane >> 3;
@@ -147,10 +303,10 @@ __global__ __launch_bounds__(Sh::kWaves * 64, Sh::NB == 4 ? 1 : 2) void norm_lin
     for (int i = 0; i < 8; ++i) {
       const int R = ((wave + W * i) << 3) + r_in;
       if (i < 4) {
-        voff[i] = (uint32_t)((long long)feature(R) * p.K * 2 + chunk * 16);
+        voff[i] = (uint32_t)((long long)gemm_feature<Sh, kSwiglu>(p, at.nt, R) * p.K * 2 + chunk * 16);
       } else {
         int m = R - kBN;
-        m = m < valid_rows ? m : valid_rows - 1;
+        m = m < at.valid_rows ? m : at.valid_rows - 1;
         voff[i] = (uint32_t)((long long)m * p.K * 2 + chunk * 16);
       }
     }
@@ -174,12 +330,7 @@ __global__ __launch_bounds__(Sh::kWaves * 64, Sh::NB == 4 ? 1 : 2) void norm_lin
   }
 
   f32x16 acc[2][NB];
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int b = 0; b < NB; ++b)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.f;
+  gemm_clear<Sh>(acc);
 
   const int k_steps = p.K / kBK;
   // stages 0 .. kStages-2 are on their way before the first step
@@ -189,15 +340,18 @@ __global__ __launch_bounds__(Sh::kWaves * 64, Sh::NB == 4 ? 1 : 2) void norm_lin
     for (int i = 0; i < 8; ++i) copy_piece(i, lds0 + st * kStageBytes, st * kBK, st < k_steps);
 
   bf16x8 ao[2][2], bo[2][NB];
-  auto fetch = [&](int set, int kk, uint32_t stage_off) __attribute__((always_inline)) {
+  auto fetch_a = [&](int set, int kk, uint32_t from) __attribute__((always_inline)) {
 #pragma unroll
-    for (int a = 0; a < 2; ++a) ao[set][a] = Sub::read_rm(va[kk] + stage_off + a * 4096);
-#pragma unroll
-    for (int b = 0; b < NB; ++b) bo[set][b] = Sub::read_rm(vb[kk] + stage_off + b * 4096);
+    for (int a = 0; a < 2; ++a) ao[set][a] = Sub::read_rm(va[kk] + from + a * 4096);
   };
-
-  uint32_t stage_off = 0;
-  for (int ks = 0; ks < k_steps; ++ks) {
+  auto fetch_b = [&](int set, int kk, uint32_t from) __attribute__((always_inline)) {
+#pragma unroll
+    for (int b = 0; b < NB; ++b) bo[set][b] = Sub::read_rm(vb[kk] + from + b * 4096);
+  };
+  // One step of 64 channels, in stage `slot`.
+  auto step = [&](auto slot, int ks) __attribute__((always_inline)) {
+    constexpr int kSlot = decltype(slot)::value;
+    constexpr uint32_t kHere = kSlot * kStageBytes, kNext = (kSlot + kStages - 1) % kStages * kStageBytes;
     // This wave's copies of this stage have landed; those of up to kStages - 2 later stages
     // (eight each, in order) may still be on their way.
     if constexpr (kStages == 2) {
@@ -211,136 +365,236 @@ __global__ __launch_bounds__(Sh::kWaves * 64, Sh::NB == 4 ? 1 : 2) void norm_lin
     }
     __syncthreads();               // this stage has landed; every reader of the stage before is done
     const uint32_t more = ks + kStages - 1 < k_steps;
-    // the stage that the last step's readers have left
-    const uint32_t next_off = stage_off == 0 ? (kStages - 1) * kStageBytes : stage_off - kStageBytes;
-    const uint32_t next_stage = lds0 + next_off;
-    fetch(0, 0, stage_off);
+    fetch_a(0, 0, kHere);
+    fetch_b(0, 0, kHere);
     sched_fence();
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) {
-      if (kk < 3) fetch((kk + 1) & 1, kk + 1, stage_off);
 #pragma unroll
-      for (int a = 0; a < 2; ++a)
+      for (int q = 0; q < 2 * NB; ++q) {
+        const int a = q / NB, b = q % NB;
+        acc[a][b] = mfma32(ao[kk & 1][a], bo[kk & 1][b], acc[a][b]);
+        if (kk < 3 && q == 0) fetch_a((kk + 1) & 1, kk + 1, kHere);
+        if (kk < 3 && q == (NB == 1 ? 0 : 1)) fetch_b((kk + 1) & 1, kk + 1, kHere);
+        // the copies of a later stage, the one that the last step's readers have left, ride in the first
+        // half of the step, spread over its products, so that they have the second half to land before
+        // the wait that opens the next step
+        if (kk < 2) {
+          const int n = kk * 2 * NB + q;
 #pragma unroll
-        for (int b = 0; b < NB; ++b) {
-          acc[a][b] = mfma32(ao[kk & 1][a], bo[kk & 1][b], acc[a][b]);
-          // the next stage's copies ride in the first half of the step, spread over its
-          // products, so that they have the second half to land before the wait that opens
-          // the next step
-          if (kk < 2) {
-            const int q = (kk * 2 + a) * NB + b;
-#pragma unroll
-            for (int i = q * 2 / NB; i < (q + 1) * 2 / NB; ++i)
-              copy_piece(i, next_stage, (ks + kStages - 1) * kBK, more);
-          }
+          for (int i = n * 2 / NB; i < (n + 1) * 2 / NB; ++i)
+            copy_piece(i, lds0 + kNext, (ks + kStages - 1) * kBK, more);
         }
-      sched_fence();
-    }
-    stage_off = stage_off + kStageBytes == kStages * kStageBytes ? 0 : stage_off + kStageBytes;
-  }
-
-  // ---- epilogue: row scale, bias, (gate); results pass through the LDS so that they leave in
-  // 16-byte pieces, eight lanes per 128-byte row segment.  Each wave stages its NB*32 x 64 part
-  // in a region of its own (row pitch 144 bytes: 16-byte aligned, rows on different banks).
-  constexpr int kPitch = Sh::kPitch;
-  __syncthreads();                                   // every wave is done with the operand stages
-  const float* bias = p.bias ? p.bias + (long long)sample * p.F : nullptr;
-  const uint32_t stage_w = lds0 + wave * (NB * 32 * kPitch);
-
-  // writes the wave's staged [NB*32][64] bf16 block (8 chunks per row) to `dst` (row pitch ld):
-  // chunk c of a row goes to column col_of(c)
-  auto flush = [&](bf16_t* dst, long long ld, int chunks, auto col_of, int limit)
-      __attribute__((always_inline)) {
-    const int rows_per_inst = 64 / chunks;
-    const int r_in = lane / chunks, c = lane % chunks;
-    const int col = col_of(c);
-    for (int t = 0; t < NB * 32 / rows_per_inst; ++t) {
-      const int ml = t * rows_per_inst + r_in;
-      const int m = wm * (NB * 32) + ml;
-      const u32x4 v = *reinterpret_cast<const AERIS_LDS u32x4*>(stage_w + ml * kPitch + c * 16);
-      if (m < valid_rows && col < limit)
-        *reinterpret_cast<u32x4*>(dst + (row0 + m) * ld + col) = v;
-    }
-  };
-
-  float rs[NB];
-#pragma unroll
-  for (int b = 0; b < NB; ++b) {
-    int m = wm * (NB * 32) + b * 32 + li;
-    m = m < valid_rows ? m : valid_rows - 1;
-    rs[b] = p.r ? p.r[row0 + m] : 1.f;
-  }
-  auto stage_store = [&](int b, int col, float o0, float o1, float o2, float o3)
-      __attribute__((always_inline)) {
-    u32x2 v = {pack_bf16(o0, o1), pack_bf16(o2, o3)};
-    *reinterpret_cast<AERIS_LDS u32x2*>(stage_w + (b * 32 + li) * kPitch + col * 2) = v;
-  };
-
-  if constexpr (kSwiglu) {
-    const int jw = nt * (kBN / 2) + wn * 32;         // first gate column of this wave
-    // u and v in place of the products; the fences here and below keep the compiler from working
-    // on all of a wave's values at once, which spills
-#pragma unroll
-    for (int vq = 0; vq < 4; ++vq) {
-      int j = jw + 8 * vq + 4 * g;
-      j = j < hidden ? j : hidden - 4;
-      const f32x4 bu = bias ? *reinterpret_cast<const f32x4*>(bias + j) : f32x4{0.f, 0.f, 0.f, 0.f};
-      const f32x4 bv = bias ? *reinterpret_cast<const f32x4*>(bias + hidden + j) : f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int b = 0; b < NB; ++b)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          acc[0][b][4 * vq + e] = __builtin_fmaf(acc[0][b][4 * vq + e], rs[b], bu[e]);
-          acc[1][b][4 * vq + e] = __builtin_fmaf(acc[1][b][4 * vq + e], rs[b], bv[e]);
-        }
-      sched_fence();
-    }
-    if (p.y) {   // the optional uv output, staged as [u 32 | v 32]
-#pragma unroll
-      for (int b = 0; b < NB; ++b)
-#pragma unroll
-        for (int vq = 0; vq < 4; ++vq) {
-          stage_store(b, 8 * vq + 4 * g, acc[0][b][4 * vq], acc[0][b][4 * vq + 1],
-                      acc[0][b][4 * vq + 2], acc[0][b][4 * vq + 3]);
-          stage_store(b, 32 + 8 * vq + 4 * g, acc[1][b][4 * vq], acc[1][b][4 * vq + 1],
-                      acc[1][b][4 * vq + 2], acc[1][b][4 * vq + 3]);
-        }
-      // chunk c: c < 4 -> u columns jw + 8c, else v columns hidden + jw + 8(c - 4); a column
-      // past `hidden` (ragged last tile) is marked by F, which the limit rejects
-      flush(p.y, p.F, 8, [&](int c) {
-        const int j = jw + 8 * (c & 3);
-        return j < hidden ? (c < 4 ? j : hidden + j) : p.F;
-      }, p.F);
-    }
-#pragma unroll
-    for (int b = 0; b < NB; ++b)
-#pragma unroll
-      for (int vq = 0; vq < 4; ++vq) {
-        float o[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) o[e] = silu(acc[0][b][4 * vq + e]) * acc[1][b][4 * vq + e];
-        stage_store(b, 8 * vq + 4 * g, o[0], o[1], o[2], o[3]);
         sched_fence();
       }
-    flush(p.g, hidden, 4, [&](int c) { return jw + 8 * c; }, hidden);
-  } else {
-    const int fw = nt * kBN + wn * 64;               // first feature of this wave
+    }
+  };
+  static_assert(kStages == 2 || kStages == 4);
+  for (int ks = 0;;) {
+    step(Const<0>{}, ks);
+    if (++ks == k_steps) break;
+    step(Const<1>{}, ks);
+    if (++ks == k_steps) break;
+    if constexpr (kStages == 4) {
+      step(Const<2>{}, ks);
+      if (++ks == k_steps) break;
+      step(Const<3>{}, ks);
+      if (++ks == k_steps) break;
+    }
+  }
+
+  __syncthreads();                                   // every wave is done with the operand stages
+  gemm_store<Sh, kSwiglu>(p, at, acc, lds0 + wave * Sh::kStoreBytes, wm, wn, lane);
+}
+
+// The 256 x 256 shape: one workgroup of eight wavefronts per CU, which walks over its tiles.
+//
+// Bound by the board's power cap (MFMA pipes busy 79 % of the cycles at 1.62 GHz).  A loop in which all
+// eight waves fetch and multiply together left the pipes idle at every barrier and first fetch (65 % busy
+// at 1.80 GHz).  Here the two waves of a SIMD take turns: a step is two halves of 16 products, and waves
+// 4-7 run one barrier behind waves 0-3, so that one multiplies while the other fetches its operands and
+// issues copies.  A half of a stage is copied over as soon as both waves have its operands in registers,
+// up to seven halves (3000 cycles) ahead of its use, so the waits count copies and hardly ever wait.
+// The last steps of a tile fetch the first of the next one, and its results, staged in the operand stage
+// just left, are stored while the next tile is multiplied: a tile costs 5.7 us beside its steps where
+// separate workgroups took 9.  Per call, us, all waves together / in turns of 8 products,
+// a workgroup per tile / as here, one session: 172800 x 2048 -> 6144 3644 / 3480 / 3292;
+// 172800 x 5504 -> 2048 3229 / 2965 / 2796; 32400 x 1024 -> 3072 185 / 184 / 171.  With
+// v_mfma_f32_16x16x32_bf16, which alone runs cooler, it takes 1.05 times as long.
+template <bool kSwiglu>
+__global__ __launch_bounds__(GemmLarge::kWaves * 64, 2) void projection_gemm_kernel(GemmParams p) {
+  using Sh = GemmLarge;
+  constexpr uint32_t kStageBytes = Sh::kStageBytes, kHalfBytes = kStageBytes / 4;
+  extern __shared__ __align__(16) unsigned char smem[];
+  GemmTileAt at;
+  int item = blockIdx.x;
+  if (!gemm_tile_at<Sh>(p, item, at)) return;
+  const int tid = threadIdx.x;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave / Sh::WN, wn = wave % Sh::WN;
+  const int li = lane & 31, g = lane >> 5;
+  const uint32_t lds0 = lds_address(smem);
+
+  // ---- copies.  A stage is four halves of 128 rows: weight rows 0, 1, token rows 2, 3; half h holds
+  // the h-th 32 of every 64 features (the u or the v features of a SwiGLU tile) and the h-th 64 of
+  // every 128 token rows, so that a wave's part of the tile is 64 features x 128 rows side by side.
+  // Wave w issues instructions w and w + 8 of a half, 8 rows each; lane: row lane / 8, LDS chunk
+  // position lane % 8.  Rows past the end repeat the last valid row (never stored).
+  unsigned long long wbase, xbase;
+  uint32_t voff[8];
+  auto sources = [&](const GemmTileAt& t) __attribute__((always_inline)) {
+    int lane_ = lane;
+    settle(lane_);
+    wbase = reinterpret_cast<unsigned long long>(p.w + (long long)t.sample * p.w_sample_stride);
+    xbase = reinterpret_cast<unsigned long long>(p.x + t.row0 * p.K);
+    const int chunk = (lane_ & 7) ^ Sub::swz(((wave & 1) << 3) | (lane_ >> 3));
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
+    for (int i = 0; i < 4; ++i) {
+      const int h = i >> 1, r = ((wave + 8 * (i & 1)) << 3) + (lane_ >> 3);   // row of the half
+      const int f = gemm_feature<Sh, kSwiglu>(p, t.nt, (r >> 5) * 64 + h * 32 + (r & 31));
+      int m = (r >> 6) * 128 + h * 64 + (r & 63);
+      m = m < t.valid_rows ? m : t.valid_rows - 1;
+      voff[i] = (uint32_t)f * (uint32_t)(p.K * 2) + chunk * 16;
+      voff[4 + i] = (uint32_t)m * (uint32_t)(p.K * 2) + chunk * 16;
+    }
+  };
+  auto copy_half = [&](int half, uint32_t stage, int step) __attribute__((always_inline)) {
 #pragma unroll
-      for (int vq = 0; vq < 4; ++vq) {
-        int f = fw + a * 32 + 8 * vq + 4 * g;
-        f = f < p.F ? f : p.F - 4;
-        const f32x4 b4 = bias ? *reinterpret_cast<const f32x4*>(bias + f) : f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int i = 0; i < 2; ++i)
+      async_copy16_at(voff[2 * half + i], (half < 2 ? wbase : xbase) + (unsigned long long)step * (kBK * 2),
+                      lds0 + stage + half * kHalfBytes + ((wave + 8 * i) << 10));
+  };
+
+  // ---- operand reads: per lane four chunk offsets (one per 16-channel block of a step)
+  uint32_t va[4], vb[4];
 #pragma unroll
-        for (int b = 0; b < NB; ++b)
-          stage_store(b, a * 32 + 8 * vq + 4 * g,
-                      __builtin_fmaf(acc[a][b][4 * vq], rs[b], b4[0]),
-                      __builtin_fmaf(acc[a][b][4 * vq + 1], rs[b], b4[1]),
-                      __builtin_fmaf(acc[a][b][4 * vq + 2], rs[b], b4[2]),
-                      __builtin_fmaf(acc[a][b][4 * vq + 3], rs[b], b4[3]));
+  for (int kk = 0; kk < 4; ++kk) {
+    const uint32_t off = li * 128 + (((2 * kk + g) ^ Sub::swz(li)) << 4);
+    va[kk] = lds0 + wn * 4096 + off;
+    vb[kk] = lds0 + 2 * kHalfBytes + wm * 8192 + off;
+  }
+
+  f32x16 acc[2][4];
+  bf16x8 w0[4], w1[4], x[2][4];
+  auto fetch_w = [&](bf16x8 (&w)[4], uint32_t from) __attribute__((always_inline)) {
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) w[kk] = Sub::read_rm(va[kk] + from);
+  };
+  auto fetch_x = [&](uint32_t from) __attribute__((always_inline)) {
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+      for (int b = 0; b < 2; ++b) x[b][kk] = Sub::read_rm(vb[kk] + from + b * 4096);
+  };
+  // all but the newest `behind` copies of this wave have landed
+  auto landed = [&](auto behind) __attribute__((always_inline)) {
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(decltype(behind)::value) : "memory");
+  };
+  auto meet = [&]() __attribute__((always_inline)) {
+    sched_fence();
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    sched_fence();
+  };
+  // Token rows of half h by all 64 features: 16 products between two meetings, while the other wave of the
+  // SIMD fetches.  Reads are complete when a wave meets the others, so that copies issued after a meeting
+  // may overwrite what was read before it.
+  auto products = [&](int h) __attribute__((always_inline)) {
+    meet();
+    __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+      for (int b = 0; b < 2; ++b) {
+        acc[0][2 * h + b] = mfma32(w0[kk], x[b][kk], acc[0][2 * h + b]);
+        acc[1][2 * h + b] = mfma32(w1[kk], x[b][kk], acc[1][2 * h + b]);
       }
-    flush(p.y, p.F, 8, [&](int c) { return fw + 8 * c; }, p.F);
+    __builtin_amdgcn_s_setprio(0);
+    meet();
+  };
+
+  const int k_steps = p.K / kBK;
+  GemmTileAt next;
+  bool follows = false, first_tile = true;        // follows: another tile after this one
+  sources(at);
+  copy_half(0, 0, 0);
+  copy_half(1, 0, 0);
+  copy_half(2, 0, 0);
+  copy_half(3, 0, 0);
+  if (k_steps > 1) {
+    copy_half(0, kStageBytes, 1);
+    copy_half(1, kStageBytes, 1);
+    copy_half(2, kStageBytes, 1);
+    landed(Const<8>{});
+  } else {
+    landed(Const<2>{});
+  }
+  meet();
+  if (wm == 1) meet();
+  gemm_clear<Sh>(acc);
+  uint32_t here = 0;
+  for (int t = 0;;) {
+    const bool fresh = t == 0 && !first_tile;     // the whole step has landed
+    if (t == 0) follows = k_steps > 1 && gemm_tile_at<Sh>(p, item + gridDim.x, next);
+    if (!fresh)
+      for (; t + 2 < k_steps; ++t, here = kStageBytes - here) {
+        fetch_w(w0, here);
+        fetch_w(w1, here + kHalfBytes);
+        fetch_x(here);
+        copy_half(3, kStageBytes - here, t + 1);
+        landed(Const<8>{});
+        products(0);
+        fetch_x(here + kHalfBytes);
+        copy_half(0, here, t + 2);
+        copy_half(1, here, t + 2);
+        copy_half(2, here, t + 2);
+        landed(Const<8>{});
+        products(1);
+      }
+    const uint32_t other = kStageBytes - here;
+    const int left = k_steps - 1 - t;             // steps of this tile after this one
+    fetch_w(w0, here);
+    fetch_w(w1, here + kHalfBytes);
+    fetch_x(here);
+    if (left >= 1 || follows) {
+      copy_half(3, other, left >= 1 ? t + 1 : 0);
+      if (!fresh) landed(Const<8>{});
+    } else {
+      landed(Const<0>{});
+    }
+    products(0);
+    fetch_x(here + kHalfBytes);
+    if (left >= 2 || (left == 1 && follows)) {
+      if (left == 1) sources(next);
+      const int ahead = left >= 2 ? t + 2 : 0;
+      copy_half(0, here, ahead);
+      copy_half(1, here, ahead);
+      copy_half(2, here, ahead);
+      landed(Const<8>{});
+    } else if (left == 1) {
+      landed(Const<2>{});
+    } else {
+      landed(Const<0>{});
+    }
+    products(1);
+
+    if (left == 0) {
+      if (wm == 0) meet();
+      gemm_store<Sh, kSwiglu>(p, at, acc, lds0 + here + wave * Sh::kStoreBytes, wm, wn, lane);
+      if (!follows) return;
+      meet();          // every wave has read its results back: the stage may be filled again
+      gemm_clear<Sh>(acc);
+      copy_half(0, here, 1);
+      copy_half(1, here, 1);
+      copy_half(2, here, 1);
+      if (wm == 1) meet();
+      at = next;
+      item += gridDim.x;
+      first_tile = false;
+      t = 0;
+    } else {
+      ++t;
+    }
+    here = other;
   }
 }
 
@@ -443,9 +697,18 @@ bool gemm_tiles(GemmParams& p) {
 
 template <class Sh, bool kSwiglu>
 int launch_gemm_kernel(const GemmParams& p, hipStream_t stream) {
-  if (!allow_full_lds<norm_linear_gemm_kernel<Sh, kSwiglu>>()) return -1;
-  return launch_kernel(norm_linear_gemm_kernel<Sh, kSwiglu>, dim3(gemm_grid(p)),
-                       dim3(Sh::kWaves * 64), (size_t)Sh::kSmem, stream, p);
+  if constexpr (std::is_same<Sh, GemmLarge>::value) {
+    // one workgroup per CU, which walks its tiles (every 256th); all of them where a tile has too few
+    // steps to look into the next one
+    const unsigned items = gemm_grid(p);
+    if (!allow_full_lds<projection_gemm_kernel<kSwiglu>>()) return -1;
+    return launch_kernel(projection_gemm_kernel<kSwiglu>, dim3(p.K > kBK && items > kCus ? kCus : items),
+                         dim3(Sh::kWaves * 64), (size_t)Sh::kSmem, stream, p);
+  } else {
+    if (!allow_full_lds<norm_linear_gemm_kernel<Sh, kSwiglu>>()) return -1;
+    return launch_kernel(norm_linear_gemm_kernel<Sh, kSwiglu>, dim3(gemm_grid(p)),
+                         dim3(Sh::kWaves * 64), (size_t)Sh::kSmem, stream, p);
+  }
 }
 template <class Sh>
 int launch_gemm_shape(const GemmParams& p, hipStream_t stream) {
@@ -456,26 +719,25 @@ int launch_gemm_shape(const GemmParams& p, hipStream_t stream) {
 // round takes (microseconds: a fixed part plus a part per 64-channel step, less of both for a last
 // round that leaves CUs empty).  Medium tiles fetch the rows twice as often as large ones, which
 // counts once rows and results exceed the last-level cache (300000 x 192 -> 576 145 us with large
-// tiles, 161 with medium ones; 60000 x 192 -> 1408 67 / 58).  Fitted to 1485 sizes of 2000 ... 300000
-// rows, 64 ... 8192 channels and 64 ... 4608 features: what it takes is 0.35 % slower than the better
-// shape on average, more than 5 % at 30 of them.  Small tiles have the shortest steps and are taken as
-// long as each has a CU of its own: 500 rows x 1024 -> 1024 takes 22.7 / 11.2 / 10.0 us with large /
-// medium / small tiles, 2000 x 512 -> 1536 (768 small tiles) 15.4 / 9.0 / 13.8.  Medium tiles win
-// while large ones leave more than about half of the CUs without work (4000 x 1024 -> 1024: 27.4 /
-// 14.1), large ones, with half the operand bytes per product, from there on (157 large tiles, 40000 x
-// 1984 -> 192: 44.6 / 57.6; 141, 12000 x 960 -> 768: 25.2 / 29.8; 172800 x 2048 -> 2048: 1247 / 1444).
+// tiles, 161 with medium ones; 60000 x 192 -> 1408 67 / 58).  Fitted to 200 sizes of 1500 ... 150000
+// rows, 64 ... 5760 channels and 128 ... 6400 features: what it takes is 0.5 % slower than the better
+// shape on average, more than 7 % at 5 of them.  Small tiles have the shortest steps and are taken as
+// long as each has a CU of its own: 914 rows x 1600 -> 512 takes 8.2 us with small, 12.7 with medium
+// tiles, 1759 x 640 -> 1344 (588 small tiles) 11.0 and 7.8.  Medium tiles win
+// while large ones leave more than about half of the CUs without work (9522 x 2944 -> 704, 114 large
+// tiles: 41 / 57), large ones, with half the operand bytes per product, from there on (148, 18926 x
+// 2560 -> 512: 70 / 53; 150, 12738 x 5248 -> 704: 133 / 99; 172800 x 2048 -> 2048: 1391 / 1097).
 enum class GemmTile { kLarge, kMedium, kSmall };
 GemmTile choose_gemm_tile(long long large_tiles, long long medium_tiles, long long small_tiles, int steps,
                           bool cached) {
-  constexpr long long kCus = 256;
-  if (small_tiles <= kCus) return GemmTile::kSmall;
+  if (small_tiles <= (long long)kCus) return GemmTile::kSmall;
   // one large workgroup per CU, two medium ones
   const double large_rest = (double)(large_tiles % kCus) / kCus;
-  const double large = (double)(large_tiles / kCus) * (9.0 + 1.5 * steps) +
-                       (large_rest > 0.0 ? 6.5 + steps * (1.09 + 0.41 * large_rest * large_rest) : 0.0);
+  const double large = (double)(large_tiles / kCus) * (5.7 + 1.45 * steps) +
+                       (large_rest > 0.0 ? 7.2 + steps * (0.83 + 0.85 * large_rest * large_rest) : 0.0);
   const double medium_rest = (double)(medium_tiles % (2 * kCus)) / (2 * kCus);
-  const double medium = (double)(medium_tiles / (2 * kCus)) * (3.6 + 0.9 * steps) +
-                        (medium_rest > 0.0 ? 3.6 + steps * (0.58 + 0.32 * medium_rest) : 0.0);
+  const double medium = (double)(medium_tiles / (2 * kCus)) * (2.5 + 0.93 * steps) +
+                        (medium_rest > 0.0 ? 4.8 + steps * (0.42 + 0.45 * medium_rest) : 0.0);
   return medium * (cached ? 1.0 : 1.2) < large ? GemmTile::kMedium : GemmTile::kLarge;
 }
 

@@ -143,10 +143,10 @@ __host__ __device__ inline int grid_blocks(const KParams& p) {
   return 8 * ((p.n_pairs + 7) / 8) * p.n_tiles;
 }
 
-// Work item of this workgroup in a list of `total` items = gridDim.x: consecutive workgroup ids
+// Place in a list of `total` of the id-th of as many work items: consecutive ids (of workgroups)
 // go to the eight XCDs in turn; XCD x gets the x-th of eight contiguous pieces of the list.
-__device__ __forceinline__ int xcd_contiguous(int total) {
-  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+__device__ __forceinline__ int xcd_contiguous(int id, int total) {
+  const int xcd = id & 7, slot = id >> 3;
   const int share = total >> 3, extra = total & 7;
   return xcd * share + (xcd < extra ? xcd : extra) + slot;
 }
@@ -448,6 +448,12 @@ __device__ __forceinline__ void async_copy16_off(uint32_t offset, unsigned long 
       : "v"(offset), "s"(base), "s"(__builtin_amdgcn_readfirstlane(lds_base)),
         "s"(__builtin_amdgcn_readfirstlane(enable))
       : "memory", "scc");
+}
+__device__ __forceinline__ void async_copy16_at(uint32_t offset, unsigned long long base, uint32_t lds_base) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+               :
+               : "v"(offset), "s"(base), "s"(__builtin_amdgcn_readfirstlane(lds_base))
+               : "memory");
 }
 __device__ __forceinline__ void wait_async_loads() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 

@@ -166,6 +166,18 @@ def test_projections_with_every_tile_shape(n_samples, rows, channels, features, 
     test_norm_linear_swiglu_fwd(n_samples, rows, channels, features // 2)
 
 
+@pytest.mark.parametrize("channels", [64, 128, 192, 320])   # one step of a tile to five
+def test_workgroups_that_walk_over_several_tiles(channels):
+    """432 tiles of 256 x 256 for 256 CUs, ragged both ways, two samples: with two steps or more a
+    workgroup fetches into its next tile while it works on the last steps of one, and stages results
+    in the operand stage that it has just left."""
+    n_samples, rows, features = 2, 2990, 4400
+    assert B.aeris_projection_plan(n_samples * rows, rows, channels, features)[0] == 256
+    test_linear_fwd(n_samples * rows, channels, features)
+    test_norm_linear_fwd(n_samples, rows, channels, features)
+    test_norm_linear_swiglu_fwd(n_samples, rows, channels, features // 2)
+
+
 def test_qkv_projection_at_the_headline_size_on_sampled_rows():
     """4 x 720 x 1440 token rows x 2048 channels -> 6144 features (the QKV projection of the
     headline workload, in the launch configuration bench.py times): sampled rows against the
