@@ -30,36 +30,6 @@ __host__ __device__ inline long long stat_entries(const KParams& p) {
 // delta and LSE*log2e in window order.  One thread per 8 channels of one token
 // of one (batch, window, head); the D/8 threads of a token reduce by shuffles.
 // ----------------------------------------------------------------------------
-// Eight channels as they lie in memory, and their values.
-template <typename T>
-struct Raw8;
-template <>
-struct Raw8<bf16_t> {
-  u32x4 r;
-  __device__ __forceinline__ void load(const bf16_t* src) { r = *reinterpret_cast<const u32x4*>(src); }
-  __device__ __forceinline__ void values(float* out) const {
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      out[2 * w] = __uint_as_float(r[w] << 16);
-      out[2 * w + 1] = __uint_as_float(r[w] & 0xffff0000u);
-    }
-  }
-};
-template <>
-struct Raw8<float> {
-  f32x4 a, b;
-  __device__ __forceinline__ void load(const float* src) {
-    a = *reinterpret_cast<const f32x4*>(src);
-    b = *reinterpret_cast<const f32x4*>(src + 4);
-  }
-  __device__ __forceinline__ void values(float* out) const {
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      out[w] = a[w];
-      out[4 + w] = b[w];
-    }
-  }
-};
 template <typename T>
 __device__ __forceinline__ void load8(const T* src, float* out) {
   Raw8<T> raw;
@@ -701,6 +671,9 @@ static int launch_bwd_t(KParams kp, const void* q, const void* k, const void* v,
 
   float* delta = workspace;
   float* lse2 = workspace + stat_entries(kp);
+  if (stages == 7u && short_backward(kp, D))
+    return launch_bwd_short(kp, D, std::is_same<OutT, float>::value, q, k, v, o, lse, d_o, delta, lse2, dq, dk, dv,
+                            stream);
   // with both stages requested the dQ kernel produces the statistics itself
   const bool fused_stats = (stages & 3u) == 3u;
   if ((stages & 1u) && !fused_stats) {

@@ -290,6 +290,12 @@ __device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 
+// v_mfma_f32_16x16x32_bf16: D[16x16] += A[16x32] * B[32x16].  Lane l supplies A[l%16] and B's column l%16
+// at contraction indices 8*(l/16) .. +8 and receives D[4*(l/16) + v][l%16].
+__device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+
 // Row of a 32x32 accumulator tile held in register v by a lane of half g.
 __device__ __forceinline__ int acc_row(int v, int g) { return 8 * (v >> 2) + 4 * g + (v & 3); }
 
@@ -463,6 +469,13 @@ __device__ __forceinline__ void wait_async_loads() { asm volatile("s_waitcnt vmc
 template <typename V>
 __device__ __forceinline__ void settle(V& v) {
   asm volatile("" : "+v"(v));
+}
+
+// Barrier for data in the LDS alone: stores to memory stay in flight, which __syncthreads() would wait for.
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
 }
 
 // Nothing is scheduled across this point: pins a hand-made interleaving of
@@ -642,6 +655,36 @@ struct Tile {
   }
 };
 
+// Eight channels as they lie in memory, and their values.
+template <typename T>
+struct Raw8;
+template <>
+struct Raw8<bf16_t> {
+  u32x4 r;
+  __device__ __forceinline__ void load(const bf16_t* src) { r = *reinterpret_cast<const u32x4*>(src); }
+  __device__ __forceinline__ void values(float* out) const {
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      out[2 * w] = __uint_as_float(r[w] << 16);
+      out[2 * w + 1] = __uint_as_float(r[w] & 0xffff0000u);
+    }
+  }
+};
+template <>
+struct Raw8<float> {
+  f32x4 a, b;
+  __device__ __forceinline__ void load(const float* src) {
+    a = *reinterpret_cast<const f32x4*>(src);
+    b = *reinterpret_cast<const f32x4*>(src + 4);
+  }
+  __device__ __forceinline__ void values(float* out) const {
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      out[w] = a[w];
+      out[4 + w] = b[w];
+    }
+  }
+};
 // Output element stores: four consecutive channels of one token.
 __device__ __forceinline__ void store4(bf16_t* dst, float a, float b, float c, float d) {
   u32x2 v = {pack_bf16(a, b), pack_bf16(c, d)};

@@ -59,6 +59,13 @@ int launch_dkdv_pipe128(const KParams& kp, bool out_f32, const void* q, const vo
                         const void* v, const void* d_o, const float* delta, const float* lse2,
                         void* dk, void* dv, hipStream_t stream);
 
+// All stages of launch_bwd in one kernel, for windows that one workgroup can hold (same contract; delta
+// and lse2 are the two workspace vectors), and whether that is the way to run a problem.
+int launch_bwd_short(const KParams& kp, int head_dim, bool out_f32, const void* q, const void* k,
+                     const void* v, const void* o, const float* lse, const void* d_o, float* delta,
+                     float* lse2, void* dq, void* dk, void* dv, hipStream_t stream);
+bool short_backward(const KParams& kp, int head_dim);
+
 // y = rotary embedding of x (inverse: the rotation by the negated angles); both
 // [B, H, W, heads, head_dim] bf16 with the given element strides.  Uses kp.rope_pos, kp.rope_c.
 int launch_rope(const KParams& kp, int head_dim, const void* x, long long x_tok, long long x_head,

@@ -252,6 +252,30 @@ def test_head_dim_128_dkdv_by_window_size(win):
              seed=56)
 
 
+@pytest.mark.parametrize("d", [32, 64, 128])
+@pytest.mark.parametrize("win", [(1, 1), (3, 5), (4, 4), (1, 17), (4, 8), (3, 11), (6, 8), (7, 7), (7, 9),
+                                 (8, 8), (5, 13), (8, 16), (3, 43), (12, 12), (5, 29), (11, 16), (12, 16),
+                                 (1, 193)])
+def test_short_windows_by_size(win, d):
+    """Windows around the units of 16 keys, blocks of 32 queries and one to four waves of the one-kernel
+    backward pass, and on both sides of where it ends (192, 144, 64 tokens at head_dim 32, 64, 128);
+    the statistics it leaves serve a dK/dV stage of its own."""
+    shape, shift = (1, 2 * win[0], 3 * win[1], 2, d), (win[0] // 2, win[1] // 3)
+    run_case(shape, win, shift, B.AERIS_MASK_SWIN, seed=77)
+    tq, tk, tv, tdo = [to_dev(b) for b in synth.make_inputs("normal", 78, shape, 4)]
+    o, lse = B.aeris_winattn_fwd(tq, tk, tv, win, shift, B.AERIS_MASK_LAT)
+    ws = torch.empty(B.aeris_winattn_bwd_workspace_bytes(B.make_params(shape, win, shift, B.AERIS_MASK_LAT)),
+                     dtype=torch.uint8, device="cuda")
+    whole, again = [[torch.full_like(tq, float("nan")) for _ in range(3)] for _ in range(2)]
+    for g, stages in ((whole, B.AERIS_BWD_ALL), (again, B.AERIS_BWD_DKDV)):
+        B.aeris_winattn_bwd_stages(tq, tk, tv, o, lse, tdo, win, shift, B.AERIS_MASK_LAT, dq=g[0], dk=g[1],
+                                   dv=g[2], workspace=ws, stages=stages)
+    torch.cuda.synchronize()
+    for a, b in zip(whole[1:], again[1:]):   # two orders of fp32 sums, each rounded to bf16 once
+        a, b = to_f64(a), to_f64(b)
+        assert np.linalg.norm(a - b) <= 3e-3 * max(np.linalg.norm(b), 1e-3 * np.sqrt(b.size))
+
+
 @pytest.mark.parametrize("shift", [(0, 0), (5, 7)])
 def test_one_window_is_global_attention(shift):
     run_case((1, 24, 40, 2, 64), (24, 40), shift, B.AERIS_MASK_NONE, seed=61)
