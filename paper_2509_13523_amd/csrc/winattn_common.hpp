@@ -695,4 +695,16 @@ __device__ __forceinline__ void store4(float* dst, float a, float b, float c, fl
   *reinterpret_cast<f32x4*>(dst) = v;
 }
 
+// Stores of a 16-lane group's token: channels 4g.. of two blocks of 16 channels, `a` at row and `b` at
+// row + 16.  bf16: neighbouring lane groups exchange halves, so that each lane stores 16 bytes.
+__device__ __forceinline__ void store_blocks(float* row, int g, const float (&a)[4], const float (&b)[4]) {
+  store4(row + 4 * g, a[0], a[1], a[2], a[3]);
+  store4(row + 16 + 4 * g, b[0], b[1], b[2], b[3]);
+}
+__device__ __forceinline__ void store_blocks(bf16_t* row, int g, const float (&a)[4], const float (&b)[4]) {
+  const auto lo = __builtin_amdgcn_permlane16_swap(pack_bf16(a[0], a[1]), pack_bf16(b[0], b[1]), false, false);
+  const auto hi = __builtin_amdgcn_permlane16_swap(pack_bf16(a[2], a[3]), pack_bf16(b[2], b[3]), false, false);
+  *reinterpret_cast<u32x4*>(row + 16 * (g & 1) + 8 * (g >> 1)) = u32x4{lo[0], hi[0], lo[1], hi[1]};
+}
+
 }  // namespace aeris

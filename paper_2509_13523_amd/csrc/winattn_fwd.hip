@@ -316,6 +316,8 @@ static int launch_fwd_t(const KParams& kp, const void* q, const void* k, const v
 
 int launch_fwd(const KParams& kp, int head_dim, bool out_f32, const void* q, const void* k,
                const void* v, void* o, float* lse, hipStream_t stream) {
+  if (short_forward(kp, head_dim))
+    return launch_fwd_short(kp, head_dim, out_f32, q, k, v, o, lse, stream);
 #define AERIS_FWD_CASE(DD)                                                             \
   case DD:                                                                             \
     return out_f32 ? launch_fwd_t<DD, float>(kp, q, k, v, o, lse, stream)              \

@@ -49,6 +49,11 @@ inline int launch_kernel(void (*kern)(Params...), dim3 grid, dim3 block, size_t 
 int launch_fwd(const KParams& kp, int head_dim, bool out_f32, const void* q, const void* k,
                const void* v, void* o, float* lse, hipStream_t stream);
 
+// The same for windows that one workgroup can hold, and whether that is the way to run a problem.
+int launch_fwd_short(const KParams& kp, int head_dim, bool out_f32, const void* q, const void* k,
+                     const void* v, void* o, float* lse, hipStream_t stream);
+bool short_forward(const KParams& kp, int head_dim);
+
 int launch_bwd(const KParams& kp, int head_dim, bool out_f32, const void* q, const void* k,
                const void* v, const void* o, const float* lse, const void* d_o, void* dq,
                void* dk, void* dv, float* workspace, hipStream_t stream, unsigned stages);
