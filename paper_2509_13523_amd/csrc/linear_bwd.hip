@@ -293,6 +293,198 @@ __global__ __launch_bounds__(S::kWaves * 64, S::kWaves * S::kPerCu / 4) void lin
     }
 }
 
+// The same for the 256 x 256 shape, whose two waves of a SIMD take turns as in projection_gemm_kernel:
+// a step is two halves of 32 rows and 16 products, and waves 4-7 run one barrier behind waves 0-3, so
+// that one multiplies while the other fetches its operands and issues copies.  A half of a stage is
+// copied over as soon as both waves have its operands in registers, three halves ahead of its use.
+// Bound by the board's power cap.  172800 rows, us, all waves together / in turns, one session: 2048 -> 2048
+// 1390 / 1251, 2048 -> 6144 3655 / 3461, 5504 -> 2048 3572 / 3325, 2048 -> 11008 6538 / 6445.
+__global__ __launch_bounds__(512, 2) void linear_wgrad_large_kernel(WgradParams p) {
+  using S = WgradLarge;
+  using Sub = S::Sub;
+  constexpr int FB = S::FB, CB = S::CB, kP = S::kPieces, kSubs = S::kFSubs + S::kCSubs;
+  static_assert(S::kPiecesPerSub == 2 && S::kStages == 2 && S::kRun == 0);
+  extern __shared__ __align__(16) unsigned char smem[];
+  int split, ft, ct;
+  wgrad_tile(p, 32, split, ft, ct);
+  const int tid = threadIdx.x;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wf = wave / S::CW, wc = wave % S::CW;
+  const int li = lane & 31, g = lane >> 5;
+  const int f0 = ft * S::kTF, c0 = ct * S::kTC;
+  const int s0 = split * p.steps_per_split;
+  const int s1 = s0 + p.steps_per_split < p.steps_total ? s0 + p.steps_per_split : p.steps_total;
+
+  // ---- copies, as above; piece 2 t + h of a wave: four rows of half h of sub-tile t
+  constexpr int kChunks = S::kWidth / 8;
+  auto piece_row = [&](int i) __attribute__((always_inline)) {
+    return S::kRowsPerInst * (wave + S::kWaves * (i & 1)) + lane / kChunks;
+  };
+  uint32_t voff[kP];
+#pragma unroll
+  for (int i = 0; i < kP; ++i) {
+    const int t = i >> 1, r = piece_row(i), chunk = (lane % kChunks) ^ Sub::swz(r);
+    const bool is_dy = t < S::kFSubs;
+    const int ld = is_dy ? p.F : p.C;
+    int col = (is_dy ? f0 + S::kWidth * t : c0 + S::kWidth * (t - S::kFSubs)) + 8 * chunk;
+    col = col < ld ? col : ld - 8;
+    voff[i] = (uint32_t)(((long long)r * ld + col) * 2);
+  }
+  const uint32_t lds0 = lds_address(smem);
+  const unsigned long long dy_step = (unsigned long long)kTM * 2 * p.F;
+  const unsigned long long x_step = (unsigned long long)kTM * 2 * p.C;
+  const unsigned long long dy0 = reinterpret_cast<unsigned long long>(p.dy), x0 = reinterpret_cast<unsigned long long>(p.x);
+  auto copy_rows = [&](int h, uint32_t stage, unsigned long long dy_at, unsigned long long x_at)
+      __attribute__((always_inline)) {
+#pragma unroll
+    for (int t = 0; t < kSubs; ++t)
+      async_copy16_at(voff[2 * t + h], t < S::kFSubs ? dy_at : x_at,
+                      lds0 + stage + (uint32_t)(t * S::kSubBytes + ((wave + S::kWaves * h) << 10)));
+  };
+  auto copy_half = [&](int h, uint32_t stage, int step) __attribute__((always_inline)) {
+    if (p.tail != 0 && step == p.steps_total - 1) {        // the last copies of all stop at the last row
+#pragma unroll
+      for (int t = 0; t < kSubs; ++t) {
+        const int past = piece_row(2 * t + h) - (p.tail - 1);
+        voff[2 * t + h] -= past > 0 ? (uint32_t)past * (uint32_t)((t < S::kFSubs ? p.F : p.C) * 2) : 0u;
+      }
+    }
+    copy_rows(h, stage, dy0 + step * dy_step, x0 + step * x_step);
+  };
+
+  // ---- transposing operand reads, as above
+  uint32_t ta[FB][2], tb[CB][2];
+  {
+    const int j = lane & 15, blk = lane >> 4;
+    auto address = [&](int first, int col, int h) __attribute__((always_inline)) {
+      const int r = 8 * h + 4 * (blk >> 1) + (j >> 2);
+      const int c = (col % S::kWidth) / 8 + 2 * (blk & 1) + ((j & 3) >> 1);
+      return lds0 + (first + col / S::kWidth) * S::kSubBytes + Sub::chunk_offset(r, c) + (j & 1) * 8;
+    };
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+#pragma unroll
+      for (int a = 0; a < FB; ++a) ta[a][h] = address(0, (wf * FB + a) * 32, h);
+#pragma unroll
+      for (int b = 0; b < CB; ++b) tb[b][h] = address(S::kFSubs, (wc * CB + b) * 32, h);
+    }
+  }
+
+  f32x16 acc[FB][CB];
+#pragma unroll
+  for (int a = 0; a < FB; ++a)
+#pragma unroll
+    for (int b = 0; b < CB; ++b)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.f;
+
+  bf16x8 ao[2][FB], bo[2][CB];
+  auto landed = [&](auto behind) __attribute__((always_inline)) {
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(decltype(behind)::value) : "memory");
+  };
+  auto fetch = [&](int h, uint32_t here) __attribute__((always_inline)) {
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk) {
+      const uint32_t off = here + (2 * h + kk) * (16 * S::kWidth * 2);
+#pragma unroll
+      for (int a = 0; a < FB; ++a) ao[kk][a] = Sub::read_tr(ta[a][0] + off, ta[a][1] + off);
+#pragma unroll
+      for (int b = 0; b < CB; ++b) bo[kk][b] = Sub::read_tr(tb[b][0] + off, tb[b][1] + off);
+    }
+  };
+  // rows past the end, which hold copies of the last row, are cleared in the operands of both sides
+  auto clear_past_end = [&](int h) __attribute__((always_inline)) {
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk) {
+      const int row0 = (2 * h + kk) * 16 + 4 * g;          // element e: row row0 + 8 (e / 4) + e % 4
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const bool keep = row0 + 8 * (e >> 2) + (e & 3) < p.tail;
+#pragma unroll
+        for (int a = 0; a < FB; ++a) ao[kk][a][e] = keep ? ao[kk][a][e] : (bf16_t)0.f;
+#pragma unroll
+        for (int b = 0; b < CB; ++b) bo[kk][b][e] = keep ? bo[kk][b][e] : (bf16_t)0.f;
+      }
+    }
+  };
+  auto products = [&]() __attribute__((always_inline)) {
+    lds_barrier();
+    __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+      for (int a = 0; a < FB; ++a)
+#pragma unroll
+        for (int b = 0; b < CB; ++b) acc[a][b] = mfma32(ao[kk][a], bo[kk][b], acc[a][b]);
+    __builtin_amdgcn_s_setprio(0);
+    lds_barrier();
+  };
+
+  copy_half(0, 0, s0);
+  copy_half(1, 0, s0);
+  if (s0 + 1 < s1) {
+    copy_half(0, S::kStageBytes, s0 + 1);
+    landed(Const<8>{});
+  } else {
+    landed(Const<4>{});
+  }
+  lds_barrier();
+  if (wf == 1) lds_barrier();
+  uint32_t here = 0;
+  int ks = s0;
+  // steps that copy whole steps only; those look for no last one, and their addresses need no products
+  const int plain_end = p.tail != 0 && s1 == p.steps_total ? s1 - 1 : s1;
+  unsigned long long dy_at = dy0 + (s0 + 1) * dy_step, x_at = x0 + (s0 + 1) * x_step;   // of the next step
+  for (; ks + 2 < plain_end; ++ks, here = S::kStageBytes - here) {
+    fetch(0, here);
+    copy_rows(1, S::kStageBytes - here, dy_at, x_at);
+    landed(Const<8>{});
+    products();
+    dy_at += dy_step;
+    x_at += x_step;
+    fetch(1, here);
+    copy_rows(0, here, dy_at, x_at);
+    landed(Const<8>{});
+    products();
+  }
+  for (; ks < s1; ++ks, here = S::kStageBytes - here) {
+    const bool clear = p.tail != 0 && ks == p.steps_total - 1, more = ks + 1 < s1;
+    fetch(0, here);
+    if (more) {
+      copy_half(1, S::kStageBytes - here, ks + 1);
+      landed(Const<8>{});
+    } else {
+      landed(Const<0>{});
+    }
+    if (clear) clear_past_end(0);
+    products();
+    fetch(1, here);
+    if (ks + 2 < s1) {
+      copy_half(0, here, ks + 2);
+      landed(Const<8>{});
+    } else if (more) {
+      landed(Const<4>{});
+    }
+    if (clear) clear_past_end(1);
+    products();
+  }
+  if (wf == 0) lds_barrier();
+
+  // ---- partial tile: a lane owns one channel column, a register one feature row
+  float* out = p.out + (long long)split * p.F * p.C;
+#pragma unroll
+  for (int a = 0; a < FB; ++a)
+#pragma unroll
+    for (int b = 0; b < CB; ++b) {
+      const int c = c0 + (wc * CB + b) * 32 + li;
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const int f = f0 + (wf * FB + a) * 32 + acc_row(e, g);
+        if (f < p.F && c < p.C) out[(long long)f * p.C + c] = acc[a][b][e];
+      }
+    }
+}
+
 // dW = sum of the partial tiles, in the order of the splits.  n4: number of 4-float groups of dW.
 // kInFlight loads of a thread at a time: eight where few threads have to cover the latency (65536 x 4
 // bytes, 48 ranges: 30 us with one, 23 with eight); one where a full grid does and more streams only
@@ -412,7 +604,7 @@ int large_ranges(int whole_steps, int32_t channels, int32_t features) {
 
 // The plan that is estimated to end first.  Times per step measured over 1000 ... 172800 rows,
 // 128 ... 5504 channels and 128 ... 11008 features; the 256 x 256 shape alone took (start to end, us)
-// 43 / 44 / 98 / 159 / 117 / 79 where this takes 12 / 22 / 80 / 86 / 72 / 55: 1000 x 1024 -> 1024,
+// 43 / 44 / 98 / 159 / 117 / 79, with all its waves together, where this takes 12 / 22 / 80 / 86 / 72 / 55: 1000 x 1024 -> 1024,
 // 4000 x 512 -> 1536, 8000 x 2048 -> 2048, 20011 x 768 -> 2304, 30000 x 1024 -> 1024,
 // 100000 x 256 -> 768.  The smaller shapes take as many ranges as the largest has, or fewer: the
 // workspace holds that many partial tiles (plan.most), and their chains of additions are broken up.
@@ -432,7 +624,7 @@ WgradPlan choose_wgrad(int64_t n_rows, int32_t channels, int32_t features) {
   best.most = ranges > 1 ? ranges : 1;
   if (ranges > 0)
     consider(WgradTile::kLarge, ranges, [&](int splits, int per) {
-      return wgrad_time<WgradLarge>(splits, per, channels, features, 8.0, {0.0, 1.6, 0.0, 0.0});
+      return wgrad_time<WgradLarge>(splits, per, channels, features, 8.0, {0.0, 1.42, 0.0, 0.0});
     });
   for (int want = 1; want <= best.most && want <= steps; ++want) {
     consider(WgradTile::kMedium, want, [&](int splits, int per) {
@@ -449,9 +641,14 @@ template <class S>
 int launch_wgrad(WgradParams p, hipStream_t stream) {
   p.f_tiles = (p.F + S::kTF - 1) / S::kTF;
   p.c_tiles = (p.C + S::kTC - 1) / S::kTC;
-  if (!allow_full_lds<linear_wgrad_kernel<S>>()) return -1;
-  return launch_kernel(linear_wgrad_kernel<S>, dim3((unsigned)(p.splits * p.f_tiles * p.c_tiles)),
-                       dim3(S::kWaves * 64), (size_t)S::kStages * S::kStageBytes, stream, p);
+  auto launch = [&](auto kernel) {
+    return launch_kernel(kernel, dim3((unsigned)(p.splits * p.f_tiles * p.c_tiles)), dim3(S::kWaves * 64),
+                         (size_t)S::kStages * S::kStageBytes, stream, p);
+  };
+  if constexpr (std::is_same<S, WgradLarge>::value)
+    return allow_full_lds<linear_wgrad_large_kernel>() ? launch(linear_wgrad_large_kernel) : -1;
+  else
+    return allow_full_lds<linear_wgrad_kernel<S>>() ? launch(linear_wgrad_kernel<S>) : -1;
 }
 
 int check_linear_bwd(int64_t n_rows, int32_t channels, int32_t features) {

@@ -106,6 +106,19 @@ def test_linear_bwd(n, channels, features, plan):
     assert torch.equal(dw.view(torch.int32), dw2.view(torch.int32))
 
 
+@pytest.mark.parametrize("n,channels,features,plan", [
+    (64, 2048, 8192, (256, 1, 1)),           # a range of one step of the largest tiles,
+    (70, 2048, 8192, (256, 1, 2)),           # of two, six rows in the last,
+    (129, 4096, 4096, (256, 1, 3)),          # of three, one row in the last,
+    (191, 2048, 8192, (256, 1, 3)),          # and 63 rows
+    (65, 5504, 2048, (256, 1, 2)),           # ragged channel tile
+])
+def test_short_ranges_of_the_largest_tiles(n, channels, features, plan):
+    """The 256 x 256 kernel fetches two steps ahead, in halves of 32 rows: ranges that end before that,
+    and last steps with rows missing from either half."""
+    test_linear_bwd(n, channels, features, plan)
+
+
 def test_linear_bwd_undoes_the_forward_pairing():
     """<dx, x> = <dW, W> = <y, dy> with y from this library's own forward projection: the three
     GEMMs (forward, dx, dW) agree with each other, not only each with the oracle."""
