@@ -101,6 +101,9 @@ __global__ __launch_bounds__(kThreads, 2) void winattn_dq_kernel(
   // dK/dV kernel, so the separate pass over O and dO is not needed; otherwise it reads them.
   using Tl = Tile<D>;
   constexpr uint32_t kBuf = 2 * Tl::kBytes;   // one buffer: K tile, V tile
+  // us without / with, 60 x 60 windows: head_dim 128 39592 / 38801, 64 10888 / 10721; 30 x 30, head_dim 128
+  // 6997 / 6864; head_dim 32 the same either way
+  constexpr bool kPriority = D >= 64;
   extern __shared__ __align__(16) unsigned char smem[];
   int* tok_grid = reinterpret_cast<int*>(smem);
   const uint32_t table = lds_address(smem);
@@ -261,6 +264,7 @@ __global__ __launch_bounds__(kThreads, 2) void winattn_dq_kernel(
 #pragma unroll
     for (int i = 0; i < 16; ++i) { sacc[i] = 0.f; dpacc[i] = 0.f; }
     sched_fence();
+    product_priority<kPriority>(1);
 #pragma unroll
     for (int kk = 0; kk < kNK; ++kk) {
       sacc = mfma32(ka[kk], qreg[kk], sacc);
@@ -273,6 +277,7 @@ __global__ __launch_bounds__(kThreads, 2) void winattn_dq_kernel(
   };
   auto vector_phase = [&](auto off, int sub_lo) __attribute__((always_inline)) {
     constexpr uint32_t kOff = decltype(off)::value;
+    product_priority<kPriority>(0);
 #pragma unroll
     for (int cb = 0; cb < D / 32; ++cb)
 #pragma unroll
@@ -301,6 +306,7 @@ __global__ __launch_bounds__(kThreads, 2) void winattn_dq_kernel(
                           uint32_t fill_tile, uint32_t en) __attribute__((always_inline)) {
     constexpr bool kFill = decltype(with_fill)::value != 0;
     sched_fence();
+    product_priority<kPriority>(1);
 #pragma unroll
     for (int j = 0; j < kNK; ++j) {
       const int c = j / (D / 32), cb = j % (D / 32);

@@ -478,6 +478,16 @@ __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_sched_barrier(0);
 }
 
+// Priority of this wave while it issues products (1) or vector work (0), for kernels whose two or more
+// waves per SIMD do both in turns: the matrix pipe then never waits behind the other wave's vector work.
+template <bool kOn>
+__device__ __forceinline__ void product_priority(int on) {
+  if constexpr (kOn) {
+    if (on) __builtin_amdgcn_s_setprio(1);
+    else __builtin_amdgcn_s_setprio(0);
+  }
+}
+
 // Nothing is scheduled across this point: pins a hand-made interleaving of
 // products, operand reads and copies.
 __device__ __forceinline__ void sched_fence() { __builtin_amdgcn_sched_barrier(0); }

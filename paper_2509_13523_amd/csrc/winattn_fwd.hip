@@ -31,6 +31,9 @@ __global__ __launch_bounds__(W * 64, W == 4 ? 2 : 1) void winattn_fwd_kernel(
     const bf16_t* __restrict__ v, OutT* __restrict__ o, float* __restrict__ lse) {
   using Tl = Tile<D, W>;
   constexpr uint32_t kBuf = 2 * Tl::kBytes;   // one buffer: K tile, V tile
+  // us without / with: head_dim 64 60 x 60 windows 16091 / 15707, 30 x 30 469 / 462; head_dim 128 60 x 60
+  // 27369 / 27255, but 30 x 30 (four waves) 4986 / 5010; head_dim 32 the same either way
+  constexpr bool kPriority = D == 64 || (D == 128 && W == 8);
   extern __shared__ __align__(16) unsigned char smem[];
   int* tok_grid = reinterpret_cast<int*>(smem);
   const uint32_t table = lds_address(smem);
@@ -132,6 +135,7 @@ __global__ __launch_bounds__(W * 64, W == 4 ? 2 : 1) void winattn_fwd_kernel(
 #pragma unroll
     for (int i = 0; i < 16; ++i) sacc[i] = 0.f;
     sched_fence();
+    product_priority<kPriority>(1);
 #pragma unroll
     for (int kk = 0; kk < D / 16; ++kk) {
       sacc = mfma32(ka[kk], qreg[kk], sacc);
@@ -143,6 +147,7 @@ __global__ __launch_bounds__(W * 64, W == 4 ? 2 : 1) void winattn_fwd_kernel(
     }
   };
   auto softmax_phase = [&](int sub_lo) __attribute__((always_inline)) {
+    product_priority<kPriority>(0);
     if (!rg.mask_free(sub_lo)) {
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
@@ -199,6 +204,7 @@ __global__ __launch_bounds__(W * 64, W == 4 ? 2 : 1) void winattn_fwd_kernel(
     constexpr uint32_t kOff = decltype(k_off)::value;
     constexpr bool kFill = decltype(with_fill)::value != 0;
     sched_fence();
+    product_priority<kPriority>(1);
 #pragma unroll
     for (int j = 0; j < D / 16; ++j) {
       const int c = j / (D / 32), cb = j % (D / 32);
