@@ -602,7 +602,7 @@ def bench_projection_bwd(args):
         "config": {"workload": "qkv_proj_bwd: %d token rows, %d channels, %d features: dx = dy W "
                                "(bf16) and dW = dy^T x (fp32)" % (n, C, F), "kernels": per,
                    "vendor_gemm_same_products": ven},
-        "roofline": {"kernel": "%s (%s)" % ("linear_wgrad_kernel" if slow == "dweight"
+        "roofline": {"kernel": "%s (%s)" % ("linear_wgrad_large_kernel" if slow == "dweight"
                                             else "projection_gemm_kernel", slow), "bound": "mfma",
                      "achieved": achieved, "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
                      "frac": round(achieved / PEAK_BF16_TFLOPS, 4),

@@ -13,7 +13,7 @@
 // reads (ds_read_b64_tr_b16), the token index landing in the registers.  The rows of the whole
 // problem are split over several workgroups per tile; each writes its partial tile, and a second
 // kernel adds the partials in a fixed order (no atomics: the result does not depend on the
-// schedule).  Rows past the end in the last step are cleared in the LDS before they are used.
+// schedule).  Rows past the end in the last step are cleared, in the LDS or in the operands, before use.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
