@@ -197,17 +197,34 @@ def _torch_out_dtype(out_dtype):
     return torch.float32 if out_dtype == AERIS_DT_F32 else torch.bfloat16
 
 
+def _empty_rows(q, out_dtype):
+    """A buffer like the contiguous bf16 tensor q, in the output type (the shape and device are parsed
+    again only where the type differs)."""
+    import torch
+    if out_dtype == AERIS_DT_F32:
+        return torch.empty(q.shape, dtype=torch.float32, device=q.device)
+    return torch.empty_like(q)
+
+
+def _check_qkv(q, k, v):
+    import torch
+    bf16, shape = torch.bfloat16, q.shape
+    for t in (q, k, v):
+        assert t.is_cuda and t.dtype == bf16 and t.is_contiguous()
+    assert k.shape == shape and v.shape == shape
+    return shape
+
+
 def aeris_winattn_fwd(q, k, v, win, shift, mask=AERIS_MASK_NONE, scale=None,
                       out_dtype=AERIS_DT_BF16, o=None, lse=None):
     """q, k, v: contiguous torch.bfloat16 device tensors [B,H,W,heads,d].
     Returns (o, lse); buffers are allocated with torch unless passed in."""
     import torch
-    B, H, W, nh, d = q.shape
-    for t in (q, k, v):
-        assert t.is_cuda and t.dtype == torch.bfloat16 and t.is_contiguous() and t.shape == q.shape
-    p = make_params(q.shape, win, shift, mask, scale, out_dtype)
+    shape = _check_qkv(q, k, v)
+    B, H, W, nh, d = shape
+    p = make_params(shape, win, shift, mask, scale, out_dtype)
     if o is None:
-        o = torch.empty(q.shape, dtype=_torch_out_dtype(out_dtype), device=q.device)
+        o = _empty_rows(q, out_dtype)
     if lse is None:
         lse = torch.empty((B, nh, H, W), dtype=torch.float32, device=q.device)
     rc = load().aeris_winattn_fwd(ctypes.byref(p), q.data_ptr(), k.data_ptr(), v.data_ptr(),
@@ -309,13 +326,12 @@ def aeris_winattn_rope_fwd(q, k, v, win, shift, base, positions, mask=AERIS_MASK
     """Attention on rotated queries and keys.  Returns (o, lse), or (o, lse, workspace) with
     return_saved: the workspace then holds the rotated k and q for aeris_winattn_rope_bwd."""
     import torch
-    B, H, W, nh, d = q.shape
-    for t in (q, k, v):
-        assert t.is_cuda and t.dtype == torch.bfloat16 and t.is_contiguous() and t.shape == q.shape
-    p = make_params(q.shape, win, shift, mask, scale, out_dtype)
+    shape = _check_qkv(q, k, v)
+    B, H, W, nh, d = shape
+    p = make_params(shape, win, shift, mask, scale, out_dtype)
     r = aeris_rope_params(float(base), int(positions))
     if o is None:
-        o = torch.empty(q.shape, dtype=_torch_out_dtype(out_dtype), device=q.device)
+        o = _empty_rows(q, out_dtype)
     if lse is None:
         lse = torch.empty((B, nh, H, W), dtype=torch.float32, device=q.device)
     need = aeris_winattn_rope_fwd_workspace_bytes(p)
