@@ -93,6 +93,10 @@ __device__ __forceinline__ void wgrad_tile(const WgradParams& p, int piece, int&
   ft = 4 * band + r - ct * height;
 }
 
+// The two smaller shapes.  Bound by the latency of a step (copies, barrier, first operand reads), which the
+// CU's other workgroups cover in part.  Against a loop with offsets worked out per step and the compiler's
+// order, us: 20011 rows 768 -> 2304 82.1 -> 76.6, 20000 x 2048 -> 2048 167.9 -> 158.5, 2000 x 1024 -> 1024
+// 14.0 -> 11.6, 1728 x 128 -> 1024 10.4 -> 9.6.
 template <class S>
 __global__ __launch_bounds__(S::kWaves * 64, S::kWaves * S::kPerCu / 4) void linear_wgrad_kernel(
     WgradParams p) {
@@ -214,68 +218,79 @@ __global__ __launch_bounds__(S::kWaves * 64, S::kWaves * S::kPerCu / 4) void lin
   }
 
   bf16x8 ao[2][FB], bo[2][CB];
-  auto fetch = [&](int set, int kk, uint32_t stage_off) __attribute__((always_inline)) {
-    const uint32_t off = stage_off + kk * (16 * S::kWidth * 2);
+  auto fetch_a = [&](int set, int kk, uint32_t from) __attribute__((always_inline)) {
+    const uint32_t off = from + kk * (16 * S::kWidth * 2);
 #pragma unroll
     for (int a = 0; a < FB; ++a) ao[set][a] = Sub::read_tr(ta[a][0] + off, ta[a][1] + off);
+  };
+  auto fetch_b = [&](int set, int kk, uint32_t from) __attribute__((always_inline)) {
+    const uint32_t off = from + kk * (16 * S::kWidth * 2);
 #pragma unroll
     for (int b = 0; b < CB; ++b) bo[set][b] = Sub::read_tr(tb[b][0] + off, tb[b][1] + off);
   };
 
-  uint32_t stage_off = 0;
-  uint32_t fill_off = (S::kStages - 1) * S::kStageBytes;
-  auto run_step = [&](auto near_end, int ks) __attribute__((always_inline)) {
-    constexpr bool kNearEnd = decltype(near_end)::value != 0;
+  // The copies of a last step with rows missing are issued kStages - 1 steps ahead of it, and only from
+  // there on do steps look for it.
+  const int plain_end = p.tail && s1 == p.steps_total ? s1 - S::kStages : s1;
+  // One step, in stage `slot`: LDS offsets are immediates, and products, reads and copies keep this order.
+  auto run_step = [&](auto slot, int ks) __attribute__((always_inline)) {
+    constexpr int kSlot = decltype(slot)::value;
+    constexpr uint32_t kHere = kSlot * S::kStageBytes;
+    constexpr uint32_t kFill = (kSlot + S::kStages - 1) % S::kStages * S::kStageBytes;
     // this stage's copies are the oldest in flight; those of the kStages - 2 steps behind it, if
     // there are that many, may stay in flight
     if (S::kStages > 2 && ks + S::kStages - 2 < s1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((S::kStages - 2) * kP) : "memory");
     else wait_async_loads();
     __syncthreads();               // this stage has landed; every reader of the one filled next is done
-    if (kNearEnd && p.tail && ks == p.steps_total - 1) {   // clear the rows past the end, once
-      const int clear = (kTM - p.tail) * kChunks;      // 16-byte chunks per sub-tile
-      for (int t = 0; t < S::kFSubs + S::kCSubs; ++t)
-        for (int i = tid; i < clear; i += S::kWaves * 64)
-          *reinterpret_cast<u32x4*>(smem + stage_off + t * S::kSubBytes +
-                                    (p.tail * kChunks + i) * 16) = u32x4{0, 0, 0, 0};
-      __syncthreads();
-    }
     const int next = ks + S::kStages - 1;
     const uint32_t more = next < s1;
-    if (kNearEnd && more) clamp_rows(next);
-    fetch(0, 0, stage_off);
+    if (ks >= plain_end) {
+      if (p.tail && ks == p.steps_total - 1) {           // clear the rows past the end, once
+        const int clear = (kTM - p.tail) * kChunks;      // 16-byte chunks per sub-tile
+        for (int t = 0; t < S::kFSubs + S::kCSubs; ++t)
+          for (int i = tid; i < clear; i += S::kWaves * 64)
+            *reinterpret_cast<u32x4*>(smem + kHere + t * S::kSubBytes +
+                                      (p.tail * kChunks + i) * 16) = u32x4{0, 0, 0, 0};
+        __syncthreads();
+      }
+      if (more) clamp_rows(next);
+    }
+    fetch_a(0, 0, kHere);
+    fetch_b(0, 0, kHere);
     sched_fence();
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) {
-      if (kk < 3) fetch((kk + 1) & 1, kk + 1, stage_off);
 #pragma unroll
-      for (int a = 0; a < FB; ++a)
+      for (int q = 0; q < FB * CB; ++q) {
+        const int a = q / CB, b = q % CB;
+        acc[a][b] = mfma32(ao[kk & 1][a], bo[kk & 1][b], acc[a][b]);
+        if (kk < 3 && q == 0) fetch_a((kk + 1) & 1, kk + 1, kHere);
+        if (kk < 3 && q == (FB * CB == 1 ? 0 : 1)) fetch_b((kk + 1) & 1, kk + 1, kHere);
+        // the copies of a later stage ride in the first half of the step, spread evenly
+        constexpr int kHalf = 2 * FB * CB;
+        const int n = kk * FB * CB + q;
+        if (n < kHalf) {
 #pragma unroll
-        for (int b = 0; b < CB; ++b) {
-          acc[a][b] = mfma32(ao[kk & 1][a], bo[kk & 1][b], acc[a][b]);
-          // the copies of a later stage ride in the first half of the step, spread evenly
-          constexpr int kHalf = 2 * FB * CB;
-          const int n = (kk * FB + a) * CB + b;
-          if (n < kHalf) {
-#pragma unroll
-            for (int i = n * kP / kHalf; i < (n + 1) * kP / kHalf; ++i)
-              copy_piece(i, lds0 + fill_off, more);
-          }
+          for (int i = n * kP / kHalf; i < (n + 1) * kP / kHalf; ++i) copy_piece(i, lds0 + kFill, more);
         }
-      sched_fence();
+        sched_fence();
+      }
     }
     if (S::kRun != 0 && ((ks - s0) & (S::kRun - 1)) == S::kRun - 1) add_run();
-    stage_off = stage_off == (S::kStages - 1) * S::kStageBytes ? 0 : stage_off + S::kStageBytes;
-    fill_off = fill_off == (S::kStages - 1) * S::kStageBytes ? 0 : fill_off + S::kStageBytes;
     dy_at += dy_step;
     x_at += x_step;
   };
-  // The copies of a last step with rows missing are issued kStages - 1 steps ahead of it, and only from
-  // there on do steps look for it: looked for in every step it cost, with 64-bit products for the
-  // addresses, 1 to 2 % (172800 x 2048 -> 6144 3858 us, now 3825; 1728 x 128 -> 384 10.4, now 10.2).
-  const int plain_end = p.tail && s1 == p.steps_total ? s1 - S::kStages : s1;
-  int ks = s0;
-  for (; ks < plain_end; ++ks) run_step(Const<0>{}, ks);
-  for (; ks < s1; ++ks) run_step(Const<1>{}, ks);
+  static_assert(S::kStages == 2 || S::kStages == 3);
+  for (int ks = s0;;) {
+    run_step(Const<0>{}, ks);
+    if (++ks == s1) break;
+    run_step(Const<1>{}, ks);
+    if (++ks == s1) break;
+    if constexpr (S::kStages == 3) {
+      run_step(Const<2>{}, ks);
+      if (++ks == s1) break;
+    }
+  }
 
   add_run();
   // ---- partial tile: a lane owns one channel column, a register one feature row
