@@ -32,11 +32,24 @@ __host__ __device__ inline int short_rows(int T) { return (T + 31) & ~31; }
 // Units of 16 keys.
 __host__ __device__ inline int short_units(int T) { return (T + 15) >> 4; }
 
-// Q, dO, K | two strips of dS, [keys][32 queries] | LSE * log2(e), delta | token table
+// Q, dO, K | two strips of dS, [keys][32 queries] | LSE * log2(e), delta | token table.  Strips are read in
+// whole blocks of 32 keys: where keys end in the middle of one, a read of the second strip runs on into what
+// lies behind it (and is cleared in the register), which for 33 to 48 tokens is shorter than that.
 constexpr size_t short_smem_bytes(int T, int D) {
-  const int rows = (T + 31) & ~31, keys = (T + 15) & ~15;
-  return 3 * (size_t)rows * D * 2 + 2 * (size_t)keys * 64 + 3 * (size_t)rows * 4;
+  const size_t rows = (T + 31) & ~31, keys = (T + 15) & ~15;
+  const size_t arrays = 2 * keys * 64 + 3 * rows * 4, read = (keys + rows) * 64;
+  return 3 * rows * D * 2 + (arrays > read ? arrays : read);
 }
+// The last byte that a block of the second strip reads, as the kernel forms its addresses.
+constexpr bool short_strip_reads_fit(int D) {
+  for (int T = 1; T <= 192; ++T) {
+    const size_t rows = (T + 31) & ~31, units = (T + 15) >> 4, n_blocks = rows >> 5;
+    const size_t second = 3 * rows * D * 2 + units * 16 * 64;
+    if (second + (n_blocks - 1) * (32 * 64) + 32 * 64 > short_smem_bytes(T, D)) return false;
+  }
+  return true;
+}
+static_assert(short_strip_reads_fit(32) && short_strip_reads_fit(64) && short_strip_reads_fit(128));
 
 // Waves a SIMD must hold (beside what the LDS allows).
 template <int D, int NU>
