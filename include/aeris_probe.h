@@ -7,6 +7,8 @@
 
 #include <stdint.h>
 
+#include "aeris_winattn.h"
+
 #ifdef __cplusplus
 extern "C" {
 #endif
@@ -22,6 +24,16 @@ extern "C" {
  */
 int aeris_mfma_loop_probe(int32_t blocks, int32_t iters, int32_t random_operands, float* sink,
                           void* hip_stream);
+
+/*
+ * How attention calls run a parameter block they accept (else its error code), with n_windows listed
+ * windows, or all of them (0).  *forward: the workgroups that share the queries of a (batch, window, head)
+ * whose keys and values each holds whole; 0: tiles of 128 or 256 queries with streamed keys.  *backward:
+ * 0: one kernel makes dQ, dK and dV of a window and head; else a dQ kernel and one for dK and dV, which is
+ * 1: the generic one, operands read first, 2: the same, operands read one block of products ahead, 3: the
+ * software-pipelined one.  Launches nothing.
+ */
+int aeris_winattn_plan(const aeris_winattn_params* p, int32_t n_windows, int32_t* forward, int32_t* backward);
 
 /*
  * How the projections (aeris_linear_fwd; with several samples aeris_norm_linear_fwd, gated != 0

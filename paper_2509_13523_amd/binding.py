@@ -20,7 +20,7 @@ EXPORTS = ("aeris_winattn_fwd", "aeris_winattn_bwd", "aeris_winattn_bwd_stages",
            "aeris_winattn_bwd_workspace_bytes", "aeris_winattn_bwd_static",
            "aeris_winattn_validate", "aeris_winattn_strerror", "aeris_winattn_version",
            "aeris_winattn_fwd_windows", "aeris_winattn_bwd_windows",
-           "aeris_mfma_loop_probe", "aeris_projection_plan", "aeris_linear_bwd_plan",
+           "aeris_mfma_loop_probe", "aeris_winattn_plan", "aeris_projection_plan", "aeris_linear_bwd_plan",
            "aeris_rope2d_apply", "aeris_winattn_rope_fwd_workspace_bytes",
            "aeris_winattn_rope_bwd_workspace_bytes", "aeris_winattn_rope_fwd",
            "aeris_winattn_rope_bwd", "aeris_winattn_rope_fwd_windows",
@@ -96,6 +96,8 @@ def load():
     lib.aeris_mfma_loop_probe.argtypes = [ctypes.c_int32, ctypes.c_int32, ctypes.c_int32, vp, vp]
     lib.aeris_mfma_loop_probe.restype = ctypes.c_int
     pi32 = ctypes.POINTER(ctypes.c_int32)
+    lib.aeris_winattn_plan.argtypes = [P, ctypes.c_int32, pi32, pi32]
+    lib.aeris_winattn_plan.restype = ctypes.c_int
     lib.aeris_projection_plan.argtypes = [ctypes.c_int64, ctypes.c_int64, ctypes.c_int32, ctypes.c_int32,
                                           ctypes.c_int32, pi32, pi32]
     lib.aeris_projection_plan.restype = ctypes.c_int
@@ -455,6 +457,16 @@ def aeris_winattn_rope_bwd_windows(q, k, v, o, lse, d_o, win, shift, base, posit
     if rc != 0:
         raise AerisError(rc, "aeris_winattn_rope_bwd_windows")
     return dq, dk, dv
+
+
+def aeris_winattn_plan(p, n_windows=0):
+    """(workgroups that share a window and head of the one-pass forward kernel, 0: streamed tiles; 0: the
+    one-kernel backward, 1 to 3: which dK/dV kernel) of a parameter block, all windows or n_windows listed."""
+    out = [ctypes.c_int32() for _ in range(2)]
+    rc = load().aeris_winattn_plan(ctypes.byref(p), n_windows, *[ctypes.byref(v) for v in out])
+    if rc != 0:
+        raise AerisError(rc, "aeris_winattn_plan")
+    return out[0].value, out[1].value
 
 
 def aeris_projection_plan(n_rows, rows_per_sample, channels, features, gated=False):

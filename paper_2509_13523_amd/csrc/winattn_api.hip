@@ -412,6 +412,22 @@ int aeris_winattn_rope_bwd_windows(const aeris_winattn_params* p, const aeris_ro
                        workspace, workspace_bytes, hip_stream);
 }
 
+int aeris_winattn_plan(const aeris_winattn_params* p, int32_t n_windows, int32_t* forward, int32_t* backward) {
+  Strides s;
+  const int rc = resolve(p, &s);
+  if (rc != AERIS_OK) return rc;
+  if (!forward || !backward) return AERIS_ERR_NULL_POINTER;
+  aeris::KParams kp = derive(p, s);
+  if (n_windows < 0 || n_windows > kp.n_win) return AERIS_ERR_INVALID_SHAPE;
+  if (n_windows > 0) {
+    kp.n_win = n_windows;
+    kp.n_pairs = kp.B * kp.n_win * kp.nh;
+  }
+  *forward = aeris::short_forward(kp, p->head_dim) ? aeris::short_forward_workgroups(kp) : 0;
+  *backward = aeris::short_backward(kp, p->head_dim) ? 0 : static_cast<int>(aeris::dkdv_kernel(kp, p->head_dim));
+  return AERIS_OK;
+}
+
 int aeris_mfma_loop_probe(int32_t blocks, int32_t iters, int32_t random_operands, float* sink,
                           void* hip_stream) {
   if (!sink) return AERIS_ERR_NULL_POINTER;

@@ -666,6 +666,12 @@ constexpr size_t kLdsOfCu = 160 * 1024;
 // 195 / 221 / 294 / 796 -> 159 / 165 / 127 / 187 / 205 / 270 / 750) and is not built for it.
 constexpr int kLeanAboveBlocks = 768;
 
+DkDv dkdv_kernel(const KParams& kp, int head_dim) {
+  if (head_dim == 128) return 2 * dkdv_smem_bytes<128>(kp.T) > kLdsOfCu ? DkDv::kPipelined : DkDv::kLean;
+  if (head_dim == 32 && (grid_blocks(kp) > kLeanAboveBlocks || kp.T <= kStream)) return DkDv::kLean;
+  return DkDv::kReadFirst;
+}
+
 template <int D, typename OutT>
 static int launch_bwd_t(KParams kp, const void* q, const void* k, const void* v,
                         const void* o, const float* lse, const void* d_o, void* dq, void* dk,
@@ -703,8 +709,9 @@ static int launch_bwd_t(KParams kp, const void* q, const void* k, const void* v,
   }
   if (stages & 4u) {
     kp.n_whole = whole_windows(kp, AttnKernel::kDkDv, D);
+    const DkDv kernel = dkdv_kernel(kp, D);
     if constexpr (D == 128) {
-      if (2 * dkdv_smem_bytes<D>(kp.T) > kLdsOfCu)
+      if (kernel == DkDv::kPipelined)
         return launch_dkdv_pipe128(kp, std::is_same<OutT, float>::value, q, k, v, d_o, delta, lse2,
                                    dk, dv, stream);
     }
@@ -718,7 +725,7 @@ static int launch_bwd_t(KParams kp, const void* q, const void* k, const void* v,
                            static_cast<OutT*>(dv));
     };
     if constexpr (D == 32) {
-      return n_blocks > kLeanAboveBlocks || kp.T <= kStream ? launch(Const<1>{}) : launch(Const<0>{});
+      return kernel == DkDv::kLean ? launch(Const<1>{}) : launch(Const<0>{});
     } else {
       return launch(Const<(D == 128)>{});
     }

@@ -1,5 +1,6 @@
-// Forward attention of short windows: one workgroup owns a whole (batch, window, head) (same contract as
-// launch_fwd).
+// Forward attention of short windows: a workgroup holds the keys and values of a whole (batch, window,
+// head); its queries are its own, or where there are few windows and heads dealt to two or three workgroups
+// (same contract as launch_fwd).
 //
 // Bound by memory and its latency.  K and V go to the LDS at once, queries to registers, and nothing is
 // streamed: a wave computes the logits of 16 queries with every key (v_mfma_f32_16x16x32_bf16, a lane has
@@ -25,8 +26,10 @@ __device__ __forceinline__ float row_pair_max(float x) {   // over lanes l, l ^ 
   return fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
 }
 
-// NB: blocks of 32 keys
-template <int D, int NB, typename OutT>
+// NB: blocks of 32 keys.  kShared: p.n_tiles workgroups share a window and head (a build of its own: with the
+// division of work in scalar registers the other is up to 6 % slower, 81 tokens, head_dim 64, 4096 windows and
+// heads 32.2 -> 33.8 us, 96 tokens 34.2 -> 36.4).
+template <int D, int NB, typename OutT, bool kShared>
 __global__ __launch_bounds__(256, 2) void winattn_fwd_short_kernel(
     KParams p, const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const bf16_t* __restrict__ v,
     OutT* __restrict__ o, float* __restrict__ lse) {
@@ -42,6 +45,8 @@ __global__ __launch_bounds__(256, 2) void winattn_fwd_short_kernel(
 
   int pair, tile;
   if (!block_to_work(p, pair, tile)) return;
+  // units of 16 queries are dealt to the waves of all workgroups of the pair in turn
+  const int unit0 = kShared ? tile * W + wave : wave, unit_step = kShared ? p.n_tiles * W : W;
   Window win;
   if (!win.init(p, pair)) return;
   const uint32_t k_at = lds_address(smem), v_at = k_at + kArrayBytes, table = v_at + kArrayBytes;
@@ -81,7 +86,7 @@ __global__ __launch_bounds__(256, 2) void winattn_fwd_short_kernel(
   unsigned own[kUnits];
 #pragma unroll
   for (int i = 0; i < kUnits; ++i) {
-    const int t = (wave + W * i) * 16 + li;
+    const int t = (unit0 + unit_step * i) * 16 + li;
     own[i] = grid_of(t < p.T ? t : p.T - 1);
     const bf16_t* row = q + q_base + (long long)own[i] * p.q_tok + 8 * g;
 #pragma unroll
@@ -102,7 +107,7 @@ __global__ __launch_bounds__(256, 2) void winattn_fwd_short_kernel(
     int lo[N], hi[N], lo_max[N], hi_min[N];               // visible keys: of the lane, of all its unit's queries
 #pragma unroll
     for (int u = 0; u < N; ++u) {
-      const int i = kFrom + u, first = (wave + W * i) * 16, last = first + 15, t = first + li;
+      const int i = kFrom + u, first = (unit0 + unit_step * i) * 16, last = first + 15, t = first + li;
       if (p.rope) {   // rotary embedding of the queries
         float p_lat, p_lon;
         rope_position(p, own[i], p_lat, p_lon);
@@ -191,7 +196,7 @@ __global__ __launch_bounds__(256, 2) void winattn_fwd_short_kernel(
 #pragma unroll
     for (int u = 0; u < N; ++u) {
       const int i = kFrom + u;
-      if ((wave + W * i) * 16 + li < p.T) {
+      if ((unit0 + unit_step * i) * 16 + li < p.T) {
         const float inv = 1.f / l[u];
         OutT* row = o + ((long long)win.b * plane + own[i]) * p.o_tok + (long long)win.head * p.o_head;
 #pragma unroll
@@ -210,41 +215,67 @@ __global__ __launch_bounds__(256, 2) void winattn_fwd_short_kernel(
     }
   };
   const int units = (p.T + 15) >> 4;
+  if (kShared && unit0 >= units) return;
   if constexpr (kPairs) {
-    if (wave + W < units) attend(Const<0>{}, Const<2>{});
+    if (unit0 + unit_step < units) attend(Const<0>{}, Const<2>{});
     else attend(Const<0>{}, Const<1>{});
   } else {
     attend(Const<0>{}, Const<1>{});
     if constexpr (kUnits >= 2) {
-      if (wave + W < units) attend(Const<1>{}, Const<1>{});
+      if (unit0 + unit_step < units) attend(Const<1>{}, Const<1>{});
     }
     if constexpr (kUnits >= 3) {
-      if (wave + 2 * W < units) attend(Const<2>{}, Const<1>{});
+      if (unit0 + 2 * unit_step < units) attend(Const<2>{}, Const<1>{});
     }
   }
+}
+
+// Workgroups that share the queries of a window and head: as many as leave each wave one unit of 16, while
+// one for each would leave a part of the 256 CUs without work (from 161 tokens on, three units per wave, also
+// at twice that).  Every workgroup loads all keys and values.  The waves do for a unit what they do alone.
+// us, streamed tiles / one workgroup / as here, 2 heads:
+//   windows x heads            32                   128                   256                   512
+//   head_dim 32,  96 tokens   6.1 / 4.9 / 3.8      6.2 / 5.1 / 4.1      6.4 / 5.3 / 4.7      7.5 /  6.2
+//                144          7.6 / 8.0 / 4.8      7.7 / 8.1 / 5.5      9.3 / 8.4 / 6.5     13.0 /  9.9
+//                192          7.2 / 8.4 / 4.8      7.4 / 8.7 / 5.8      8.7 / 9.0 / 7.0     12.0 / 11.1 / 10.5
+//   head_dim 64, 144          8.8 / 8.9 / 5.4      8.9 / 9.0 / 6.3     11.4 / 9.5 / 7.6     16.1 / 12.5
+//                192          8.5 / 9.6 / 5.4      8.8 / 9.8 / 6.6     10.3 / 10.3 / 8.3    16.0 / 16.9 / 15.2
+//   head_dim 128, 128         9.1 / 7.7 / 5.9      9.5 / 8.1 / 6.5     10.7 / 9.2 / 8.8     17.0 / 16.6
+// At twice the limits: 96 tokens 512 6.2 -> 6.5, 144 tokens head_dim 64 512 12.5 -> 12.9, 192 tokens head_dim
+// 32 1024 17.2 -> 17.2, 64 27.6 -> 26.2 but 176 tokens 768 13.9 -> 14.7.
+int short_forward_workgroups(const KParams& kp) {
+  const int units = (kp.T + 15) / 16;
+  return kp.n_pairs <= (units > 10 ? 512 : 256) ? (units + 3) / 4 : 1;
 }
 
 template <int D, int NB, typename OutT>
 static int launch_fwd_short_t(KParams kp, const void* q, const void* k, const void* v, void* o, float* lse,
                               hipStream_t stream) {
-  kp.n_tiles = 1;
+  kp.n_tiles = short_forward_workgroups(kp);
   kp.n_whole = whole_windows(kp, AttnKernel::kForward, D);
   const int units = (kp.T + 15) / 16;
-  if (!allow_full_lds<winattn_fwd_short_kernel<D, NB, OutT>>()) return -1;
-  return launch_kernel(winattn_fwd_short_kernel<D, NB, OutT>, dim3(grid_blocks(kp)), dim3((units < 4 ? units : 4) * 64),
-                       fwd_short_smem_bytes(NB, D), stream, kp, static_cast<const bf16_t*>(q),
-                       static_cast<const bf16_t*>(k), static_cast<const bf16_t*>(v), static_cast<OutT*>(o), lse);
+  auto launch = [&](auto shared) {
+    constexpr bool kShared = decltype(shared)::value != 0;
+    if (!allow_full_lds<winattn_fwd_short_kernel<D, NB, OutT, kShared>>()) return -1;
+    return launch_kernel(winattn_fwd_short_kernel<D, NB, OutT, kShared>, dim3(grid_blocks(kp)),
+                         dim3((units < 4 ? units : 4) * 64), fwd_short_smem_bytes(NB, D), stream, kp,
+                         static_cast<const bf16_t*>(q), static_cast<const bf16_t*>(k),
+                         static_cast<const bf16_t*>(v), static_cast<OutT*>(o), lse);
+  };
+  if constexpr (NB >= 3) {
+    if (kp.n_tiles > 1) return launch(Const<1>{});
+  }
+  return launch(Const<0>{});
 }
 
 // Windows of up to 192 tokens that leave room for a second workgroup in a CU's LDS (128 tokens at head_dim
 // 128); above, 196 tokens at head_dim 32 take as long either way.  At head_dim 64 windows of 97 to 128
 // tokens fill the streamed kernel's tile of 128 queries, which reads an operand for 32 queries where this
-// reads it for 16: 121 tokens 45.4 / 48.6 us, 128 tokens 43.9 / 46.1.  From 161 tokens on, grids of fewer
-// windows and heads than CUs have two streamed workgroups for each of them (160 at head_dim 32, 192 tokens
-// 8.4 / 9.1 us; 120 at 144 tokens 8.0 / 8.0).
+// reads it for 16: 121 tokens 45.4 / 48.6 us, 128 tokens 43.9 / 46.1.  By window and head_dim alone: a window
+// has the same bits in every grid, batch and list of windows.
 bool short_forward(const KParams& kp, int head_dim) {
   const int blocks = (kp.T + 31) / 32;
-  if ((head_dim == 64 && blocks == 4) || (blocks == 6 && kp.n_pairs < 256)) return false;
+  if (head_dim == 64 && blocks == 4) return false;
   return blocks <= 6 && 2 * fwd_short_smem_bytes(blocks, head_dim) <= 160 * 1024;
 }
 

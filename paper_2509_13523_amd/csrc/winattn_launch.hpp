@@ -49,10 +49,12 @@ inline int launch_kernel(void (*kern)(Params...), dim3 grid, dim3 block, size_t 
 int launch_fwd(const KParams& kp, int head_dim, bool out_f32, const void* q, const void* k,
                const void* v, void* o, float* lse, hipStream_t stream);
 
-// The same for windows that one workgroup can hold, and whether that is the way to run a problem.
+// The same for windows that one workgroup can hold, whether that is the way to run a problem, and then the
+// workgroups that share a window and head.
 int launch_fwd_short(const KParams& kp, int head_dim, bool out_f32, const void* q, const void* k,
                      const void* v, void* o, float* lse, hipStream_t stream);
 bool short_forward(const KParams& kp, int head_dim);
+int short_forward_workgroups(const KParams& kp);
 
 int launch_bwd(const KParams& kp, int head_dim, bool out_f32, const void* q, const void* k,
                const void* v, const void* o, const float* lse, const void* d_o, void* dq,
@@ -70,6 +72,11 @@ int launch_bwd_short(const KParams& kp, int head_dim, bool out_f32, const void* 
                      const void* v, const void* o, const float* lse, const void* d_o, float* delta,
                      float* lse2, void* dq, void* dk, void* dv, hipStream_t stream);
 bool short_backward(const KParams& kp, int head_dim);
+
+// What makes dK and dV where that is not: the generic kernel with all operands read first, or read one block
+// of products ahead, or the software-pipelined kernel of head_dim 128.
+enum class DkDv { kReadFirst = 1, kLean = 2, kPipelined = 3 };
+DkDv dkdv_kernel(const KParams& kp, int head_dim);
 
 // y = rotary embedding of x (inverse: the rotation by the negated angles); both
 // [B, H, W, heads, head_dim] bf16 with the given element strides.  Uses kp.rope_pos, kp.rope_c.

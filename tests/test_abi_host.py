@@ -337,3 +337,21 @@ def test_stream_handle_with_and_without_the_raw_accessor(monkeypatch):
     assert B._stream() == 103
     monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream")
     assert B._stream() == 11
+
+
+def test_attention_kernels_depend_on_window_and_head_dim_alone():
+    """A window and head is computed with the same arithmetic, so to the same bits, in every grid, batch and
+    list of windows; the workgroups that share its queries and the order of dK/dV's reads may follow the grid."""
+    for d in (32, 64, 128):
+        for tokens in range(1, 257):
+            seen = set()
+            for nb, ny, nx, heads, listed in ((1, 1, 1, 1, 0), (1, 4, 8, 3, 0), (3, 16, 32, 16, 0), (3, 16, 32, 16, 5)):
+                p = B.make_params((nb, ny, tokens * nx, heads, d), (1, tokens), (0, 0), B.AERIS_MASK_SWIN)
+                fwd, bwd = B.aeris_winattn_plan(p, listed)
+                assert fwd <= 3
+                seen.add((fwd > 0, bwd > 0))
+            assert len(seen) == 1, (d, tokens, seen)
+    p = B.make_params((1, 12, 24, 2, 64), (12, 12), (0, 0), B.AERIS_MASK_SWIN)
+    for n in (-1, 3):
+        with pytest.raises(B.AerisError):
+            B.aeris_winattn_plan(p, n)

@@ -77,6 +77,40 @@ def test_full_list_equals_plain_call_bitwise():
         assert torch.equal(a, b)
 
 
+@pytest.mark.parametrize("win,d", [((9, 9), 32), ((8, 16), 128), ((10, 13), 64), ((12, 12), 32), ((7, 23), 64),
+                                   ((11, 16), 32), ((11, 16), 64), ((12, 16), 32), ((12, 16), 64)])
+@pytest.mark.parametrize("out", [B.AERIS_DT_BF16, B.AERIS_DT_F32])
+def test_share_of_short_windows_equals_whole_bitwise(win, d, out):
+    """640 windows and heads, each the work of one forward workgroup, and a share of 80, whose queries two or
+    three workgroups share: the same bits, and those of the oracle."""
+    nh, mask = 5, B.AERIS_MASK_SWIN
+    H, W, shift = win[0] * 8, win[1] * 16, (win[0] // 2, win[1] // 3)
+    shape = (1, H, W, nh, d)
+    picks = list(range(3, 128, 8))
+    p = B.make_params(shape, win, shift, mask, None, out)
+    units = (win[0] * win[1] + 15) // 16
+    assert B.aeris_winattn_plan(p)[0] == 1 and B.aeris_winattn_plan(p, len(picks))[0] == (units + 3) // 4 > 1
+    bits = synth.make_inputs("normal", 6100, shape, 4)
+    q64, k64, v64, do64 = [synth.bf16_bits_to_f64(b) for b in bits]
+    tq, tk, tv, tdo = [to_dev(b) for b in bits]
+    o, lse = B.aeris_winattn_fwd(tq, tk, tv, win, shift, mask, out_dtype=out)
+    grads = B.aeris_winattn_bwd(tq, tk, tv, o, lse, tdo, win, shift, mask, out_dtype=out)
+    lst = torch.tensor(picks, dtype=torch.int32, device="cuda")
+    o2, lse2 = torch.full_like(o, float("nan")), torch.full_like(lse, float("nan"))
+    B.aeris_winattn_fwd_windows(tq, tk, tv, win, shift, lst, o2, lse2, mask, out_dtype=out)
+    grads2 = [torch.full_like(g, float("nan")) for g in grads]
+    B.aeris_winattn_bwd_windows(tq, tk, tv, o2, lse2, tdo, win, shift, lst, *grads2, mask=mask, out_dtype=out)
+    torch.cuda.synchronize()
+    inside = torch.from_numpy(window_token_mask(H, W, win, shift, picks)).cuda()
+    assert torch.equal(o[:, inside], o2[:, inside]) and torch.isnan(o2[:, ~inside]).all()
+    assert torch.equal(lse[:, :, inside], lse2[:, :, inside]) and torch.isnan(lse2[:, :, ~inside]).all()
+    for a, b in zip(grads, grads2):
+        assert torch.equal(a[:, inside], b[:, inside]) and torch.isnan(b[:, ~inside]).all()
+    o_ref, lse_ref = orc.winattn_fwd(q64, k64, v64, win, shift, mask)
+    check("o", o, o_ref, out == B.AERIS_DT_BF16)
+    assert np.abs(to_f64(lse) - lse_ref).max() <= LSE_ABS
+
+
 @pytest.mark.parametrize("mode", [B.AERIS_ROPE_POS_WINDOW, B.AERIS_ROPE_POS_GRID])
 def test_rotary_attention_on_a_window_subset(mode):
     """A rank's share with the rotary embedding: inside the listed windows the result matches the
