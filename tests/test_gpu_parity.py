@@ -276,6 +276,46 @@ def test_short_windows_by_size(win, d):
         assert np.linalg.norm(a - b) <= 3e-3 * max(np.linalg.norm(b), 1e-3 * np.sqrt(b.size))
 
 
+@pytest.mark.parametrize("value", [float("inf"), float("nan")])
+@pytest.mark.parametrize("win,shift,d,clean,poisoned", [
+    ((9, 16), 3, 32, 96, 128),     # regions of 96 and 48 tokens: a window and head whole in a workgroup
+    ((9, 16), 3, 64, 96, 128),
+    ((12, 16), 6, 32, 96, 128),    # 96 and 96
+    ((12, 16), 6, 64, 96, 128),    # forward whole, backward streamed
+    ((8, 16), 4, 32, 64, 64),      # 64 and 64
+    ((8, 16), 4, 64, 64, 64),      # forward streamed, backward whole
+    ((8, 16), 4, 128, 64, 64),     # forward whole, backward streamed
+    ((4, 16), 2, 128, 32, 32),     # 32 and 32
+    ((16, 16), 8, 64, 128, 128),   # streamed
+    ((16, 16), 8, 128, 128, 128),
+])
+def test_nonfinite_tokens_do_not_reach_other_mask_regions(win, shift, d, clean, poisoned, value):
+    """Masked pairs of tokens are left out in blocks, not multiplied by zero: tokens from `poisoned` on that
+    are not finite change nothing for the first `clean` tokens of their window, which another mask region
+    holds (the two share no block), and nothing in other windows."""
+    nh, mask, shift = 3, B.AERIS_MASK_LAT, (shift, 0)
+    H, W = 2 * win[0], 3 * win[1]
+    shape = (1, H, W, nh, d)
+    good = [to_dev(b) for b in synth.make_inputs("normal", 79, shape, 4)]
+    at = torch.arange(win[0] * win[1], device="cuda").view(win)      # tokens of a window of the last row,
+    at = torch.cat([torch.full((win[0], W), -1, device="cuda"), at.repeat(1, 3)])    # in the shifted frame
+    at = torch.roll(at, shift[0], 0)
+    bad, keep = at >= poisoned, at < clean
+    poison = []
+    for t in good:
+        t = t.clone()
+        t[:, bad] = value
+        poison.append(t)
+    runs = []
+    for q, k, v, do in (good, poison):
+        o, lse = B.aeris_winattn_fwd(q, k, v, win, shift, mask)
+        runs.append([o, lse.permute(0, 2, 3, 1), *B.aeris_winattn_bwd(q, k, v, o, lse, do, win, shift, mask)])
+    torch.cuda.synchronize()
+    for name, a, b in zip(("o", "lse", "dq", "dk", "dv"), *runs):
+        assert torch.isfinite(a.float()).all(), name
+        assert torch.equal(a[:, keep], b[:, keep]), name
+
+
 @pytest.mark.parametrize("shift", [(0, 0), (5, 7)])
 def test_one_window_is_global_attention(shift):
     run_case((1, 24, 40, 2, 64), (24, 40), shift, B.AERIS_MASK_NONE, seed=61)
