@@ -250,8 +250,8 @@ int aeris_winattn_bwd_static(const aeris_winattn_params* p, const void* q, const
   float* stats = nullptr;
   rc = static_scratch_address(&stats);
   if (rc != AERIS_OK) return rc;
-  // Nothing in the array has to start at zero: the dQ kernel writes every statistic the dK/dV
-  // kernel reads (all tokens of all pairs plus the padding behind the last pair) in this call.
+  // Nothing in the array has to start at zero: what makes dQ writes every statistic that dK and dV
+  // need (all tokens of all pairs plus the padding behind the last pair) in this call.
   if (aeris::launch_bwd(kp, p->head_dim, p->out_dtype == AERIS_DT_F32, q, k, v, o, lse, d_o, dq,
                         dk, dv, stats, static_cast<hipStream_t>(hip_stream), AERIS_BWD_ALL) != 0)
     return AERIS_ERR_HIP_LAUNCH;

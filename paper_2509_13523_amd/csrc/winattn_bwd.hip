@@ -3,7 +3,8 @@
 // formulas are the ones listed in include/aeris_winattn.h).  P is recomputed
 // from the saved log-sum-exp; nothing of size T x T touches memory.
 //
-// Three kernels, no atomics (bitwise reproducible):
+// Three kernels, no atomics (bitwise reproducible), for windows longer than one workgroup can hold
+// (short_backward; those have dq and dkdv in one kernel of their own):
 //   delta   delta_i = sum_c dO_ic O_ic, and LSE_i * log2(e)   (HBM-bound pre-pass)
 //   dq      queries resident, keys streamed:   S^T, dP^T -> dS^T -> dQ^T += K^T dS^T
 //   dkdv    keys resident, queries streamed:   S, dP -> P, dS -> dV^T += dO^T P,
@@ -171,12 +172,11 @@ __global__ __launch_bounds__(kThreads, 2) void winattn_dq_kernel(
     // delta = sum_c dO*O with the summation tree of winattn_delta_kernel: an fma chain over
     // the 8 channels of a chunk, then pairwise over the chunk index (bit 0 first).  This lane
     // holds chunks 2*kk + g; the partner lane (l ^ 32) holds the other chunk of every pair.
-    // Up to head_dim 64 every load is issued before the first value is used.  Short windows are bound by
-    // round trips to memory, and left to itself the compiler may take the chunks and the log-sum-exp one
-    // after the other, each behind the chain of the one before (head_dim 32, 8 heads, dQ, us: 4 tokens
-    // 237 -> 220, 16: 175 -> 161, 25: 79 -> 73, 144: 74 -> 66).  At head_dim 128 the same order would
-    // serve windows of 4 to 25 tokens (16: 600 -> 562) but cost those of 2304 and 3600, 0.6 to 1 %:
-    // there the waves of a SIMD start apart otherwise, and their loops overlap better.
+    // Up to head_dim 64 every load is issued before the first value is used: left to itself the compiler
+    // may take the chunks and the log-sum-exp one after the other, each behind the chain of the one before
+    // (head_dim 32, 8 heads, us: 196 tokens 60.0 -> 54.9, 256: 52.9 -> 48.5, 400: 86.2 -> 84.2; 64 the same
+    // either way).  At head_dim 128 that order costs windows of 2304 and 3600 tokens 0.6 to 1 %: there the
+    // waves of a SIMD start apart otherwise, and their loops overlap better.
     constexpr bool kAtOnce = D <= 64;
     const OutT* orow = o + o_base + (long long)q_grid * p.o_tok + 8 * g;
     const float* lse_q = lse + ((long long)win.b * p.nh + win.head) * plane + q_grid;
@@ -657,18 +657,16 @@ __global__ __launch_bounds__(kThreads, 2) void winattn_dkdv_kernel(
 constexpr size_t kLdsOfCu = 160 * 1024;
 
 // head_dim 32: grids of more than this many workgroups, the three per CU that the other order has
-// registers for, run the lean dK/dV kernel, and so do windows of a single streamed tile, which have
-// little to overlap.  Other / lean, 4 heads, us: 3600 tokens 116 workgroups 44.1 / 46.3, 464 95.3 /
-// 100.1, 928 153 / 148, 4060 511 / 499; 256 tokens 128 8.7 / 9.1, 720 15.0 / 14.8, 968 20.6 / 18.9, 4048
-// 62.8 / 56.0; 144 tokens 968 16.1 / 13.0; 16 tokens 728 6.0 / 5.6, 4096 19.2 / 16.1.  At head_dim 64 the
-// lean order would fit 168 registers, three waves per SIMD instead of two, but loses below 400 tokens
-// (65,000 tokens, 8 heads, windows of 64 / 144 / 256 / 400 / 529 / 900 / 3600 tokens: 126 / 160 / 119 /
-// 195 / 221 / 294 / 796 -> 159 / 165 / 127 / 187 / 205 / 270 / 750) and is not built for it.
+// registers for, run the lean dK/dV kernel.  Other / lean, 4 heads, us: 3600 tokens 116 workgroups 44.1 /
+// 46.3, 464 95.3 / 100.1, 928 153 / 148, 4060 511 / 499; 256 tokens 128 8.7 / 9.1, 720 15.0 / 14.8, 968
+// 20.6 / 18.9, 4048 62.8 / 56.0.  At head_dim 64 the lean order would fit 168 registers, three waves per
+// SIMD instead of two, but loses below 400 tokens (65,000 tokens, 8 heads, windows of 256 / 400 / 529 / 900 /
+// 3600 tokens: 119 / 195 / 221 / 294 / 796 -> 127 / 187 / 205 / 270 / 750) and is not built for it.
 constexpr int kLeanAboveBlocks = 768;
 
 DkDv dkdv_kernel(const KParams& kp, int head_dim) {
   if (head_dim == 128) return 2 * dkdv_smem_bytes<128>(kp.T) > kLdsOfCu ? DkDv::kPipelined : DkDv::kLean;
-  if (head_dim == 32 && (grid_blocks(kp) > kLeanAboveBlocks || kp.T <= kStream)) return DkDv::kLean;
+  if (head_dim == 32 && grid_blocks(kp) > kLeanAboveBlocks) return DkDv::kLean;
   return DkDv::kReadFirst;
 }
 
@@ -683,9 +681,9 @@ static int launch_bwd_t(KParams kp, const void* q, const void* k, const void* v,
 
   float* delta = workspace;
   float* lse2 = workspace + stat_entries(kp);
-  if (stages == 7u && short_backward(kp, D))
+  if ((stages & 6u) && short_backward(kp, D))
     return launch_bwd_short(kp, D, std::is_same<OutT, float>::value, q, k, v, o, lse, d_o, delta, lse2, dq, dk, dv,
-                            stream);
+                            stream, stages);
   // with both stages requested the dQ kernel produces the statistics itself
   const bool fused_stats = (stages & 3u) == 3u;
   if ((stages & 1u) && !fused_stats) {

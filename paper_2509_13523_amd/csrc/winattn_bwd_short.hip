@@ -1,6 +1,9 @@
 // Backward attention of short windows in one kernel: one workgroup owns a whole (batch, window, head)
-// and makes dQ, dK and dV of it (same contract as all three stages of launch_bwd, statistics in the
-// workspace included, so that a later single stage finds them).
+// and makes dQ, dK and dV of it (same contract as launch_bwd, statistics in the workspace included).  dQ
+// alone, and dK and dV alone, are builds of the same kernel without the other's work: stages give the bits of
+// the whole.  (A selection at run time in one build cost the whole 1 to 7 %.)  dQ with its statistics and then dK
+// and dV, us, the two kernels of longer windows / these two: 8 heads of 32, 16 tokens 218 / 124, 64: 81 / 82,
+// 120: 90 / 124, 144: 135 / 131, 192: 107 / 145; 7 of 64, 64 tokens 167 / 163, 120: 162 / 196, 144: 242 / 214.
 //
 // Short windows are bound by memory and its latency, and the two kernels of longer windows serve them
 // badly: 14 passes over tensors and seven products where 8 and five would do, tiles of 128 resident tokens
@@ -60,13 +63,16 @@ __device__ __forceinline__ float dpp(float x) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), kCtrl, 0xf, 0xf, true));
 }
 
-// NU: units of 16 keys per wave, W wavefronts
-template <int D, int NU, typename OutT>
+// NU: units of 16 keys per wave, W wavefronts.  kStages: 7, or 2 (dQ), or 4 (dK, dV), which take the statistics
+// from the workspace unless told to make them.
+template <int D, int NU, typename OutT, int kStages>
 __global__ __launch_bounds__(256, (kShortWaves<D, NU>)) void winattn_bwd_short_kernel(
     KParams p, const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const bf16_t* __restrict__ v,
     const bf16_t* __restrict__ d_o, const OutT* __restrict__ o, const float* __restrict__ lse,
     float* __restrict__ delta, float* __restrict__ lse2v, OutT* __restrict__ dq, OutT* __restrict__ dk,
-    OutT* __restrict__ dv) {
+    OutT* __restrict__ dv, int make) {
+  constexpr bool kDq = kStages & 2, kDkDv = kStages & 4;
+  const bool make_stats = kStages == 7 || make != 0;
   using Tl = Tile<D>;
   using Strip = Tile<32>;
   constexpr int kKK = D / 32, kCB = D / 16;               // products over channels; blocks of 16 channels
@@ -82,14 +88,14 @@ __global__ __launch_bounds__(256, (kShortWaves<D, NU>)) void winattn_bwd_short_k
 
   int pair, tile;
   if (!block_to_work(p, pair, tile)) return;
-  if (blockIdx.x == 0)   // padding behind the last pair, which the other kernels' streamed tiles may read
+  if (make_stats && blockIdx.x == 0)   // padding behind the last pair, as the other kernels leave it
     for (int t = tid; t < kStream; t += blockDim.x) {
       delta[(long long)p.n_pairs * p.T + t] = 0.f;
       lse2v[(long long)p.n_pairs * p.T + t] = 0.f;
     }
   Window win;
   if (!win.init(p, pair)) {
-    for (int t = tid; t < p.T; t += blockDim.x) {   // a skipped window still gets finite statistics
+    for (int t = tid; make_stats && t < p.T; t += blockDim.x) {   // a skipped window still gets finite statistics
       delta[(long long)pair * p.T + t] = 0.f;
       lse2v[(long long)pair * p.T + t] = 0.f;
     }
@@ -175,25 +181,28 @@ __global__ __launch_bounds__(256, (kShortWaves<D, NU>)) void winattn_bwd_short_k
     const int c = tid % kChunks, per_pass = blockDim.x / kChunks;
     Raw8<OutT> o8[kPasses];
 #pragma unroll
-    for (int i = 0; i < kPasses; ++i) {
+    for (int i = 0; i < kPasses && make_stats; ++i) {
       const int t = i * per_pass + tid / kChunks;
       const long long at = grid_of(t < p.T ? t : p.T - 1);
       o8[i].load(o + o_base + at * p.o_tok + 8 * c);
     }
-    const float own_lse = lse[((long long)win.b * p.nh + win.head) * plane + grid_of(tid < p.T ? tid : p.T - 1)];
+    const float own_lse =
+        make_stats ? lse[((long long)win.b * p.nh + win.head) * plane + grid_of(tid < p.T ? tid : p.T - 1)] : 0.f;
     for (int t = p.T + tid; t < rows; t += blockDim.x) {   // phantom queries: finite statistics
       *reinterpret_cast<AERIS_LDS float*>(stat_at + t * 4) = 0.f;
       *reinterpret_cast<AERIS_LDS float*>(stat_at + (rows + t) * 4) = 0.f;
     }
     wait_async_loads();
     __syncthreads();
+    if (!make_stats && tid < p.T)
+      *reinterpret_cast<AERIS_LDS float*>(stat_at + (rows + tid) * 4) = delta[(long long)pair * p.T + tid];
     if (tid < p.T) {
-      const float l2 = own_lse * kLog2e;
+      const float l2 = make_stats ? own_lse * kLog2e : lse2v[(long long)pair * p.T + tid];
       *reinterpret_cast<AERIS_LDS float*>(stat_at + tid * 4) = l2;
-      lse2v[(long long)pair * p.T + tid] = l2;
+      if (make_stats) lse2v[(long long)pair * p.T + tid] = l2;
     }
 #pragma unroll
-    for (int i = 0; i < kPasses; ++i) {
+    for (int i = 0; i < kPasses && make_stats; ++i) {
       const int t = i * per_pass + tid / kChunks;
       if (t < p.T) {   // whole token groups leave together
         const bf16x8 d8 = Tl::read_rm(do_at + Tl::chunk_offset(t, c));
@@ -310,7 +319,7 @@ __global__ __launch_bounds__(256, (kShortWaves<D, NU>)) void winattn_bwd_short_k
 #pragma unroll
     for (int i = 0; i < NU; ++i) {
       const int u = wave + W * i;
-      if (u < units) {
+      if (kDq && u < units) {
         const uint32_t at = ds_at + u * (16 * 64) + strip_off;
         *reinterpret_cast<AERIS_LDS u32x2*>(at) = u32x2{dsb[i].u[0], dsb[i].u[1]};
         *reinterpret_cast<AERIS_LDS u32x2*>(at ^ 32) = u32x2{dsb[i].u[2], dsb[i].u[3]};
@@ -329,13 +338,14 @@ __global__ __launch_bounds__(256, (kShortWaves<D, NU>)) void winattn_bwd_short_k
     }
 #pragma unroll
     for (int i = 0; i < NU; ++i) {
-      if (!(seen >> i & 1)) continue;
+      if (!kDkDv || !(seen >> i & 1)) continue;
 #pragma unroll
       for (int c = 0; c < kCB; ++c) {
         dvacc[i][c] = mfma16(dot[c], pb[i].h, dvacc[i][c]);
         dkacc[i][c] = mfma16(qt[c], dsb[i].h, dkacc[i][c]);
       }
     }
+    if constexpr (!kDq) continue;
     // the strip is complete; the one of the block before is free again
     lds_barrier();
     // ---- dQ of these 32 queries: pieces of 16 queries x 32 channels, dealt to the waves in turn
@@ -404,6 +414,7 @@ __global__ __launch_bounds__(256, (kShortWaves<D, NU>)) void winattn_bwd_short_k
     turn -= kCB % W;
     if (turn < 0) turn += W;
   }
+  if constexpr (!kDkDv) return;
 
 #pragma unroll
   for (int i = 0; i < NU; ++i) {
@@ -440,15 +451,23 @@ inline int short_units_per_wave(int T) { return (short_units(T) + short_waves(T)
 template <int D, int NU, typename OutT>
 static int launch_short_t(KParams kp, const void* q, const void* k, const void* v, const void* o, const float* lse,
                           const void* d_o, float* delta, float* lse2, void* dq, void* dk, void* dv,
-                          hipStream_t stream) {
+                          hipStream_t stream, unsigned stages) {
   kp.n_tiles = 1;
   kp.n_whole = whole_windows(kp, AttnKernel::kDkDv, D);
-  if (!allow_full_lds<winattn_bwd_short_kernel<D, NU, OutT>>()) return -1;
-  return launch_kernel(winattn_bwd_short_kernel<D, NU, OutT>, dim3(grid_blocks(kp)), dim3(short_waves(kp.T) * 64),
-                       short_smem_bytes(kp.T, D), stream, kp, static_cast<const bf16_t*>(q),
-                       static_cast<const bf16_t*>(k), static_cast<const bf16_t*>(v),
-                       static_cast<const bf16_t*>(d_o), static_cast<const OutT*>(o), lse, delta, lse2,
-                       static_cast<OutT*>(dq), static_cast<OutT*>(dk), static_cast<OutT*>(dv));
+  auto launch = [&](auto which, int make) {
+    constexpr int kStages = decltype(which)::value;
+    if (!allow_full_lds<winattn_bwd_short_kernel<D, NU, OutT, kStages>>()) return -1;
+    return launch_kernel(winattn_bwd_short_kernel<D, NU, OutT, kStages>, dim3(grid_blocks(kp)),
+                         dim3(short_waves(kp.T) * 64), short_smem_bytes(kp.T, D), stream, kp,
+                         static_cast<const bf16_t*>(q), static_cast<const bf16_t*>(k), static_cast<const bf16_t*>(v),
+                         static_cast<const bf16_t*>(d_o), static_cast<const OutT*>(o), lse, delta, lse2,
+                         static_cast<OutT*>(dq), static_cast<OutT*>(dk), static_cast<OutT*>(dv), make);
+  };
+  if (stages == 7u) return launch(Const<7>{}, 1);
+  const int make = stages & 1u;
+  if (!(stages & 4u)) return launch(Const<2>{}, make);
+  if (!(stages & 2u)) return launch(Const<4>{}, make);
+  return launch(Const<2>{}, make) == 0 ? launch(Const<4>{}, 0) : -1;
 }
 
 // Windows that leave room for a second workgroup in a CU's LDS, with at most three units of keys per wave:
@@ -461,11 +480,12 @@ bool short_backward(const KParams& kp, int head_dim) {
 
 int launch_bwd_short(const KParams& kp, int head_dim, bool out_f32, const void* q, const void* k, const void* v,
                      const void* o, const float* lse, const void* d_o, float* delta, float* lse2, void* dq,
-                     void* dk, void* dv, hipStream_t stream) {
+                     void* dk, void* dv, hipStream_t stream, unsigned stages) {
 #define AERIS_SHORT_CASE(DD, NN)                                                                              \
   if (head_dim == DD && short_units_per_wave(kp.T) == NN)                                                     \
-    return out_f32 ? launch_short_t<DD, NN, float>(kp, q, k, v, o, lse, d_o, delta, lse2, dq, dk, dv, stream) \
-                   : launch_short_t<DD, NN, bf16_t>(kp, q, k, v, o, lse, d_o, delta, lse2, dq, dk, dv, stream);
+    return out_f32                                                                                                \
+               ? launch_short_t<DD, NN, float>(kp, q, k, v, o, lse, d_o, delta, lse2, dq, dk, dv, stream, stages) \
+               : launch_short_t<DD, NN, bf16_t>(kp, q, k, v, o, lse, d_o, delta, lse2, dq, dk, dv, stream, stages);
   AERIS_SHORT_CASE(32, 1)
   AERIS_SHORT_CASE(32, 2)
   AERIS_SHORT_CASE(32, 3)

@@ -66,11 +66,11 @@ int launch_dkdv_pipe128(const KParams& kp, bool out_f32, const void* q, const vo
                         const void* v, const void* d_o, const float* delta, const float* lse2,
                         void* dk, void* dv, hipStream_t stream);
 
-// All stages of launch_bwd in one kernel, for windows that one workgroup can hold (same contract; delta
-// and lse2 are the two workspace vectors), and whether that is the way to run a problem.
+// Any stages of launch_bwd, DQ or DKDV among them, in one kernel, for windows that one workgroup can hold (same
+// contract; delta and lse2 are the two workspace vectors), and whether that is the way to run a problem.
 int launch_bwd_short(const KParams& kp, int head_dim, bool out_f32, const void* q, const void* k,
                      const void* v, const void* o, const float* lse, const void* d_o, float* delta,
-                     float* lse2, void* dq, void* dk, void* dv, hipStream_t stream);
+                     float* lse2, void* dq, void* dk, void* dv, hipStream_t stream, unsigned stages);
 bool short_backward(const KParams& kp, int head_dim);
 
 // What makes dK and dV where that is not: the generic kernel with all operands read first, or read one block

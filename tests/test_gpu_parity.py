@@ -414,6 +414,39 @@ def test_backward_is_bitwise_reproducible_and_staged_equals_whole():
         assert torch.equal(x.view(torch.int16), z.view(torch.int16))
 
 
+@pytest.mark.parametrize("d,win", [(32, (4, 4)), (32, (6, 7)), (32, (12, 16)), (32, (14, 14)), (64, (1, 9)), (64, (8, 8)),
+                                   (64, (12, 12)), (64, (5, 29)), (128, (5, 5)), (128, (8, 8)), (128, (5, 13))])
+@pytest.mark.parametrize("out", [B.AERIS_DT_BF16, B.AERIS_DT_F32])
+def test_any_order_of_stages_equals_the_whole(d, win, out):
+    """Every selection of stages, in any order after the statistics, gives the bits of the whole backward call,
+    leaves the outputs of the others alone and leaves the same statistics, on both sides of the window
+    size from which one kernel makes all three gradients."""
+    shape, shift, mask = (2, 2 * win[0], 3 * win[1], 2, d), (win[0] // 2, win[1] // 3), B.AERIS_MASK_SWIN
+    tq, tk, tv, tdo = [to_dev(b) for b in synth.make_inputs("normal", 10, shape, 4)]
+    o, lse = B.aeris_winattn_fwd(tq, tk, tv, win, shift, mask, out_dtype=out)
+    need = B.aeris_winattn_bwd_workspace_bytes(B.make_params(shape, win, shift, mask, None, out))
+
+    def run(*selections):
+        ws = torch.full((need // 4,), float("nan"), dtype=torch.float32, device="cuda")
+        g = [torch.full_like(o, float("nan")) for _ in range(3)]
+        for stages in selections:
+            B.aeris_winattn_bwd_stages(tq, tk, tv, o, lse, tdo, win, shift, mask, out_dtype=out, dq=g[0], dk=g[1],
+                                       dv=g[2], workspace=ws.view(torch.uint8), stages=stages)
+        torch.cuda.synchronize()
+        return g, ws
+
+    whole, stats = run(B.AERIS_BWD_ALL)
+    for selections in ((1, 2, 4), (1, 4, 2), (3, 4), (5, 2), (1, 6), (1,), (3,), (5,)):
+        g, ws = run(*selections)
+        assert torch.equal(ws, stats), selections
+        did = sum(selections) if len(selections) > 1 else selections[0]
+        for i, t in enumerate(g):
+            if did & (2 if i == 0 else 4):
+                assert torch.equal(t, whole[i]), (selections, i)
+            else:
+                assert torch.isnan(t).all(), (selections, i)
+
+
 def test_errors_raise_on_gpu_box():
     tq = torch.zeros((1, 16, 16, 1, 64), dtype=torch.bfloat16, device="cuda")
     with pytest.raises(B.AerisError) as e:
