@@ -453,7 +453,7 @@ static int launch_short_t(KParams kp, const void* q, const void* k, const void* 
                           const void* d_o, float* delta, float* lse2, void* dq, void* dk, void* dv,
                           hipStream_t stream, unsigned stages) {
   kp.n_tiles = 1;
-  kp.n_whole = whole_windows(kp, AttnKernel::kDkDv, D);
+  kp.n_whole = whole_short_windows(kp, AttnKernel::kDkDv, D);
   auto launch = [&](auto which, int make) {
     constexpr int kStages = decltype(which)::value;
     if (!allow_full_lds<winattn_bwd_short_kernel<D, NU, OutT, kStages>>()) return -1;

@@ -83,42 +83,60 @@ __host__ __device__ inline int table_bytes(int T) { return ((T + kStream - 1) / 
 // does not fall on one XCD; the last n % 8 windows are dealt pair by pair.
 // Grid size: grid_blocks().  Returns false for padding.
 //
-// Ratio of times, whole windows to round-robin (1 to 16 heads, 65,000 and 300,000 tokens; a single
-// point repeats to 2 %):
-//   head_dim 32, 2 to 16 heads  49-121 tokens  144-256    324-400    529-640    900
-//     forward                   0.75-1.00      0.82-1.05  0.97-1.04  0.98-1.04  0.99-1.05
-//     dQ                        0.68-0.92      0.77-0.97  0.89-1.00  0.91-1.02  0.94-1.07
-//     dK/dV                     0.69-0.95      0.74-1.00  0.94-1.01  0.96-1.04  0.98-1.06
-//   head_dim 64, 8 and 16 heads 49-121         144-256    324-400    529-784    900
-//     forward                   0.87-1.00      0.87-1.01  0.93-1.00  0.97-1.04  1.00-1.06
-//     dQ                        0.83-0.91      0.83-0.90  0.88-0.94  0.91-0.97  0.96-1.02
-//     dK/dV                     0.87-0.97      0.86-0.95  0.91-0.95  0.95-1.01  0.97-1.02
-//   head_dim 128, 4, 8, 12, 16  49-121         144-256    324-400    529-784    900
-//     forward                   0.93-1.10      0.94-1.02  0.94-1.00  0.95-1.02  0.99-1.03
-//     dQ                        0.97-1.06      0.94-1.02  0.93-0.98  0.96-1.00  0.97-1.03
-//     dK/dV                     0.96-1.02      0.95-0.99  0.94-0.98  0.97-1.01  0.98-1.05
+// Ratio of times, whole windows to round-robin, of the kernels that stream (1 to 16 heads, 65,000 and 300,000
+// tokens; a single point repeats to 2 %):
+//   head_dim 32, 2 to 16 heads  100-121    144-256    324-400    529-640    900
+//     forward                              0.82-1.05  0.97-1.04  0.98-1.04  0.99-1.05
+//     dQ                                   0.77-0.97  0.89-1.00  0.91-1.02  0.94-1.07
+//     dK/dV                                0.74-1.00  0.94-1.01  0.96-1.04  0.98-1.06
+//   head_dim 64, 8 and 16 heads 100-121    144-256    324-400    529-784    900
+//     forward                   0.87-1.00  0.87-1.01  0.93-1.00  0.97-1.04  1.00-1.06
+//     dQ                                   0.83-0.90  0.88-0.94  0.91-0.97  0.96-1.02
+//     dK/dV                                0.86-0.95  0.91-0.95  0.95-1.01  0.97-1.02
+//   head_dim 128, 4, 8, 12, 16  81-121     144-256    324-400    529-784    900
+//     forward                              0.94-1.02  0.94-1.00  0.95-1.02  0.99-1.03
+//     dQ                        0.97-1.06  0.94-1.02  0.93-0.98  0.96-1.00  0.97-1.03
+//     dK/dV                     0.96-1.02  0.95-0.99  0.94-0.98  0.97-1.01  0.98-1.05
 //   other head counts at 64 and 128, and one head of 32: 0.97-1.05 everywhere.
 // ----------------------------------------------------------------------------
-struct WholeWindows {
-  int from, to;   // tokens of a window
-};
-enum class AttnKernel { kForward, kDq, kDkDv };
-// The ranges in which the ratios above are below 1 but for single points.  Below, workgroups live for
-// a few microseconds and the longer way to the work item shows; above, products take over from
-// memory; at head_dim 128 windows of a single resident tile (up to kResident tokens) have nothing to
+// The longest windows for which the ratios above are below 1 but for single points: above, products take over
+// from memory.  At head_dim 128 windows of a single resident tile (up to kResident tokens) have nothing to
 // share between workgroups.
-constexpr WholeWindows whole_window_range(AttnKernel kernel, int head_dim) {
-  if (head_dim == 128) return {kResident + 1, 784};
-  if (head_dim == 64) return kernel == AttnKernel::kForward ? WholeWindows{36, 400} : WholeWindows{36, 784};
-  return kernel == AttnKernel::kForward ? WholeWindows{40, 256} : WholeWindows{32, 576};
+enum class AttnKernel { kForward, kDq, kDkDv };
+constexpr int whole_window_most_tokens(AttnKernel kernel, int head_dim) {
+  if (head_dim == 128) return 784;
+  if (kernel == AttnKernel::kForward) return head_dim == 64 ? 400 : 256;
+  return head_dim == 64 ? 784 : 576;
 }
 
+// Rows that share lines, or crowd channels (above).
+inline bool rows_meet(const KParams& p, int head_dim) {
+  return (head_dim == 32 && p.nh > 1) || (long long)p.nh * head_dim * 2 % 1024 == 0;
+}
 // Windows dealt whole; the pairs of the others, if any, are dealt round-robin.
 inline int whole_windows(const KParams& p, AttnKernel kernel, int head_dim) {
-  const WholeWindows range = whole_window_range(kernel, head_dim);
-  const bool shared_lines = head_dim == 32 && p.nh > 1;
-  const bool crowded = (long long)p.nh * head_dim * 2 % 1024 == 0;
-  return (shared_lines || crowded) && p.T >= range.from && p.T <= range.to ? (p.B * p.n_win) & ~7 : 0;
+  const bool in_range = p.T <= whole_window_most_tokens(kernel, head_dim) && (head_dim < 128 || p.T > kResident);
+  return in_range && rows_meet(p, head_dim) ? (p.B * p.n_win) & ~7 : 0;
+}
+// The same for the kernels that hold a window and head whole.  Workgroups of the shortest windows live for a
+// few microseconds and the longer way to the work item shows; and rows have to come from behind the caches
+// that would hide the double fetch (head_dim 32) or the crowding (64).  Ratios of times as above, by the bytes
+// of all inputs and outputs:
+//   head_dim 32, 2 to 16 heads  1-8 tokens  9          12-64      81-169
+//     forward, > 24 MB          0.95-1.11   0.87-1.08  0.63-0.96  0.67-0.91
+//     backward, > 24 MB         0.86-1.02   0.82-0.94  0.73-0.88  0.72-0.94
+//     both, < 24 MB             0.99-1.08   0.99-1.07  0.99-1.08  0.98-1.03
+//   head_dim 64, 8 and 16 heads
+//     forward, > 400 MB         0.97-1.05   0.90-0.91  0.80-0.90  0.83-0.96
+//     backward, > 400 MB        0.98-1.02   0.97-0.98  0.84-1.01  0.89-1.05
+//     both, < 400 MB            1.01-1.07   1.02-1.07  0.96-1.07  0.98-1.06
+//   head_dim 128, 2 to 16 heads, forward 0.92-1.05, backward 0.98-1.12; other head counts at 64, and one head of
+//   32: 0.94-1.06.
+inline int whole_short_windows(const KParams& p, AttnKernel kernel, int head_dim) {
+  const bool forward = kernel == AttnKernel::kForward;
+  const double bytes = (double)p.n_pairs * p.T * head_dim * 2.0 * (forward ? 4.0 : 8.0);
+  const bool pays = head_dim < 128 && p.T >= (forward ? 12 : 9) && bytes > (head_dim == 32 ? 24e6 : 400e6);
+  return pays && rows_meet(p, head_dim) ? (p.B * p.n_win) & ~7 : 0;
 }
 __device__ __forceinline__ bool block_to_work(const KParams& p, int& pair, int& tile) {
   const int id = blockIdx.x;

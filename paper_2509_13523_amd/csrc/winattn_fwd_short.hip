@@ -273,7 +273,7 @@ template <int D, int NB, typename OutT>
 static int launch_fwd_short_t(KParams kp, const void* q, const void* k, const void* v, void* o, float* lse,
                               hipStream_t stream) {
   kp.n_tiles = short_forward_workgroups(kp);
-  kp.n_whole = whole_windows(kp, AttnKernel::kForward, D);
+  kp.n_whole = whole_short_windows(kp, AttnKernel::kForward, D);
   const int units = (kp.T + 15) / 16;
   auto launch = [&](auto shared) {
     constexpr bool kShared = decltype(shared)::value != 0;
