@@ -818,7 +818,11 @@ int norm_projection(const void* x, const float* w, const float* gamma, const flo
   const int64_t n_samples = n_rows / rows_per_sample;
   const Folded f = carve(workspace, n_rows, n_samples, channels, features);
   const long long waves = (n_rows + 3) / 4;
-  const unsigned row_blocks = (unsigned)(((waves < 8192 ? waves : 8192) + n_samples - 1) / n_samples);
+  unsigned row_blocks = (unsigned)(((waves < 8192 ? waves : 8192) + n_samples - 1) / n_samples);
+  // a launch holds less than 2^32 work items along x: nearly that many features leave room for few row blocks
+  constexpr unsigned kMostBlocks = 0xffffffffu / 256;
+  if ((unsigned)features < kMostBlocks && row_blocks > kMostBlocks - (unsigned)features)
+    row_blocks = kMostBlocks - (unsigned)features;
   if (launch_kernel(norm_fold_kernel, dim3(row_blocks + (unsigned)features, (unsigned)n_samples), dim3(256), 0,
                     st, static_cast<const bf16_t*>(x), (long long)n_rows, eps, f.r, row_blocks,
                     static_cast<const bf16_t*>(weight), w, gamma, beta, channels, features, f.w, f.bias) != 0)

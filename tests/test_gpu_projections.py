@@ -242,6 +242,25 @@ def test_attention_branch_from_the_fused_projections():
     assert errs["qkv"] <= 3e-3 and errs["a"] <= 5e-3 and errs["y"] <= 6e-3 and errs["out"] <= 3e-3, errs
 
 
+def test_norm_projection_to_as_many_features_as_a_launch_holds():
+    """16,777,208 features, a workgroup of 256 threads each: what a launch holds (2^32 - 1 work items), with seven
+    workgroups left for the row pass, which walks over 40 rows with them.  Sampled features against the oracle."""
+    rows, C, F, eps = 40, 64, 16777208, 1e-6
+    gen = torch.Generator(device="cuda").manual_seed(4)
+    try:
+        tx = torch.randn(rows, C, device="cuda", dtype=torch.bfloat16, generator=gen)
+        tw = 1.0 + 0.1 * torch.randn(C, device="cuda", generator=gen)
+        tgamma, tbeta = [0.3 * torch.randn(1, C, device="cuda", generator=gen) for _ in range(2)]
+        tweight = torch.randn(F, C, device="cuda", dtype=torch.bfloat16, generator=gen).mul_(C ** -0.5)
+        y = B.aeris_norm_linear_fwd(tx, tw, tgamma, tbeta, eps, tweight, rows)
+        at = torch.tensor([0, 1, 255, 65536, 8388607, 16768999, F - 9, F - 1], device="cuda")
+        c = dict(x=to_f64(tx), weight=to_f64(tweight[at]), w=to_f64(tw), gamma=to_f64(tgamma), beta=to_f64(tbeta))
+        ref = bo.norm_linear_fwd(c["x"], c["w"], c["gamma"], c["beta"], eps, rows, c["weight"])
+        close("y", y[:, at], ref, rounding_bound(c, eps, rows))
+    finally:
+        torch.cuda.empty_cache()
+
+
 def test_projection_errors_are_reported():
     x = torch.zeros(256, 64, dtype=torch.bfloat16, device="cuda")
     wt = torch.zeros(16, 64, dtype=torch.bfloat16, device="cuda")
