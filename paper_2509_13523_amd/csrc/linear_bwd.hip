@@ -313,7 +313,32 @@ __global__ __launch_bounds__(S::kWaves * 64, S::kWaves * S::kPerCu / 4) void lin
 // that one multiplies while the other fetches its operands and issues copies.  A half of a stage is
 // copied over as soon as both waves have its operands in registers, three halves ahead of its use.
 // Bound by the board's power cap.  172800 rows, us, all waves together / in turns, one session: 2048 -> 2048
-// 1390 / 1251, 2048 -> 6144 3655 / 3461, 5504 -> 2048 3572 / 3325, 2048 -> 11008 6538 / 6445.
+// 1390 / 1251, 2048 -> 6144 3655 / 3461, 5504 -> 2048 3572 / 3325.
+//
+// The 32 workgroups of an XCD that walk the same rows share them through its L2 only while they stay
+// together.  A wave that waits for its copies is held when it leads (they come from memory) and not when it
+// follows (from the L2), but copies issued three halves ahead are hardly ever waited for, and in a long range the
+// workgroups drift apart (4,147,200 rows, 2048 -> 6144, 12 ranges of 5400 steps: 732 GB fetched into the L2s
+// where 166 had been, 81.5 -> 93.7 ms).  So long ranges wait for copies issued one half earlier (kNear), and the
+// longest also for all of them at every 64th step (kHeld).  us, all waves together / kFar / kNear / kHeld:
+//   rows x channels -> features   steps of a range
+//   130000 x 2048 -> 2048           64               1062 /   948 /   980 /   992
+//   172800 x 2048 -> 2048           85               1380 /  1198 /  1226 /  1265
+//   100000 x 2048 -> 6144          131               2166 /  1980 /  2002 /  2058
+//   300000 x 2048 -> 2048          147               2231 /  1948 /  1980 /  2040
+//   400000 x 2048 -> 2048          196               2934 /  2559 /  2578 /  2679
+//   172800 x 5504 -> 2048          225               3473 /  3194 /  3166 /  3271
+//   230000 x 2048 -> 6144          300               4694 /  4435 /  4362 /  4464
+//   172800 x 2048 -> 11008         338               6452 /  6189 /  6072 /  6069
+//   400000 x 2048 -> 6144          521               8030 /  7819 /  7503 /  7621
+//   691200 x 2048 -> 6144          900              13619 / 13852 / 12902 / 13155
+//   1036800 x 5504 -> 2048        1350              20702 / 21344 / 20424 / 20203
+//   1036800 x 2048 -> 11008       2025              37508 / 40231 / 38587 / 37728
+//   4147200 x 2048 -> 6144        5400              81497 / 93697 / 84310 / 81022
+enum class Pace { kFar, kNear, kHeld };
+constexpr int kNearFromSteps = 211, kHeldFromSteps = 1200;
+
+template <Pace kPace>
 __global__ __launch_bounds__(512, 2) void linear_wgrad_large_kernel(WgradParams p) {
   using S = WgradLarge;
   using Sub = S::Sub;
@@ -450,16 +475,18 @@ __global__ __launch_bounds__(512, 2) void linear_wgrad_large_kernel(WgradParams 
   // steps that copy whole steps only; those look for no last one, and their addresses need no products
   const int plain_end = p.tail != 0 && s1 == p.steps_total ? s1 - 1 : s1;
   unsigned long long dy_at = dy0 + (s0 + 1) * dy_step, x_at = x0 + (s0 + 1) * x_step;   // of the next step
+  constexpr int kBehind = kPace == Pace::kFar ? 8 : 4;      // copies that may be on their way
   for (; ks + 2 < plain_end; ++ks, here = S::kStageBytes - here) {
     fetch(0, here);
     copy_rows(1, S::kStageBytes - here, dy_at, x_at);
-    landed(Const<8>{});
+    if (kPace == Pace::kHeld && ((ks - s0) & 63) == 63) landed(Const<0>{});
+    else landed(Const<kBehind>{});
     products();
     dy_at += dy_step;
     x_at += x_step;
     fetch(1, here);
     copy_rows(0, here, dy_at, x_at);
-    landed(Const<8>{});
+    landed(Const<kBehind>{});
     products();
   }
   for (; ks < s1; ++ks, here = S::kStageBytes - here) {
@@ -660,9 +687,15 @@ int launch_wgrad(WgradParams p, hipStream_t stream) {
     return launch_kernel(kernel, dim3((unsigned)(p.splits * p.f_tiles * p.c_tiles)), dim3(S::kWaves * 64),
                          (size_t)S::kStages * S::kStageBytes, stream, p);
   };
-  if constexpr (std::is_same<S, WgradLarge>::value)
-    return allow_full_lds<linear_wgrad_large_kernel>() ? launch(linear_wgrad_large_kernel) : -1;
-  else
+  if constexpr (std::is_same<S, WgradLarge>::value) {
+    auto launch_at = [&](auto pace) {
+      constexpr auto kernel = linear_wgrad_large_kernel<decltype(pace)::value>;
+      return allow_full_lds<kernel>() ? launch(kernel) : -1;
+    };
+    if (p.steps_per_split >= kHeldFromSteps) return launch_at(std::integral_constant<Pace, Pace::kHeld>{});
+    if (p.steps_per_split >= kNearFromSteps) return launch_at(std::integral_constant<Pace, Pace::kNear>{});
+    return launch_at(std::integral_constant<Pace, Pace::kFar>{});
+  } else
     return allow_full_lds<linear_wgrad_kernel<S>>() ? launch(linear_wgrad_kernel<S>) : -1;
 }
 

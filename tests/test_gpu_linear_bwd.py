@@ -119,6 +119,31 @@ def test_short_ranges_of_the_largest_tiles(n, channels, features, plan):
     test_linear_bwd(n, channels, features, plan)
 
 
+@pytest.mark.parametrize("n,channels,features,plan", [
+    (80671, 2048, 6144, (256, 12, 106)),     # copies far ahead
+    (180017, 5504, 2048, (256, 12, 235)),    # one half ahead; 49 rows in the last step
+    (620003, 2048, 11008, (256, 8, 1211)),   # and all of them landed at every 64th step; 35 rows
+])
+def test_long_ranges_of_the_largest_tiles_on_samples(n, channels, features, plan):
+    """The paces at which the 256 x 256 kernel walks ranges of more steps: sampled entries of dW against the
+    oracle, which needs one column of dy and one of x each."""
+    assert B.aeris_linear_bwd_plan(n, channels, features) == plan
+    gen = torch.Generator(device="cuda").manual_seed(5200)
+    tx = torch.randn(n, channels, device="cuda", dtype=torch.bfloat16, generator=gen)
+    tdy = torch.randn(n, features, device="cuda", dtype=torch.bfloat16, generator=gen)
+    tw = torch.zeros(features, channels, device="cuda", dtype=torch.bfloat16)
+    _, dw = B.aeris_linear_bwd(tx, tw, tdy, want_dx=False)
+    torch.cuda.synchronize()
+    got, ref, mag = [], [], []
+    for f, c in [(0, 0), (255, 255), (256, 256), (features - 1, channels - 1), (1000, 77), (features - 130, 1999), (31, 2016)]:
+        dcol, xcol = [t.double().cpu().numpy() for t in (tdy[:, f], tx[:, c])]
+        _, r = bo.linear_bwd(xcol[:, None], np.zeros((1, 1)), dcol[:, None])
+        got.append(float(dw[f, c])); ref.append(r[0, 0]); mag.append(float(np.abs(dcol) @ np.abs(xcol)))
+    close_dw(np.array(got), np.array(ref), np.array(mag), n)
+    del tx, tdy, tw, dw
+    torch.cuda.empty_cache()
+
+
 def test_linear_bwd_undoes_the_forward_pairing():
     """<dx, x> = <dW, W> = <y, dy> with y from this library's own forward projection: the three
     GEMMs (forward, dx, dW) agree with each other, not only each with the oracle."""
