@@ -730,14 +730,17 @@ int launch_gemm_shape(const GemmParams& p, hipStream_t stream) {
 // round takes (microseconds: a fixed part plus a part per 64-channel step, less of both for a last
 // round that leaves CUs empty).  Medium tiles fetch the rows twice as often as large ones, which
 // counts once rows and results exceed the last-level cache (300000 x 192 -> 576 145 us with large
-// tiles, 161 with medium ones; 60000 x 192 -> 1408 67 / 58).  Fitted to 200 sizes of 1500 ... 150000
-// rows, 64 ... 5760 channels and 128 ... 6400 features: what it takes is 0.5 % slower than the better
-// shape on average, more than 7 % at 5 of them.  Small tiles have the shortest steps and are taken as
-// long as each has a CU of its own: 914 rows x 1600 -> 512 takes 8.2 us with small, 12.7 with medium
-// tiles, 1759 x 640 -> 1344 (588 small tiles) 11.0 and 7.8.  Medium tiles win
-// while large ones leave more than about half of the CUs without work (9522 x 2944 -> 704, 114 large
-// tiles: 41 / 57), large ones, with half the operand bytes per product, from there on (148, 18926 x
-// 2560 -> 512: 70 / 53; 150, 12738 x 5248 -> 704: 133 / 99; 172800 x 2048 -> 2048: 1391 / 1097).
+// tiles, 161 with medium ones; 60000 x 192 -> 1408 67 / 58) and rows are a good part of the bytes: hardly with
+// 64 channels, whose large tiles of a single step overlap nothing (699334 x 64 -> 896 352 / 286, 170130 x 64 ->
+// 2368 199 / 185).  Fitted to 200 sizes of 1500 ... 150000 rows, 64 ... 5760 channels and 128 ... 6400 features; at
+// 300 others (1500 ... 1230689 rows, 64 ... 3840 channels, 64 ... 6976 features) what it takes is 0.7 % slower than
+// the better shape on average, more than 5 % at 20 of them, most with up to 192 channels, where one round of
+// large tiles takes 1.2 us longer than estimated.  Small tiles have the shortest steps and are taken as long
+// as each has a CU of its own: 914 rows x 1600 -> 512 takes 8.2 us with small, 12.7 with medium tiles, 1759 x
+// 640 -> 1344 (588 small tiles) 11.0 and 7.8.  Medium tiles win while large ones leave more than about half
+// of the CUs without work (9522 x 2944 -> 704, 114 large tiles: 41 / 57), large ones, with half the operand
+// bytes per product, from there on (148, 18926 x 2560 -> 512: 70 / 53; 150, 12738 x 5248 -> 704: 133 / 99;
+// 172800 x 2048 -> 2048: 1391 / 1097).
 enum class GemmTile { kLarge, kMedium, kSmall };
 GemmTile choose_gemm_tile(long long large_tiles, long long medium_tiles, long long small_tiles, int steps,
                           bool cached) {
@@ -749,7 +752,7 @@ GemmTile choose_gemm_tile(long long large_tiles, long long medium_tiles, long lo
   const double medium_rest = (double)(medium_tiles % (2 * kCus)) / (2 * kCus);
   const double medium = (double)(medium_tiles / (2 * kCus)) * (2.5 + 0.93 * steps) +
                         (medium_rest > 0.0 ? 4.8 + steps * (0.42 + 0.45 * medium_rest) : 0.0);
-  return medium * (cached ? 1.0 : 1.2) < large ? GemmTile::kMedium : GemmTile::kLarge;
+  return medium * (cached ? 1.0 : steps == 1 ? 1.05 : 1.2) < large ? GemmTile::kMedium : GemmTile::kLarge;
 }
 
 }  // namespace
