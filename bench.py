@@ -3,12 +3,13 @@
 
 A step is one pass of the whole hot path over one synthetic batch: for every
 layer of the workload (an unshifted and a half-window-shifted attention layer
-alternate in the AERIS Swin stack) the forward kernel, then the delta, dK/dV
-and dQ kernels.  Inputs are generated on the device before the clock starts.
+alternate in the AERIS Swin stack) the forward call, then the backward call (a dQ
+kernel and one for dK and dV, or one for all three where windows are short).  Inputs are generated on the device before the clock starts.
 
 Prints ONE JSON line.  `value` is model TFLOP/s: 4*d*U forward + 8*d*U backward
 per layer, U = unmasked (query, key) pairs; recomputation inside the backward
-kernels (18*d*U are executed in total) is not credited.
+kernels (18*d*U are executed in total, 14*d*U where one kernel makes all gradients) is
+not credited.
 """
 import argparse
 import json
@@ -118,24 +119,28 @@ class PowerSampler:
         return out
 
 
-def kernel_symbol(stage, head_dim, window_tokens):
-    """Name of the kernel the library launches for a stage (its dispatch rule: the dK/dV stage has a
-    software-pipelined kernel of its own at head_dim 128 for windows of more than 1792 tokens)."""
-    if stage == "dkdv" and head_dim == 128 and window_tokens > 1792:
-        return "winattn_dkdv_pipe_kernel"
-    return "winattn_%s_kernel" % stage
+def kernel_symbol(stage, plan):
+    """Name of the kernel (of a backward call of two, both) that the library launches for a stage; plan
+    is what aeris_winattn_plan says of the workload."""
+    forward, backward = plan
+    if stage == "fwd":
+        return "winattn_fwd_short_kernel" if forward else "winattn_fwd_kernel"
+    if backward == 0:
+        return "winattn_bwd_short_kernel"
+    dkdv = "winattn_dkdv_pipe_kernel" if backward == 3 else "winattn_dkdv_kernel"
+    return {"dq": "winattn_dq_kernel", "dkdv": dkdv, "bwd": "winattn_dq_kernel + " + dkdv}[stage]
 
 
-def profiled_traffic(workload, stage, summary="c5_kernels_and_counters.txt"):
+def profiled_traffic(workload, stage, kernel, summary="c5_kernels_and_counters.txt"):
     """HBM bytes per launch of a kernel as the committed rocprofv3 counter summary records them
-    (lines `TRAFFIC <workload> <stage> <bytes>` in profiles/): measured in that profiling
+    (lines `TRAFFIC <workload> <stage> <kernel> <bytes>` in profiles/): measured in that profiling
     session, not in this run, and labelled so.  None when no summary covers the kernel."""
     path = os.path.join(ROOT, "profiles", summary)
     try:
         for line in open(path):
             f = line.split()
-            if len(f) == 4 and f[0] == "TRAFFIC" and f[1] == workload and f[2] == stage:
-                return {"traffic": float(f[3]),
+            if len(f) == 5 and f[:4] == ["TRAFFIC", workload, stage, kernel]:
+                return {"traffic": float(f[4]),
                         "traffic_source": "profiles/%s (rocprofv3 --pmc FETCH_SIZE + WRITE_SIZE "
                                           "of an earlier run of this file)" % summary}
     except OSError:
@@ -240,7 +245,10 @@ def main():
         U = {s: Bn * nh * sum(window_pairs(H, W, win, s, mask, w // nwx, w % nwx) for w in picks)
              for s in wl["layers"]}
     model_flops = sum((12 if wl["bwd"] else 4) * d * U[s] for s in wl["layers"])
-    kernel_flops = {"fwd": 4, "dq": 6, "dkdv": 8, "bwd": 14}
+    # which kernels run; a backward call of one kernel makes five products of 2*d*U, of two kernels seven
+    plan = B.aeris_winattn_plan(B.make_params(shape, win, wl["layers"][-1], mask), len(picks or ()))
+    one_bwd = wl["bwd"] and plan[1] == 0
+    kernel_flops = {"fwd": 4, "dq": 6, "dkdv": 8, "bwd": 10 if one_bwd else 14}
     events = {k: [] for k in kernel_flops}
 
     def timed(name, fn, record):
@@ -276,10 +284,11 @@ def main():
             timed("fwd", lambda: B.aeris_winattn_fwd(tq, tk, tv, win, s, mask, o=o, lse=lse),
                   record)
             if wl["bwd"]:
-                # the backward pass as aeris_winattn_bwd runs it, one event pair per kernel: the
-                # dQ kernel (which also produces delta and LSE*log2e), then the dK/dV kernel
-                for name, st in (("dq", B.AERIS_BWD_DELTA | B.AERIS_BWD_DQ),
-                                 ("dkdv", B.AERIS_BWD_DKDV)):
+                # the backward pass as aeris_winattn_bwd runs it, one event pair per kernel: the one
+                # kernel of short windows, or the dQ kernel (which also produces delta and LSE*log2e),
+                # then the dK/dV kernel
+                for name, st in ((("bwd", B.AERIS_BWD_ALL),) if one_bwd else
+                                 (("dq", B.AERIS_BWD_DELTA | B.AERIS_BWD_DQ), ("dkdv", B.AERIS_BWD_DKDV))):
                     timed(name, lambda: B.aeris_winattn_bwd_stages(
                         tq, tk, tv, o, lse, tdo, win, s, mask, dq=dq, dk=dk, dv=dv,
                         workspace=ws, stages=st), record)
@@ -325,13 +334,11 @@ def main():
     dom = max((k for k in kern if kernel_flops[k]), key=lambda k: kern[k]["avg_ms"] * len(events[k]))
     dom_flops = kernel_flops[dom] * d * sum(U.values()) / len(U)
     achieved = dom_flops / (kern[dom]["avg_ms"] * 1e-3) / 1e12
-    tokens = win[0] * win[1]
-    dom_name = (kernel_symbol("dq", d, tokens) + " + " + kernel_symbol("dkdv", d, tokens)
-                if dom == "bwd" else kernel_symbol(dom, d, tokens))
+    dom_name = kernel_symbol(dom, plan)
     roofline = {"kernel": dom_name, "bound": "mfma", "achieved": round(achieved, 2),
                 "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
                 "frac": round(achieved / PEAK_BF16_TFLOPS, 4)}
-    roofline.update(profiled_traffic(args.workload, dom))
+    roofline.update(profiled_traffic(args.workload, dom, dom_name))
     extra = {}
     if rope or share:
         # the same layers through the plain full-grid entry points, timed in this run, so that the
@@ -366,12 +373,12 @@ def main():
            "kernels": kern, "roofline": roofline}
     out.update(extra)
     out["board_power"] = board_power
-    # algorithmic HBM bytes per step: fwd reads Q,K,V and writes O, LSE; bwd reads Q,K,V,O,dO
-    # twice over its three kernels (O,dO; Q,K,V,dO; Q,K,V,dO) and writes dQ,dK,dV
+    # algorithmic HBM bytes per step: fwd reads Q,K,V and writes O, LSE; bwd of one kernel reads
+    # Q,K,V,O,dO, of two Q,K,V,O,dO and Q,K,V,dO, and both write dQ,dK,dV
     tensor = 2.0 * Bn * H * W * nh * d
     if picks is not None:
         tensor *= len(picks) / ((H // win[0]) * nwx)
-    step_bytes = len(wl["layers"]) * ((4 + (13 if wl["bwd"] else 0)) * tensor)
+    step_bytes = len(wl["layers"]) * ((4 + ((8 if one_bwd else 12) if wl["bwd"] else 0)) * tensor)
     out["algorithmic_gbs"] = round(step_bytes / (ms_per_step * 1e-3) / 1e9, 1)
 
     if not args.no_mfma_loop:
@@ -524,7 +531,7 @@ def bench_projections(args):
         "roofline": {"kernel": "projection_gemm_kernel (%s)" % slow[0], "bound": "mfma",
                      "achieved": achieved, "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
                      "frac": round(achieved / PEAK_BF16_TFLOPS, 4),
-                     **profiled_traffic("qkv_proj", slow[0],
+                     **profiled_traffic("qkv_proj", slow[0], "projection_gemm_kernel",
                                         "projection_gemm_kernel_trace_and_counters.txt")}}))
 
 
@@ -594,6 +601,7 @@ def bench_projection_bwd(args):
         ven[name] = {"median_ms": round(ts[1], 3), "tflops": round(fl / (ts[1] * 1e-3) / 1e12, 1)}
     slow = min(per, key=lambda k: per[k]["tflops"])
     achieved = per[slow]["tflops"]
+    symbol = "linear_wgrad_large_kernel" if slow == "dweight" else "projection_gemm_kernel"
     print(json.dumps({
         "metric": "projection_backward_tflops", "value": round(2 * fl / (step_ms * 1e-3) / 1e12, 1),
         "unit": "TFLOP/s", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
@@ -602,11 +610,10 @@ def bench_projection_bwd(args):
         "config": {"workload": "qkv_proj_bwd: %d token rows, %d channels, %d features: dx = dy W "
                                "(bf16) and dW = dy^T x (fp32)" % (n, C, F), "kernels": per,
                    "vendor_gemm_same_products": ven},
-        "roofline": {"kernel": "%s (%s)" % ("linear_wgrad_large_kernel" if slow == "dweight"
-                                            else "projection_gemm_kernel", slow), "bound": "mfma",
+        "roofline": {"kernel": "%s (%s)" % (symbol, slow), "bound": "mfma",
                      "achieved": achieved, "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
                      "frac": round(achieved / PEAK_BF16_TFLOPS, 4),
-                     **profiled_traffic("qkv_proj_bwd", slow,
+                     **profiled_traffic("qkv_proj_bwd", slow, symbol,
                                         "projection_gemm_kernel_trace_and_counters.txt")}}))
 
 

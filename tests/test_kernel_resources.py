@@ -1,6 +1,7 @@
 """No kernel of the built library keeps registers in scratch memory: a reload inside a main loop waits
 behind the copies in flight and undoes their overlap with the products.  Read from the metadata that
 the compiler writes into the code objects of this library."""
+import os
 import struct
 
 import pytest
@@ -40,11 +41,34 @@ def kernel_metadata(elf):
             pos = desc + (desc_size + 3) // 4 * 4
 
 
-def test_no_kernel_uses_scratch_memory():
+def library_kernels():
     with open(build.LIB, "rb") as f:
         blob = f.read()
-    kernels = [k for elf in code_objects(blob) for k in kernel_metadata(elf)]
+    return [k for elf in code_objects(blob) for k in kernel_metadata(elf)]
+
+
+def test_no_kernel_uses_scratch_memory():
+    kernels = library_kernels()
     assert sum("winattn_dkdv" in k[".name"] for k in kernels) == 10   # two at 32, 64, 128, pipelined
     bad = {k[".name"]: (k[".private_segment_fixed_size"], k[".vgpr_spill_count"]) for k in kernels
            if k[".private_segment_fixed_size"] or k[".vgpr_spill_count"]}
     assert not bad
+
+
+def test_bench_and_profiles_name_kernels_of_the_library():
+    """bench.py names the kernels that run, and attaches to a kernel only the traffic that a profile
+    recorded of it: both by names that the library has."""
+    import bench
+    names = [k[".name"] for k in library_kernels()]
+    has = lambda kernel: any("%d%s" % (len(kernel), kernel) in n for n in names)     # a mangled name
+    assert not has("norm_fold") and has("norm_fold_kernel")
+    for plan in ((0, 1), (0, 2), (0, 3), (1, 0), (3, 0), (2, 2)):
+        for stage in ("fwd", "bwd", "dq", "dkdv"):
+            assert all(has(k) for k in bench.kernel_symbol(stage, plan).split(" + ")), (stage, plan)
+    folder = os.path.join(bench.ROOT, "profiles")
+    lines = [line.split() for name in sorted(os.listdir(folder)) for line in open(os.path.join(folder, name))]
+    traffic = [f for f in lines if f and f[0] == "TRAFFIC"]
+    assert traffic
+    for f in traffic:
+        assert len(f) == 5 and has(f[3]) and float(f[4]) > 0, f
+        assert bench.profiled_traffic(f[1], f[2], "another_kernel") == {"traffic": None}
