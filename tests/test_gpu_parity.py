@@ -217,20 +217,26 @@ def test_every_pair_has_one_workgroup(shape, win):
 
 
 @pytest.mark.parametrize("heads,d,win", [
-    (2, 32, (31, 1)), (2, 32, (8, 4)),        # from 32 tokens: dQ and dK/dV
-    (2, 32, (13, 3)), (3, 32, (8, 5)),        # from 40: the forward kernel too
+    (2, 32, (31, 1)), (2, 32, (8, 4)),        # held whole, few bytes: pairs dealt one by one
+    (2, 32, (13, 3)), (3, 32, (8, 5)),
+    (3, 32, (12, 16)), (3, 32, (1, 193)),     # 192 tokens held whole, 193 streamed
     (3, 32, (16, 16)), (3, 32, (13, 20)),     # up to 256: the forward kernel
     (2, 32, (24, 24)), (2, 32, (20, 29)),     # up to 576: the others
-    (1, 32, (8, 8)),                          # one head: never
-    (16, 32, (8, 8)),
-    (8, 64, (5, 7)), (8, 64, (6, 6)),         # rows of a multiple of 1 KB: from 36 tokens
+    (1, 32, (8, 8)), (1, 32, (14, 14)),       # one head: never
+    (16, 32, (8, 8)), (16, 32, (14, 14)),
+    (8, 64, (5, 7)), (8, 64, (6, 6)),
+    (8, 64, (8, 12)), (8, 64, (1, 97)),       # rows of a multiple of 1 KB: forward streamed from 97 to 128
+    (8, 64, (8, 16)), (8, 64, (3, 43)),
+    (8, 64, (12, 12)), (8, 64, (5, 29)),      # 144, backward streamed from 145
+    (8, 64, (12, 16)), (8, 64, (1, 193)),     # 192, both streamed from 193
     (8, 64, (20, 20)), (8, 64, (18, 23)),     # up to 400: the forward kernel
     (8, 64, (28, 28)), (8, 64, (28, 29)),     # up to 784: the others
     (4, 128, (8, 16)), (4, 128, (43, 3)),     # from 129 tokens
     (4, 128, (28, 28)), (4, 128, (28, 29)),   # up to 784
 ])
 def test_whole_windows_dealt_to_an_xcd(heads, d, win):
-    """The edges of the ranges in which whole windows, eight of these nine, are dealt to XCDs."""
+    """The edges of the ranges in which the streamed kernels have whole windows, eight of these nine, dealt to
+    XCDs, and of the windows that reach those kernels at all."""
     run_case((1, win[0], win[1] * 9, heads, d), win, (win[0] // 2, win[1] // 2), B.AERIS_MASK_SWIN, seed=57)
 
 
@@ -249,15 +255,21 @@ def test_whole_short_windows_dealt_to_an_xcd(shape, win):
     run_case(shape, win, (win[0] // 2, win[1] // 2), B.AERIS_MASK_SWIN, seed=59, outs=(B.AERIS_DT_F32,))
 
 
-@pytest.mark.parametrize("shape,win", [
-    ((1, 16, 16, 3, 32), (8, 8)),           # one streamed tile
-    ((1, 26, 15, 3, 32), (13, 5)),          # 65 tokens, 18 workgroups
-    ((1, 104, 160, 3, 32), (13, 5)),        # 768 workgroups
-    ((1, 104, 170, 3, 32), (13, 5)),        # 816
+@pytest.mark.parametrize("shape,win,kernel", [
+    ((1, 16, 16, 3, 32), (8, 8), 0),          # 64 tokens: one kernel for all three gradients
+    ((1, 26, 15, 3, 32), (13, 5), 0),
+    ((1, 104, 160, 3, 32), (13, 5), 0),
+    ((1, 104, 170, 3, 32), (13, 5), 0),
+    ((1, 28, 42, 3, 32), (14, 14), 1),        # 196 tokens, 48 workgroups
+    ((1, 112, 224, 3, 32), (14, 14), 1),      # 768
+    ((1, 112, 238, 3, 32), (14, 14), 2),      # 816
+    ((1, 160, 260, 2, 32), (20, 20), 2),      # 400 tokens, 832
 ])
-def test_head_dim_32_dkdv_by_window_and_grid_size(shape, win):
-    """Both orders of reads of the dK/dV kernel, at the edges of their rule."""
-    run_case(shape, win, (win[0] // 2, win[1] // 2), B.AERIS_MASK_SWIN, seed=58)
+def test_head_dim_32_dkdv_by_window_and_grid_size(shape, win, kernel):
+    """Both orders of reads of the dK/dV kernel, at the edges of their rule, and the windows below it."""
+    shift = (win[0] // 2, win[1] // 2)
+    assert B.aeris_winattn_plan(B.make_params(shape, win, shift, B.AERIS_MASK_SWIN))[1] == kernel
+    run_case(shape, win, shift, B.AERIS_MASK_SWIN, seed=58)
 
 
 @pytest.mark.parametrize("win", [(2, 2), (12, 16), (13, 15), (28, 64), (33, 55)])
@@ -379,8 +391,25 @@ def test_maximum_window_tokens(d):
              outs=(B.AERIS_DT_BF16,))
 
 
-def test_packed_qkv_strides():
-    shape, win, shift, mask = (1, 24, 24, 2, 64), (12, 12), (6, 6), B.AERIS_MASK_SWIN
+@pytest.mark.parametrize("d,win,windows,plan", [
+    (64, (12, 12), (2, 2), (3, 0)),       # window and head whole, forward and backward; three share the queries
+    (32, (9, 16), (2, 3), (3, 0)),
+    (128, (8, 8), (2, 3), (1, 0)),
+    (64, (10, 10), (2, 3), (0, 0)),       # forward streamed
+    (32, (14, 14), (2, 3), (0, 1)),       # streamed; dK/dV with its operands read first
+    (64, (14, 17), (2, 3), (0, 1)),       # dQ of 238 tokens: a second, partly filled resident tile
+    (32, (16, 16), (10, 20), (0, 2)),     # one block ahead
+    (128, (9, 9), (2, 3), (2, 2)),        # dK/dV one block ahead, forward whole
+    (128, (17, 17), (2, 3), (0, 2)),
+    (128, (33, 55), (1, 2), (0, 3)),      # 1815 tokens: pipelined
+    (64, (46, 45), (1, 2), (0, 1)),       # 2070: forward tiles of 256 queries
+    (128, (46, 45), (2, 1), (0, 3)),
+])
+def test_packed_qkv_strides(d, win, windows, plan):
+    """Queries, keys and values interleaved per token, and their gradients in the same packing, in every
+    kernel that a window can take: a row of a token is three times as far
+    from the next as its heads are, and each kernel makes these addresses for itself."""
+    shape, shift, mask = (1, win[0] * windows[0], win[1] * windows[1], 2, d), (win[0] // 2, win[1] // 2), B.AERIS_MASK_SWIN
     Bn, H, W, nh, d = shape
     bits = synth.make_inputs("normal", 5, shape, 4)
     q64, k64, v64, do64 = [synth.bf16_bits_to_f64(b) for b in bits]
@@ -390,6 +419,7 @@ def test_packed_qkv_strides():
     o = torch.empty(shape, dtype=torch.bfloat16, device="cuda")
     lse = torch.empty((Bn, nh, H, W), dtype=torch.float32, device="cuda")
     p = B.make_params(shape, win, shift, mask, qkv_strides=(3 * nh * d, d))
+    assert B.aeris_winattn_plan(p) == plan
     import ctypes
     lib = B.load()
     esz = 2

@@ -179,13 +179,20 @@ def test_rope_seeded_sweep_of_small_shapes():
                       outs=(out,))
 
 
-def test_rope_attention_on_packed_qkv_is_bitwise_the_contiguous_result():
+@pytest.mark.parametrize("d,win,windows", [
+    (64, (12, 12), (2, 3)),                                     # a window and head whole in a workgroup
+    (64, (20, 20), (2, 3)),                                     # streamed
+    (32, (20, 20), (10, 10)),                                   # dK/dV with operands one block ahead
+    (128, (20, 20), (1, 2)), (128, (46, 45), (1, 1)),           # 2070 tokens: pipelined dK/dV, wide forward tiles
+])
+def test_rope_attention_on_packed_qkv_is_bitwise_the_contiguous_result(d, win, windows):
     """Queries, keys and values interleaved per token, as a fused QKV projection writes them
     ([B,H,W,3,heads,d]), gradients written into the same packing: the rotary entry points must
     give exactly what they give on separate contiguous tensors (which the cases above hold to the
     oracle)."""
     import ctypes
-    shape, win, shift, mask = (2, 24, 36, 3, 64), (12, 12), (6, 6), B.AERIS_MASK_SWIN
+    shape = (2, win[0] * windows[0], win[1] * windows[1], 3, d)
+    shift, mask = (win[0] // 2, win[1] // 2), B.AERIS_MASK_SWIN
     Bn, H, W, nh, d = shape
     bits = synth.make_inputs("normal", 4300, shape, 4)
     tq, tk, tv, tdo = [to_dev(b) for b in bits]

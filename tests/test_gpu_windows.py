@@ -111,12 +111,13 @@ def test_share_of_short_windows_equals_whole_bitwise(win, d, out):
     assert np.abs(to_f64(lse) - lse_ref).max() <= LSE_ABS
 
 
+@pytest.mark.parametrize("win,d", [((12, 12), 64), ((15, 16), 32), ((15, 16), 64), ((15, 16), 128)])   # 240: streamed
 @pytest.mark.parametrize("mode", [B.AERIS_ROPE_POS_WINDOW, B.AERIS_ROPE_POS_GRID])
-def test_rotary_attention_on_a_window_subset(mode):
+def test_rotary_attention_on_a_window_subset(mode, win, d):
     """A rank's share with the rotary embedding: inside the listed windows the result matches the
     fp64 rotary oracle of the whole grid (and is bit for bit that of the full-grid rotary calls);
     nothing outside them is written, and q, k outside them are never read (NaN there)."""
-    shape, win, shift, mask = (2, 36, 72, 2, 64), (12, 12), (6, 6), B.AERIS_MASK_SWIN
+    shape, shift, mask = (2, 3 * win[0], 6 * win[1], 2, d), (win[0] // 2, win[1] // 2), B.AERIS_MASK_SWIN
     Bn, H, W, nh, d = shape
     picks = [17, 0, 5, 11, 6]          # corner, seam and interior windows of the 3 x 6 grid
     bits = synth.make_inputs("normal", 6003, shape, 4)
