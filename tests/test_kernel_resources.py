@@ -55,6 +55,17 @@ def test_no_kernel_uses_scratch_memory():
     assert not bad
 
 
+def test_scalar_registers_are_spilled_outside_of_step_loops_only():
+    """Scalar values that do not fit are parked in lanes of a vector register.  The three kernels that do so
+    fetch them before the loop over steps, per output tile (projection_gemm_kernel) or in the last steps of
+    a row range (linear_wgrad_large_kernel), never in the loop that a workgroup spends its time in: read
+    from their assembly with these counts.  More of them, or another kernel, has to be looked at again."""
+    looked_at = {"projection_gemm_kernel": 7, "linear_wgrad_large_kernel": 14, "winattn_bwd_short_kernelILi128E": 6}
+    spills = {k[".name"]: k[".sgpr_spill_count"] for k in library_kernels() if k[".sgpr_spill_count"]}
+    more = {n: c for n, c in spills.items() if c > max((v for k, v in looked_at.items() if k in n), default=0)}
+    assert not more
+
+
 def test_bench_and_profiles_name_kernels_of_the_library():
     """bench.py names the kernels that run, and attaches to a kernel only the traffic that a profile
     recorded of it: both by names that the library has."""
