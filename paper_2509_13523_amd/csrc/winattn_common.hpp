@@ -120,22 +120,26 @@ inline int whole_windows(const KParams& p, AttnKernel kernel, int head_dim) {
 }
 // The same for the kernels that hold a window and head whole.  Workgroups of the shortest windows live for a
 // few microseconds and the longer way to the work item shows; and rows have to come from behind the caches
-// that would hide the double fetch (head_dim 32) or the crowding (64).  Ratios of times as above, by the bytes
-// of all inputs and outputs:
-//   head_dim 32, 2 to 16 heads  1-8 tokens  9          12-64      81-169
-//     forward, > 24 MB          0.95-1.11   0.87-1.08  0.63-0.96  0.67-0.91
-//     backward, > 24 MB         0.86-1.02   0.82-0.94  0.73-0.88  0.72-0.94
-//     both, < 24 MB             0.99-1.08   0.99-1.07  0.99-1.08  0.98-1.03
+// that would hide the double fetch (head_dim 32) or the crowding (64).  Ratios of times as above with forward
+// and backward calls in turn, by the bytes of all inputs and outputs of the kernel (in a training pass rows have
+// left the last-level cache at a size at which the forward kernel alone, called again and again, still finds
+// them there: head_dim 64, 12 x 12 windows, 265 MB 0.93 in turn, 1.02 alone):
+//   head_dim 32, 2 to 16 heads  4 tokens    9          16-64      100-192
+//     forward, > 24 MB          1.07-1.09   0.87-1.08  0.64-0.95  0.73-0.97
+//     backward, > 24 MB         0.99-1.02   0.80-0.95  0.72-0.89  0.73-0.93
+//     both, < 24 MB             0.98-1.07   0.96-1.05  0.86-1.05  0.85-1.04
 //   head_dim 64, 8 and 16 heads
-//     forward, > 400 MB         0.97-1.05   0.90-0.91  0.80-0.90  0.83-0.96
-//     backward, > 400 MB        0.98-1.02   0.97-0.98  0.84-1.01  0.89-1.05
-//     both, < 400 MB            1.01-1.07   1.02-1.07  0.96-1.07  0.98-1.06
-//   head_dim 128, 2 to 16 heads, forward 0.92-1.05, backward 0.98-1.12; other head counts at 64, and one head of
+//     forward, > 150 MB         1.04-1.06   0.91-1.02  0.83-0.96  0.91-1.01
+//     forward, < 150 MB         1.01-1.06   0.97-1.05  0.98-1.09  0.99-1.05
+//     backward, > 400 MB        1.01        0.97-0.99  0.94-1.00  0.93-1.01
+//     backward, < 400 MB        1.00-1.02   1.00-1.03  0.98-1.04  0.93-1.02
+//   head_dim 128, 4 and 8 heads, forward 0.94-1.03, backward 1.00-1.10; other head counts at 64, and one head of
 //   32: 0.94-1.06.
 inline int whole_short_windows(const KParams& p, AttnKernel kernel, int head_dim) {
   const bool forward = kernel == AttnKernel::kForward;
   const double bytes = (double)p.n_pairs * p.T * head_dim * 2.0 * (forward ? 4.0 : 8.0);
-  const bool pays = head_dim < 128 && p.T >= (forward ? 12 : 9) && bytes > (head_dim == 32 ? 24e6 : 400e6);
+  const double least = head_dim == 32 ? 24e6 : forward ? 150e6 : 400e6;
+  const bool pays = head_dim < 128 && p.T >= (forward ? 12 : 9) && bytes > least;
   return pays && rows_meet(p, head_dim) ? (p.B * p.n_win) & ~7 : 0;
 }
 __device__ __forceinline__ bool block_to_work(const KParams& p, int& pair, int& tile) {
