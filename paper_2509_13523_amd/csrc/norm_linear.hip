@@ -730,21 +730,24 @@ int launch_gemm_shape(const GemmParams& p, hipStream_t stream) {
 // round takes (microseconds: a fixed part plus a part per 64-channel step, less of both for a last
 // round that leaves CUs empty).  Medium tiles fetch the rows twice as often as large ones, which
 // counts once rows and results exceed the last-level cache (300000 x 192 -> 576 145 us with large
-// tiles, 161 with medium ones; 60000 x 192 -> 1408 67 / 58) and rows are a good part of the bytes: hardly with
-// 64 channels, whose large tiles of a single step overlap nothing (699334 x 64 -> 896 352 / 286, 170130 x 64 ->
-// 2368 199 / 185).  Fitted to 200 sizes of 1500 ... 150000 rows, 64 ... 5760 channels and 128 ... 6400 features; at
-// 300 others (1500 ... 1230689 rows, 64 ... 3840 channels, 64 ... 6976 features) what it takes is 0.7 % slower than
-// the better shape on average, more than 5 % at 20 of them, most with up to 192 channels, where one round of
-// large tiles takes 1.2 us longer than estimated.  Small tiles have the shortest steps and are taken as long
+// tiles, 161 with medium ones; 60000 x 192 -> 1408 67 / 58).  With 64 channels a large tile is a single step that
+// overlaps nothing: medium tiles were the faster ones at all sizes of more than one round of large tiles (large /
+// medium 9165 x 64 -> 2944 21.2 / 19.1, 105886 x 64 -> 192 19.4 / 18.0, 26387 x 64 -> 6144 82.7 / 77.0, 699334 x 64 ->
+// 896 352 / 286), and by up to 5 % below.  Fitted to 200 sizes of 1500 ... 150000 rows, 64 ... 5760 channels and 128
+// ... 6400 features; at 417 others (700 ... 200000 rows, 64 ... 2048 channels, 64 ... 6400 features, operands in the
+// last-level cache and out of it) what it takes is 1 % slower than the best shape on average, more than 5 % at 22
+// of them.  Small tiles have the shortest steps and are taken as long
 // as each has a CU of its own: 914 rows x 1600 -> 512 takes 8.2 us with small, 12.7 with medium tiles, 1759 x
 // 640 -> 1344 (588 small tiles) 11.0 and 7.8.  Medium tiles win while large ones leave more than about half
 // of the CUs without work (9522 x 2944 -> 704, 114 large tiles: 41 / 57), large ones, with half the operand
 // bytes per product, from there on (148, 18926 x 2560 -> 512: 70 / 53; 150, 12738 x 5248 -> 704: 133 / 99;
 // 172800 x 2048 -> 2048: 1391 / 1097).
 enum class GemmTile { kLarge, kMedium, kSmall };
+constexpr long long kNoTiles = 1LL << 40;   // of a count that does not fit a launch: rules the finer tiles out
 GemmTile choose_gemm_tile(long long large_tiles, long long medium_tiles, long long small_tiles, int steps,
                           bool cached) {
   if (small_tiles <= (long long)kCus) return GemmTile::kSmall;
+  if (steps == 1 && large_tiles > (long long)kCus && medium_tiles < kNoTiles) return GemmTile::kMedium;
   // one large workgroup per CU, two medium ones
   const double large_rest = (double)(large_tiles % kCus) / kCus;
   const double large = (double)(large_tiles / kCus) * (5.7 + 1.45 * steps) +
@@ -752,7 +755,7 @@ GemmTile choose_gemm_tile(long long large_tiles, long long medium_tiles, long lo
   const double medium_rest = (double)(medium_tiles % (2 * kCus)) / (2 * kCus);
   const double medium = (double)(medium_tiles / (2 * kCus)) * (2.5 + 0.93 * steps) +
                         (medium_rest > 0.0 ? 4.8 + steps * (0.42 + 0.45 * medium_rest) : 0.0);
-  return medium * (cached ? 1.0 : steps == 1 ? 1.05 : 1.2) < large ? GemmTile::kMedium : GemmTile::kLarge;
+  return medium * (cached ? 1.0 : 1.2) < large ? GemmTile::kMedium : GemmTile::kLarge;
 }
 
 }  // namespace
@@ -763,9 +766,7 @@ namespace {
 bool plan_gemm(GemmParams& p, GemmTile& tile) {
   GemmParams large = p, medium = p, small = p;
   if (!gemm_tiles<GemmLarge>(large)) return false;
-  // a count that does not fit a launch rules the finer tiles out
-  constexpr long long kNone = 1LL << 40;
-  auto tiles = [](bool fits, const GemmParams& q) { return fits ? (long long)q.m_tiles * q.n_tiles : kNone; };
+  auto tiles = [](bool fits, const GemmParams& q) { return fits ? (long long)q.m_tiles * q.n_tiles : kNoTiles; };
   const bool cached = (double)p.n_samples * p.rows_per_sample * ((double)p.K + p.F) * 2.0 <= 256e6;
   tile = choose_gemm_tile(tiles(true, large), tiles(gemm_tiles<GemmMedium>(medium), medium),
                           tiles(gemm_tiles<GemmSmall>(small), small), p.K / kBK, cached);

@@ -170,9 +170,10 @@ def test_projections_with_every_tile_shape(n_samples, rows, channels, features, 
 def test_workgroups_that_walk_over_several_tiles(channels):
     """432 tiles of 256 x 256 for 256 CUs, ragged both ways, two samples: with two steps or more a
     workgroup fetches into its next tile while it works on the last steps of one, and stages results
-    in the operand stage that it has just left."""
+    in the operand stage that it has just left.  A single step has nothing to fetch into: 1680 or 1645 tiles of
+    128 x 128, one workgroup each."""
     n_samples, rows, features = 2, 2990, 4400
-    assert B.aeris_projection_plan(n_samples * rows, rows, channels, features)[0] == 256
+    assert B.aeris_projection_plan(n_samples * rows, rows, channels, features)[0] == (128 if channels == 64 else 256)
     test_linear_fwd(n_samples * rows, channels, features)
     test_norm_linear_fwd(n_samples, rows, channels, features)
     test_norm_linear_swiglu_fwd(n_samples, rows, channels, features // 2)
